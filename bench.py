@@ -739,7 +739,8 @@ def chain_bench(args, cfg, runs, ft, torch):
     return 0 if ok_fault else 1
 
 
-CONV_SOURCES = ("conv_mfma.hip", "ftcnn_internal.h", "coc_tile.h", "encode_block.h")
+CONV_SOURCES = ("conv_mfma.hip", "conv_kernel.h", "conv_launch.h", "conv_tiles.h", "ftcnn_internal.h",
+                "coc_tile.h", "encode_block.h")
 
 
 def conv_source_hash():
@@ -811,7 +812,7 @@ def cpu_baseline(cfg, seconds):
 # ---- rocprofv3 summaries (no GPU work) --------------------------------------------------------
 
 def _short(name):
-    s = name.replace("ftcnn::(anonymous namespace)::", "").replace("ftcnn::", "")
+    s = name.replace("ftcnn::(anonymous namespace)::", "").replace("ftcnn::", "").replace("convk::", "")
     if s.startswith("void "):
         s = s[5:]
     depth = 0

@@ -1,0 +1,163 @@
+// The tiles of the convolution kernel (conv_kernel.h) and the arguments of their launches.
+#pragma once
+
+#include <type_traits>
+
+#include "ftcnn_internal.h"
+#include "encode_block.h"
+#include "coc_tile.h"
+
+namespace ftcnn {
+namespace convk {
+
+// Element-type traits: fp32 uses v_mfma_f32_32x32x2_f32 (2 k per instruction),
+// bf16 uses v_mfma_f32_32x32x16_bf16 (16 k per instruction).  TK_ is the k
+// extent of one LDS chunk; rows are padded by 16 bytes against bank conflicts.
+template <int TK_> struct F32T {
+    using T = float;
+    static constexpr int TK = TK_;
+    static constexpr int LDK = TK_ + 4;
+    static constexpr int VEC = 4;      // elements per 16-byte load
+    static constexpr int NP = 1;
+};
+template <int TK_> struct BF16T {
+    using T = uint16_t;
+    static constexpr int TK = TK_;
+    static constexpr int LDK = TK_ + 8;
+    static constexpr int VEC = 8;
+    static constexpr int NP = 1;       // bf16 planes of an operand in the direct-to-LDS loop
+};
+
+// DSTAGES > 0: the direct-to-LDS loop with that many stages of (TM + TP) rows of ROWB bytes.
+template <typename Tr, int WM, int WP, int FM, int FP, bool KVEC_ = true, int DSTAGES = 0>
+struct Cfg {
+    using T = typename Tr::T;
+    static constexpr bool KVEC = KVEC_;   // W rows 16-byte aligned: whole-slot weight loads
+    static constexpr int NT = 64 * WM * WP;
+    static constexpr int TM = WM * FM * 32;
+    static constexpr int TP = WP * FP * 32;
+    static constexpr int TK = Tr::TK;
+    static constexpr int LDK = Tr::LDK;
+    static constexpr int VEC = Tr::VEC;
+    static constexpr int A_SLOTS = TM * TK / VEC;                    // 16-byte slots of the A tile
+    static constexpr int A_PER = (A_SLOTS + NT - 1) / NT;
+    static constexpr int KG = NT / TP;                               // threads per pixel along k
+    static constexpr int KR = TK / KG;                               // k per thread in the gather
+    static_assert(NT % TP == 0 && TK % KG == 0 && KR % VEC == 0, "tile shape");
+    static_assert(KR <= 64 && A_PER * VEC <= 64, "gather masks are at most 64-bit");
+    // one bit per gathered element of a thread
+    using Mask = typename std::conditional<(KR > 32 || A_PER * VEC > 32), uint64_t, uint32_t>::type;
+    static constexpr int ROWB = TK * 2 * Tr::NP;
+    static constexpr size_t LDS_BYTES = DSTAGES > 0 ? (size_t)DSTAGES * (TM + TP) * ROWB
+                                                    : 2ull * (TM + TP) * LDK * sizeof(T);
+    static_assert(LDS_BYTES <= 160 * 1024, "tile exceeds the LDS of a CU");
+};
+
+// Epilogue arguments.  EPI 0: plain store.  EPI 1: the CoC-D summations of
+// every stored value as well (Sec. 3.6): for each pixel p of the tile, the tile's
+// rows give sum O, sum (m + wbase) O, (n + wbase) sum O and sum O^2, written as
+// slice (tile_m * N + n) of a [slices][4][E*F] float64 array; block 0 resets the
+// report.  EPI 2: EPI 1 with faults planted in the stored values first.
+// With EPI 1 and 2, aux_groups groups of eight consecutive workgroup ids (one per
+// XCD) may do other work of the protected layer instead of a tile, memory-bound work
+// that runs beside the matrix-bound tiles of the same launch:
+//   aux_kind 1: encode the input checksums Cd1, Cd2 of D (Sec. 3.2), in the first
+//               groups of the grid (they read D as the first tiles do);
+//   aux_kind 2: combine the image-split partials of Cd1, Cd2 left by the
+//               channels-last copy, and compute the Co5..Co7 partial products
+//               (coc_tile.h), in the last groups, after the tile_groups groups of
+//               tiles, where they fill the slots the tiles' last round leaves.
+struct NoFaults {};
+// Stream-K schedule of the channels-last loops (S > 0): the launch has S workgroups (after the
+// extra ones), as many as are resident at once.  The first dp_waves x S tiles run whole, tile
+// r S + w being workgroup w's r-th, so that the workgroups resident together work on neighbouring
+// tiles, as in the plain grid.  The last one to two waves' tiles (T of them) are shared evenly:
+// workgroup w runs their iterations [w U / S, (w + 1) U / S) of the U = T x nch (tile, chunk)
+// pairs in tile order.  A tile whose chunks span several workgroups is summed by the last of them
+// to arrive: each writes its partial accumulators to a slot (0: the workgroup's first shared
+// segment, 1: its last), counts itself in cnt[tile], and the last adds the slots in chunk order (a
+// fixed order, whichever workgroup is last) before the epilogue.
+struct SkArgs {
+    float *part;    // [S][2][TM * TP]
+    int *cnt;       // [tiles], zero at the launch (the channels-last copy clears it); left zero
+    int S;          // 0: one tile per workgroup
+    int nch;        // chunks per tile
+    int dp_waves;   // waves of whole tiles before the shared ones
+};
+template <int EPI> struct Epi {
+    double *part;
+    ftcnn_report *rep;
+    int cap;
+    int aux_kind, aux_blocks, aux_groups;
+    int tile_groups;     // groups of eight tile workgroups in front of the aux_kind 2 ones
+    double *cd1, *cd2;   // kind 1: encoded here; kind 2: written by the combine workgroups
+    int enc_vec;         // kind 1: 16-byte loads
+    CdSrc src;           // kind 2
+    const double *cw1, *cw2;
+    double *copart;
+    CocTile co;
+    int co_slices;       // Co partial slices this launch writes (recorded in rep->reserved[1])
+    typename std::conditional<EPI == 2, FaultList, NoFaults>::type fl;
+    const float *bias;   // NULL, or [M] added to every stored value of filter m (Sec. 5.1)
+};
+template <> struct Epi<0> {
+    const float *bias;
+};
+
+// One tile configuration.  WEAVE: the main loop (0 register-staged, 1 gather woven between the
+// MFMAs, 2 two chunks in flight, 3 direct-to-LDS).  run() and stream_k() are instantiated per tile
+// in the conv_*.hip files.
+template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE> struct Tile {
+    static constexpr int TM = WM * FM * 32;
+    static constexpr int TP = WP * FP * 32;
+    static constexpr int TK = Tr::TK;
+    static constexpr int WEAVE_KIND = WEAVE;
+    static constexpr int NT = Cfg<Tr, WM, WP, FM, FP>::NT;
+    static constexpr size_t LDS_BYTES = Cfg<Tr, WM, WP, FM, FP, true, (WEAVE >= 3 ? WEAVE - 1 : 0)>::LDS_BYTES;
+    static constexpr bool SK_FORM = WEAVE != 2 && sizeof(typename Tr::T) == 4;
+    // stream-K workgroups of the channels-last form on the current device (0: whole tiles)
+    static int stream_k(const Geom &g, int smax);
+    // NCHW: D and W as given; NHWC: the channels-last copies Dt and Wt (always aligned, K % VEC == 0)
+    template <int EPI>
+    static hipError_t run(const Geom &g, const void *D, const void *W, void *O, hipStream_t st, const Epi<EPI> &ep,
+                          bool nhwc = false, const void *zp = nullptr, const SkArgs &sk = SkArgs{nullptr, nullptr, 0, 0, 0});
+};
+
+using F32_M32 = Tile<F32T<16>, 1, 4, 1, 2, true>;
+using F32_M64 = Tile<F32T<16>, 2, 2, 1, 2, true>;
+using F32_64x256 = Tile<F32T<16>, 1, 4, 2, 2, true>;   // channels-last M <= 64: 64 x 64 a wave
+using F32_M96 = Tile<F32T<16>, 1, 4, 3, 1, true>;   // 96 x 128: AlexNet conv1 gets 1513 tiles, 3 full rounds
+using F32_128x128 = Tile<F32T<16>, 2, 2, 2, 2, true>;
+using F32_128x128_K32 = Tile<F32T<32>, 2, 2, 2, 2, true>;   // 32-deep chunks: half the barriers
+using F32_128x64 = Tile<F32T<32>, 2, 2, 2, 1, true>;
+using F32_64x64 = Tile<F32T<32>, 2, 2, 1, 1, true>;
+using BF16_M32 = Tile<BF16T<32>, 1, 4, 1, 2, 0>;
+using BF16_M64 = Tile<BF16T<32>, 1, 4, 2, 2, 2>;
+using BF16_128x128_K64 = Tile<BF16T<64>, 2, 2, 2, 2, 2>;
+using BF16_256x256 = Tile<BF16T<32>, 2, 2, 4, 4, 2>;
+using BF16_DMA_128x128 = Tile<BF16T<64>, 2, 2, 2, 2, 3>;
+// four waves of 64 x 32, a 48 KB ring (three workgroups a compute unit): for layers with fewer
+// 128 x 128 tiles than compute units (VGG-19 v13-v16 and ResNet-18 layer4, 196 tiles: 63.5 -> 55.5
+// us a layer unprotected); where it only adds a partly filled round it is slower (ResNet-18 l3
+// 49 -> 62 us, l2 62 -> 65 us)
+using BF16_DMA_128x64 = Tile<BF16T<64>, 2, 2, 2, 1, 3>;
+// M <= 64: four waves of 64 x 32, a 48 KB ring, three workgroups a compute unit (against 64 x 256
+// tiles of four 64 x 64 waves, two a compute unit: ResNet-18 l1 89 -> 79 us, VGG-19 v2 299 -> 287 us
+// with the channels-last copy; 64 x 64 tiles of two waves, 64 x 128 of two waves and deeper rings
+// were slower)
+using BF16_DMA_64x128 = Tile<BF16T<64>, 1, 4, 2, 1, 3>;
+// eight waves of 128 x 64 (two a SIMD, accumulators in 128 registers a lane): against four waves
+// of 128 x 128 (one a SIMD) 5-8 % faster on VGG-19 bf16 v5-v12, which also beat 128 x 128 tiles
+using BF16_DMA_256x256 = Tile<BF16T<64>, 2, 4, 4, 2, 3>;
+
+// Stream-K pays (the partial writes and the last workgroup's sums of a split tile) where a plain
+// grid of whole tiles would leave its last round of S resident workgroups partly idle, and where
+// every workgroup still has a long run of chunks.
+inline bool use_stream_k(long long tiles, int S, int nch) {
+    if (tiles * nch < 32LL * S) return false;   // under 32 chunks a workgroup
+    const long long rounds = (tiles + S - 1) / S;
+    return tiles * 100 < rounds * S * 90;       // the whole-tile grid would use < 90 % of its slots
+}
+
+}  // namespace convk
+}  // namespace ftcnn

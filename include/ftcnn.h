@@ -180,7 +180,8 @@ const char *ftcnn_last_error(void);
  * that takes a workspace (ftcnn_conv_fwd_ws, ftcnn_conv_fwd_sums, ftcnn_protected_conv,
  * ...).  out[0] = filters (rows of W) per workgroup tile, out[1] = output pixels per tile,
  * out[2] = k per LDS chunk, out[3] = main loop (0 register-staged gather, 1 gather woven
- * between the matrix-core instructions, 2 two chunks in flight, 3 direct-to-LDS loads),
+ * between the matrix-core instructions, 2 two chunks in flight, 3 direct-to-LDS loads,
+ * 4 the same with three stages; an fp32 layer on 3 or 4 multiplies bf16 planes),
  * out[4] = 1 when the convolution reads channels-last copies, out[5] = 1 when its tiles
  * skip the channels of other groups (grouped layers).  Lets a test check that it covers
  * every kernel a set of layers runs. */
@@ -192,8 +193,8 @@ int ftcnn_conv_tile(const ftcnn_conv_desc *desc, int32_t path, int32_t out[6]);
  * schedule, not another operation: every workgroup takes an equal run of the layer's
  * (tile, chunk of K) pairs, and a tile whose chunks span several workgroups is summed by the
  * last of them to finish, in chunk order (so the protected convolution and its unprotected
- * twin store the same bits).  It is used for dense channels-last fp32 layers whose tile count
- * would leave the last round of resident workgroups less than 90 % busy. */
+ * twin store the same bits).  It is used for dense channels-last fp32 layers whose whole tiles
+ * would leave workgroups idle (in the last round, or all along) for longer than sharing takes. */
 int ftcnn_conv_stream_k(const ftcnn_conv_desc *desc, int32_t *workgroups);
 
 /* ---- device work -------------------------------------------------------- */
@@ -280,7 +281,9 @@ int ftcnn_verify_correct(const ftcnn_conv_desc *desc, const void *D, const void 
  * into the workspace (D as [n][h][w][ch], W as [m][r][s][ch]) so that the
  * convolution gathers 16-byte runs; K is then summed in (r, s, ch) order, so
  * O may differ from ftcnn_conv_fwd's in the last bits (both are eq. (1) with
- * fp32 accumulation).  O is bitwise that of ftcnn_conv_fwd_sums.  Other layers
+ * fp32 accumulation; fp32 copies hold every value as three bf16 planes whose sum it
+ * is, six of whose nine products the matrix cores add up, the other three being below
+ * an fp32 rounding of the product).  O is bitwise that of ftcnn_conv_fwd_sums.  Other layers
  * take ftcnn_conv_fwd's kernel.  Needs the workspace of ftcnn_workspace_bytes. */
 int ftcnn_conv_fwd_ws(const ftcnn_conv_desc *desc, const void *D, const void *W, void *O,
                       void *workspace, hipStream_t stream);

@@ -40,7 +40,9 @@ int row_splits(long long rows, long long col_blocks, long long target_blocks, lo
 
 // allow_nhwc = false: every convolution gathers from D as given (no channels-last copies in
 // the workspace), a plan with a smaller workspace for layers that would otherwise copy.
-int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool allow_sk = true) {
+// allow_split = false: fp32 copies stay fp32; allow_sk = false: no stream-K scratch.
+int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool allow_sk = true,
+              bool allow_split = true) {
     if (!d) return fail(FTCNN_E_ARG, "null descriptor");
     if (d->groups < 1 || d->ch % d->groups != 0 || d->m % d->groups != 0)
         return fail(FTCNN_E_SHAPE, "groups = %d must divide ch = %d and m = %d", d->groups, d->ch, d->m);
@@ -94,6 +96,7 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     pl->ver_splits = row_splits(rows_o, ceil_div(cols_v, ctt), 1024, 32);
     if (pl->ver_splits > part_cap) pl->ver_splits = part_cap > 1 ? (int)part_cap : 1;
     pl->nhwc = allow_nhwc && nhwc_layer(g);
+    g.split = pl->nhwc && allow_split && split_layer(g);
     // summations fused into the convolution epilogue: one slice per (filter tile, image)
     pl->sum_splits = (int)(ceil_div(g.M, conv_tile_m(g, pl->nhwc)) * g.N);
     // correction: the standalone launch hands the flagged positions over from at most corr_blocks
@@ -118,7 +121,7 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     // Cd1, Cd2 too, over image ranges when the layer has few tiles: enough ranges for about 1024
     // workgroups, with at least 16 images (fp32) or 32 (bf16) a range, so that the float64 partial
     // pairs (16 bytes per element of Cd) cost at most a quarter of D's traffic, and at most 16
-    const size_t es = g.dtype == FTCNN_F32 ? 4 : 2;
+    const size_t es = g.dtype == FTCNN_F32 ? 4 : 2, cs = copy_bytes(g);
     pl->prep_ns = 1;
     pl->co_in_conv = false;
     pl->co = CocTile{1, 1, 1, 1, 1, 1, 0, 1};
@@ -156,9 +159,9 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     pl->off_zero = off;
     off += pl->nhwc ? 256 : 0;
     pl->off_dt = off;
-    off += pl->nhwc ? align256((size_t)g.N * CHW * es) : 0;
+    off += pl->nhwc ? align256((size_t)g.N * CHW * cs) : 0;
     pl->off_wt = off;
-    off += pl->nhwc ? align256((size_t)g.M * K * es) : 0;
+    off += pl->nhwc ? align256((size_t)g.M * K * cs) : 0;
     pl->off_encp = off;
     off += pl->prep_ns > 1 ? align256(2ull * pl->prep_ns * CHW * sizeof(double)) : 0;
     pl->off_copart = off;
@@ -502,12 +505,14 @@ int ftcnn_protected_conv_noalloc(const ftcnn_conv_desc *desc, const void *D, con
                                  const ftcnn_checksums *ck, const ftcnn_policy *policy, ftcnn_report *rep,
                                  int32_t cap_fixes, hipStream_t stream) {
     // the plan of ftcnn_protected_conv when its workspace fits the static scratch, else that plan
-    // without the stream-K scratch (whole tiles per workgroup: K split at other places), else the
-    // plan without channels-last copies (K summed in (c, r, s) order instead of (r, s, c)); the
-    // last two give the same results within the output tolerance
+    // without the stream-K scratch (whole tiles per workgroup: K split at other places), else with
+    // fp32 copies instead of split ones (4 bytes a value instead of 6), else the plan without
+    // channels-last copies (K summed in (c, r, s) order instead of (r, s, c)); all of them give the
+    // same results within the output tolerance
     Plan pl;
     FT_TRY(make_plan(desc, &pl));
     if (pl.bytes > kStaticScratchBytes) FT_TRY(make_plan(desc, &pl, true, false));
+    if (pl.bytes > kStaticScratchBytes) FT_TRY(make_plan(desc, &pl, true, false, false));
     if (pl.bytes > kStaticScratchBytes) {
         FT_TRY(make_plan(desc, &pl, false));
         if (pl.bytes > kStaticScratchBytes)

@@ -428,6 +428,10 @@ __device__ inline void chunk_f32(const float *As, const float *Bs, int lane, int
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
+// Cache policy of buffer loads and stores that other XCDs' workgroups must see (the sc1 bit: device
+// scope, past this XCD's L2).
+constexpr int kDeviceCoherent = 16;
+
 // s_waitcnt: at most V vector-memory operations of this wave outstanding.
 template <int V> __device__ inline void wait_vmcnt() {
     static_assert(V >= 0 && V < 64, "vmcnt is six bits");
@@ -462,7 +466,7 @@ __device__ inline unsigned tap_mask(const Geom &g, int ih0, int iw0) {
     return run(ih0, g.H, g.R) | (run(iw0, g.W, g.S) << 16);
 }
 
-// The K loop of one tile (or of chunks [k0, k0 + kn) of it; kn < 0: all), through a ring of two LDS
+// The K loop of one tile (or of chunks [k0, k0 + kn) of it; kn < 0: all), through a ring of STAGES LDS
 // stages.  Chunks follow TapWalk over the channel blocks [c_lo, c_hi) (outer) and the taps (inner).
 //
 // What bounds it: the matrix cores, as long as nothing sits between their instructions.  So
@@ -480,7 +484,7 @@ __device__ inline unsigned tap_mask(const Geom &g, int ih0, int iw0) {
 // 125 us; so it takes 110 us, 1075 TFLOP/s on 77 % of the compute units (torch.mm on 8192^3 random
 // bf16 operands: 1205 TFLOP/s).  Spreading a chunk's loads over two or three steps: 107-111 us there,
 // 1-5 % slower on the 128 x 128 and smaller tiles.
-template <typename C, int NP, int FM, int FP>
+template <typename C, int NP, int STAGES, int FM, int FP>
 __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, int m0, long long p0,
                                     const unsigned char *zp_dt, unsigned char *smem, floatx16 (&acc)[FM][FP],
                                     int tid, int arow0, int brow0, int k0, int kn, int c_lo, int c_hi) {
@@ -488,8 +492,11 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     constexpr int ROWL = C::ROWB / 16;               // 16-byte units per row
     constexpr int CH = C::TK, Q = CH / 16;           // channels per chunk, MFMA steps per chunk
     constexpr unsigned EB = 2 * NP;                  // bytes per channel of an operand
-    constexpr int NIA = C::TM * ROWL / C::NT, NIB = C::TP * ROWL / C::NT, NI = NIA + NIB;
-    static_assert(C::TM * ROWL % C::NT == 0 && C::TP * ROWL % C::NT == 0 && NI < 64, "DMA tile shape");
+    // wave loads (64 units) of a chunk's weight and input rows, and the most of them one wave issues
+    constexpr int NLA = C::TM * ROWL / 64, NLB = C::TP * ROWL / 64;
+    constexpr int NIA = (NLA + NW - 1) / NW, NIB = NLB / NW, NI = NIA + NIB;
+    static_assert(C::TM * ROWL % 64 == 0 && NLB % NW == 0 && STAGES * NI < 64, "DMA tile shape");
+    static_assert(STAGES == 2 || NLA % NW == 0, "every wave counts the same loads");
     static_assert(Q % 2 == 0, "fragment sets alternate");
     constexpr int STAGE_A = C::TM * C::ROWB, STAGE = (C::TM + C::TP) * C::ROWB;
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -508,6 +515,7 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     unsigned b_off[NIB], b_tap[NIB];
     auto issue = [&](const TapWalk &t, unsigned char *base, int j) {
         if (j < NIA) {
+            if (NLA % NW != 0 && j * NW + w >= NLA) return;
             buffer_load_lds16(rw, base + (j * NW + w) * 1024, a_off[j], EB * (unsigned)t.kb(g));
         } else {
             const int i = j - NIA;
@@ -517,17 +525,11 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
         }
     };
     const int nch = kn >= 0 ? kn : g.R * g.S * ((c_hi - c_lo) / CH);
-    TapWalk t0 = tap_at(g, k0, CH);
-    t0.c0 += c_lo;
-    TapWalk ti = t0;   // the chunk whose loads are issued next
-    ti.next(g, CH);
-    // the first two chunks' weights are on their way while the pixels are worked out
+    TapWalk ti = tap_at(g, k0, CH);   // the chunk whose loads are issued next
+    ti.c0 += c_lo;
+    // the first chunk's weights are on their way while the pixels are worked out
 #pragma unroll
-    for (int j = 0; j < NIA; ++j) issue(t0, smem, j);
-    if (nch > 1) {
-#pragma unroll
-        for (int j = 0; j < NIA; ++j) issue(ti, smem + STAGE, j);
-    }
+    for (int j = 0; j < NIA; ++j) issue(ti, smem, j);
 #pragma unroll
     for (int j = 0; j < NIB; ++j) {
         const int s = (j * NW + w) * 64 + lane, row = s / ROWL;
@@ -542,15 +544,15 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
                    16u * (unsigned)unit(row, s % ROWL);
     }
 #pragma unroll
-    for (int j = NIA; j < NI; ++j) issue(t0, smem, j);
-    if (nch > 1) {
+    for (int st = 0; st < STAGES; ++st)
+        if (st < nch) {
 #pragma unroll
-        for (int j = NIA; j < NI; ++j) issue(ti, smem + STAGE, j);
-        ti.next(g, CH);
-        wait_vmcnt<NIB>();
-    } else {
-        wait_vmcnt<0>();
-    }
+            for (int j = st == 0 ? NIA : 0; j < NI; ++j) issue(ti, smem + st * STAGE, j);
+            ti.next(g, CH);
+        }
+    // (a wave with fewer weight loads than NIA must not leave one of its first chunk's behind)
+    if (nch >= STAGES) wait_vmcnt<(STAGES - 1) * (NLA % NW ? NI - 1 : NI)>();
+    else wait_vmcnt<0>();
     lds_barrier();
     // fragment reads: lanes 0-31 take the first half of the chunk's units of a plane, lanes 32-63 the second
     const int l32 = lane & 31, h = lane >> 5;
@@ -582,16 +584,17 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
 
 #pragma unroll
     for (int i = 0; i < NR; ++i) read(smem, 0, 0, i);
-    // one chunk; next: another chunk follows; more: and one after that, whose loads are issued here
+    // one chunk, in stage cur; next: another chunk follows, in stage oth; more: and the one STAGES
+    // after this one too, whose loads are issued here
     auto chunk = [&](unsigned char *cur, unsigned char *oth, auto next, auto more) {
         constexpr bool NEXT = decltype(next)::value, MORE = decltype(more)::value;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const bool last = q == Q - 1;
             if (last && NEXT) {
-                // the next chunk's loads (issued a chunk ago) have landed and this wave has its last
-                // fragments of this chunk; after the barrier that holds for every wave
-                wait_vmcnt<0>();
+                // the next chunk's loads have landed (the later chunks' may be in flight) and this wave
+                // has its last fragments of this chunk; after the barrier that holds for every wave
+                wait_vmcnt<MORE ? (STAGES - 2) * NI : 0>();
                 wait_lgkm0();
                 lds_barrier();
             }
@@ -610,18 +613,70 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
         if (MORE) ti.next(g, CH);
     };
     using std::integral_constant;
+    using yes = integral_constant<bool, true>;
+    using no = integral_constant<bool, false>;
     int kc = 0;
-    for (; kc + 2 < nch; ++kc)
-        chunk(smem + (kc & 1) * STAGE, smem + ((kc & 1) ^ 1) * STAGE, integral_constant<bool, true>{},
-              integral_constant<bool, true>{});
-    if (kc + 1 < nch) {
-        chunk(smem + (kc & 1) * STAGE, smem + ((kc & 1) ^ 1) * STAGE, integral_constant<bool, true>{},
-              integral_constant<bool, false>{});
-        ++kc;
+    unsigned char *cur = smem;
+    auto after = [&](unsigned char *p) { return p == smem + (STAGES - 1) * STAGE ? smem : p + STAGE; };
+    for (; kc + STAGES < nch; ++kc) {
+        chunk(cur, after(cur), yes{}, yes{});
+        cur = after(cur);
     }
-    chunk(smem + (kc & 1) * STAGE, smem + ((kc & 1) ^ 1) * STAGE, integral_constant<bool, false>{},
-          integral_constant<bool, false>{});
+    for (; kc + 1 < nch; ++kc) {
+        chunk(cur, after(cur), yes{}, no{});
+        cur = after(cur);
+    }
+    chunk(cur, cur, no{}, no{});
     wait_lgkm0();
+}
+
+// The outputs of a split tile that came out non-finite, again in fp32 from D and W as given (eq. (1),
+// the filter's own channels): an infinite, NaN or nearly overflowing operand has no split whose planes
+// multiply to what fp32 gives (its lower planes are NaN or of either sign), so such an output says only
+// that it must be redone.  The accumulators pass through LDS so that the loop over them is not unrolled;
+// a finite tile pays one multiply-add an accumulator and a barrier.
+template <typename C, int FM, int FP>
+__device__ inline void redo_nonfinite(const Geom &g, const float *__restrict__ D, const float *__restrict__ W, int m0,
+                                      long long p0, unsigned char *smem, floatx16 (&acc)[FM][FP], int tid, int arow0,
+                                      int brow0) {
+    constexpr int NA = FM * FP * 16;
+    static_assert((size_t)C::NT * NA * sizeof(float) <= C::LDS_BYTES, "accumulators fit LDS");
+    float t = 0.0f;   // 0 while every accumulator is finite, else NaN
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FP; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) t = fmaf(acc[i][j][e], 0.0f, t);
+    __syncthreads();   // every wave is done with the operand tiles
+    if (__ballot(!(t == 0.0f)) == 0) return;
+    float *mine = reinterpret_cast<float *>(smem) + tid;
+#pragma unroll
+    for (int k = 0; k < NA; ++k) mine[k * C::NT] = acc[k / 16 / FP][k / 16 % FP][k % 16];
+    const int l32 = tid & 31, h = (tid >> 5) & 1;
+    for (int k = 0; k < NA; ++k) {
+        if (isfinite(mine[k * C::NT])) continue;
+        const int e = k % 16, j = k / 16 % FP, i = k / 16 / FP;
+        const int m = m0 + arow0 + i * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+        const long long pg = p0 + brow0 + j * 32 + l32;
+        if (m >= g.M || pg >= g.P_total) continue;
+        const int n = (int)(pg / g.EF), pix = (int)(pg - (long long)n * g.EF);
+        const int x = pix / g.F, y = pix - x * g.F, c0 = group_first_channel(g, m);
+        const int ih0 = g.U * x - g.P, iw0 = g.U * y - g.P;
+        float s = 0.0f;
+        for (int c = c0; c < c0 + g.Cg && !isnan(s); ++c)   // NaN stays NaN
+            for (int r = 0; r < g.R; ++r) {
+                if ((unsigned)(ih0 + r) >= (unsigned)g.H) continue;
+                const float *d = D + n * g.CHW + ((long long)c * g.H + ih0 + r) * g.W;
+                const float *w = W + ((long long)m * g.C + c) * (g.R * g.S) + r * g.S;
+                for (int q = 0; q < g.S; ++q)
+                    if ((unsigned)(iw0 + q) < (unsigned)g.W) s = fmaf(d[iw0 + q], w[q], s);
+            }
+        mine[k * C::NT] = s;
+    }
+#pragma unroll
+    for (int k = 0; k < NA; ++k) acc[k / 16 / FP][k / 16 % FP][k % 16] = mine[k * C::NT];
+    // the next use of LDS in this workgroup is behind a barrier
 }
 
 template <typename T> struct Bits;
@@ -685,7 +740,7 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
     constexpr bool DMA = NHWC && WEAVE >= 3;
     // the stream-K form (a separate kernel: the whole-tile kernels keep their registers) of the
     // loops that can run a range of a tile's chunks (channels-last, dense)
-    constexpr bool SKOK = SK && NHWC && !GRP && WEAVE != 2;
+    constexpr bool SKOK = SK && NHWC && WEAVE >= 3;
     constexpr bool skm = SKOK;
     long long sk_it = 0, sk_end = 0, sk_u = 0, sk_i0 = 0;
     int wl = 0, dp = 0;
@@ -804,10 +859,6 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
         tw.c0 = cg0;
         if (!(KSKIP && cpr > 0)) nch = g.R * g.S * (g.C / C::TK);
         pix_off = lane_base + (ih0 * g.W + iw0) * g.C + bkg * C::KR;
-        if (SKOK && kn >= 0) {
-            tw = tap_at(g, k0, C::TK);
-            nch = kn;
-        }
     }
     if constexpr (!DMA) {
         if constexpr (TAPS) {
@@ -824,8 +875,13 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
 
     if constexpr (DMA) {
         // D is the channels-last copy, which the workspace keeps right behind the zero page zp
-        dma_mainloop<C, Tr::NP, FM, FP>(Wt, g, m0, p0, static_cast<const unsigned char *>(zp), smem, acc, tid, arow0,
-                                        brow0, k0, kn, 0, g.C);
+        // grouped layers run on the block-diagonal expansion of W: the tile walks the channel blocks
+        // its filters' groups reach into (all of them when G = 1)
+        const int mlast = (m0 + C::TM < g.M ? m0 + C::TM : g.M) - 1;
+        const int c_lo = group_first_channel(g, m0) / C::TK * C::TK;
+        const int c_hi = (group_first_channel(g, mlast) + g.Cg + C::TK - 1) / C::TK * C::TK;
+        dma_mainloop<C, Tr::NP, WEAVE - 1, FM, FP>(Wt, g, m0, p0, static_cast<const unsigned char *>(zp), smem, acc, tid, arow0,
+                                        brow0, k0, kn, c_lo, c_hi);
     } else if constexpr (NHWC && WEAVE == 2) {
         // channels-last, two chunks in flight: chunk kc + 2 is loaded into one register set
         // while chunk kc is consumed from LDS, and chunk kc + 1 (loaded a whole chunk earlier,
@@ -945,17 +1001,24 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
             // the workgroup whose range holds iteration i
             auto owner = [&](long long i) { return (int)(((i - sk_i0 + 1) * sk.S - 1) / sk_u); };
             const int w0 = owner(ib), w1 = owner(ib + sk.nch - 1);
-            constexpr int NR = FM * FP * 16;   // accumulators per thread; slot layout [NR][NT]
-            float *mine = sk.part + ((size_t)wl * 2 + (first_seg ? 0 : 1)) * (size_t)(C::TM * C::TP);
+            // a slot: FM * FP * 4 rows of NT 16-byte units, four accumulators of a thread each
+            static_assert(FM * FP * 16 * C::NT == C::TM * C::TP, "slot size");
+            const __amdgpu_buffer_rsrc_t rp = buffer_rsrc(sk.part, (unsigned)sk.S * 2u * (C::TM * C::TP * 4u));
+            auto slot_at = [&](int w, int slot) { return ((unsigned)w * 2u + (unsigned)slot) * (C::TM * C::TP * 4u); };
+            const unsigned mine = slot_at(wl, first_seg ? 0 : 1);
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
                 for (int j = 0; j < FP; ++j) {
 #pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        __hip_atomic_store(mine + ((i * FP + j) * 16 + e) * C::NT + tid, acc[i][j][e],
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __builtin_amdgcn_sched_barrier(0);   // a few store addresses live at a time
+                    for (int q = 0; q < 4; ++q) {
+                        const floatx4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2],
+                                           acc[i][j][4 * q + 3]};
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rp,
+                                                               (((i * FP + j) * 4 + q) * C::NT + tid) * 16, mine,
+                                                               kDeviceCoherent);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // a few units live at a time
                 }
             // The parts go to memory with device-coherent stores (they bypass the XCD's L2), so
             // once every wave has seen its stores complete, one device-scope count publishes the
@@ -979,27 +1042,46 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
             if (tid == 0) __hip_atomic_store(sk.cnt + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // the tile's parts in chunk order (this workgroup's own from its slot too): part w lies
             // in slot 0 of workgroup w when its range starts inside this tile, else in its slot 1
-            // (its last segment).  Sixteen loads at a time, so the sums need few registers beyond
-            // the accumulators.
-            static_assert(NR * C::NT == C::TM * C::TP, "slot size");
-            for (int w = w0; w <= w1; ++w) {
-                const int slot = sk_i0 + (long long)w * sk_u / sk.S >= ib ? 0 : 1;
-                const float *src = sk.part + ((size_t)w * 2 + slot) * (size_t)(C::TM * C::TP) + tid;
+            // (its last segment).  A block of 32 x 32 at a time, four parts of it in flight.
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
-                    for (int j = 0; j < FP; ++j) {
-                        float v[16];
+                for (int j = 0; j < FP; ++j) {
+                    for (int w = w0; w <= w1; w += 4) {
+                        floatx4 v[4][4];
 #pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            v[e] = __hip_atomic_load(src + ((i * FP + j) * 16 + e) * C::NT, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
+                        for (int u = 0; u < 4; ++u) {
+                            const int wu = w + u <= w1 ? w + u : w1;   // past the last: read again, not added
+                            const unsigned src = slot_at(wu, sk_i0 + (long long)wu * sk_u / sk.S >= ib ? 0 : 1);
 #pragma unroll
-                        for (int e = 0; e < 16; ++e) acc[i][j][e] = w == w0 ? v[e] : acc[i][j][e] + v[e];
-                        __builtin_amdgcn_sched_barrier(0);
+                            for (int q = 0; q < 4; ++q)
+                                v[u][q] = __builtin_bit_cast(
+                                    floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                 rp, (((i * FP + j) * 4 + q) * C::NT + tid) * 16, src, kDeviceCoherent));
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (w + u <= w1)
+#pragma unroll
+                                for (int e = 0; e < 16; ++e)
+                                    acc[i][j][e] = w + u == w0 ? v[u][e / 4][e % 4] : acc[i][j][e] + v[u][e / 4][e % 4];
                     }
-            }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
         }
+    }
+
+    if constexpr (DMA && Tr::NP == 3) {
+        // the copies' scale out, and odd filters' sums negated back (split_weight_scale): an accumulator's
+        // filter has its index's parity
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FP; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] *= e & 1 ? -kSplitUnscale : kSplitUnscale;
+        redo_nonfinite<C, FM, FP>(g, static_cast<const float *>(ep.src_dw.d), static_cast<const float *>(ep.src_dw.w),
+                                  m0, p0, smem, acc, tid, arow0, brow0);
     }
 
     // epilogue: lane owns pixel (lane & 31) of each 32-wide block; register e of

@@ -63,14 +63,14 @@ int sk_workgroups(int smax) {
 template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE, bool KVEC, bool NHWC>
 int sk_decide(const Geom &g, int smax) {
     using C = Cfg<Tr, WM, WP, FM, FP, KVEC, (WEAVE >= 3 ? WEAVE - 1 : 0)>;
-    if constexpr (!(NHWC && WEAVE != 2 && sizeof(typename C::T) == 4)) {
+    if constexpr (!(NHWC && WEAVE >= 3 && sizeof(typename C::T) == 4)) {
         return 0;
     } else {
-        if (smax <= 0 || g.G > 1 || g.C % C::TK != 0) return 0;
+        if (smax <= 0 || g.G > 1) return 0;
         const int nch = g.R * g.S * (g.C / C::TK);
         const long long tiles = ((g.P_total + C::TP - 1) / C::TP) * (long long)((g.M + C::TM - 1) / C::TM);
         const int S = sk_workgroups<Tr, WM, WP, FM, FP, WEAVE, KVEC, NHWC>(smax);
-        return S > 0 && use_stream_k(tiles, S, nch) ? S : 0;
+        return S > 0 ? stream_k_workgroups(tile_cost<Tile<Tr, WM, WP, FM, FP, WEAVE>>(), tiles, S, nch) : 0;
     }
 }
 
@@ -85,7 +85,7 @@ hipError_t launch_one(const Geom &g, const void *D, const void *W, void *O, hipS
     const long long total = tiles_p * tiles_m;
     Epi<EPI> e = ep;
     SkArgs sk{nullptr, nullptr, 0, 0, 0};
-    constexpr bool SKF = NHWC && !GRP && WEAVE != 2 && sizeof(T) == 4;   // has a stream-K form
+    constexpr bool SKF = NHWC && WEAVE >= 3 && sizeof(T) == 4;   // has a stream-K form
     if constexpr (SKF) {
         if (skin.S > 0 && skin.part && skin.cnt) {
             const int S = sk_decide<Tr, WM, WP, FM, FP, WEAVE, KVEC, NHWC>(g, skin.S);

@@ -6,15 +6,19 @@ namespace ftcnn {
 using namespace convk;
 namespace {
 
-// Tile choice per layer, from sweeps over the workload shapes on MI355X.  The
-// filter tile follows M so small-M layers waste no MFMA rows; for larger M the
-// biggest tile that still leaves about two workgroups per CU wins.  For bf16
-// (eight times the fp32 matrix rate per instruction), channels-last layers with
-// 64-channel multiples take direct-to-LDS loads (WEAVE 3): 64 x 128 tiles for
-// M <= 64, 256 x 256 tiles (eight waves of 128 x 64) for M >= 256 where there
-// are enough of them, 128 x 64 where 128 x 128 tiles would not fill the compute
-// units, 128 x 128 elsewhere; the other channels-last layers keep
-// two chunks in flight (WEAVE 2), and the rest take 64 x 256, 256 x 256 or
+// Tile choice per layer, from sweeps over the workload shapes on MI355X.  The filter tile follows M so
+// small-M layers waste no MFMA rows.
+//
+// fp32 channels-last layers run on split copies (three bf16 planes a value, six products): the bf16
+// matrix cores do six products in 3/8 of the time the fp32 ones take for one, and errors are no larger
+// (VGG-19 v6: 951 -> 505 us for the convolution, 124 -> 235 TFLOP/s against 157 of the fp32 matrix cores;
+// distance from float64 8.0e-7 -> 7.2e-7).  Their tile and its schedule are the ones with the least
+// predicted time (TileCost).  The other fp32 layers take 128 x 128, 128 x 64 or 64 x 64 fp32 tiles.
+//
+// bf16 channels-last layers with 64-channel multiples take direct-to-LDS loads (WEAVE 3): 64 x 128 tiles
+// for M <= 64, 256 x 256 tiles (eight waves of 128 x 64) for M >= 256 where there are enough of them,
+// 128 x 64 where 128 x 128 tiles would not fill the compute units, 128 x 128 elsewhere; the other
+// channels-last layers keep two chunks in flight (WEAVE 2), and the rest take 64 x 256, 256 x 256 or
 // 128 x 128 tiles with register-staged loads.
 long long n_tiles(const Geom &g, int tm, int tp) {
     return ((g.P_total + tp - 1) / tp) * (long long)((g.M + tm - 1) / tm);
@@ -24,6 +28,28 @@ long long n_tiles(const Geom &g, int tm, int tp) {
 // channels-last copies).
 template <typename Fn>
 auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
+    if (nhwc && g.split) {
+        if (g.M <= 32) return f(S3_32x128{});
+        // the tile with the least predicted time, on whole tiles or shared ones
+        auto cost = [&](auto t) {
+            using Tl = decltype(t);
+            constexpr TileCost c = tile_cost<Tl>();
+            const long long tiles = n_tiles(g, Tl::TM, Tl::TP);
+            // a tile walks the channel blocks that its filters' groups reach into
+            const int spans = g.G > 1 ? (Tl::TM + g.Mg - 1) / g.Mg : 1;
+            const int ch = g.G > 1 && spans * g.Cg + 32 < g.C ? spans * g.Cg + 32 : g.C;
+            const int nch = g.R * g.S * ((ch + 31) / 32);
+            const double whole = whole_cost(c, tiles, c.resident, nch);
+            const int S = g.G > 1 ? 0 : stream_k_size(tiles, c.resident, nch);
+            const double shared = S > 0 ? shared_cost(c, tiles, c.resident, nch, S) : whole;
+            return shared < whole ? shared : whole;
+        };
+        const double c64 = cost(S3_64x64{});
+        if (g.M <= 64) return c64 <= cost(S3_64x128{}) ? f(S3_64x64{}) : f(S3_64x128{});
+        const double c128 = cost(S3_128x128{}), c256 = cost(S3_128x256{});
+        if (c256 <= c128 && c256 <= c64) return f(S3_128x256{});
+        return c128 <= c64 ? f(S3_128x128{}) : f(S3_64x64{});
+    }
     if (g.dtype == FTCNN_F32) {
         if (g.M <= 32) return f(F32_M32{});
         // on channels-last layers a wave of the 64 x 256 tile holds 64 x 64 outputs, as in the
@@ -33,21 +59,6 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
         // grouped layers: rows of tiles inside one group, so that every tile skips the other
         // groups' channels (192 filters a group: 64-row tiles)
         if (g.G > 1 && g.Mg % 128 != 0 && g.Mg % 64 == 0) return f(F32_64x64{});
-        // dense channels-last layers whose tiles the stream-K schedule shares out evenly (at the two
-        // workgroups a compute unit that these tiles keep on 256 compute units) lose nothing to the
-        // last round of tiles: there the larger tile is the faster one per output (VGG-19 v5-v9:
-        // 128 x 128 3-5 % faster than 128 x 64; v13-v16, Darknet-19 c9-c18 and AlexNet conv5:
-        // 128 x 64 6-9 % faster than 64 x 64 or 128 x 128)
-        if (nhwc && g.G == 1) {
-            auto shared = [&](long long tiles, int tk) {
-                return g.C % tk == 0 && use_stream_k(tiles, 2 * kSkComputeUnits, g.R * g.S * (g.C / tk));
-            };
-            // with 512 or more channels the 32-deep chunks pay (VGG-19 v10-v12 1013 -> 986 us; on
-            // v3-v8, 64 to 256 channels, they were up to 2.6 % slower)
-            if (n_tiles(g, 128, 128) >= 600 && shared(n_tiles(g, 128, 128), 16))
-                return g.C >= 512 ? f(F32_128x128_K32{}) : f(F32_128x128{});
-            if (n_tiles(g, 128, 64) >= 256 && shared(n_tiles(g, 128, 64), 32)) return f(F32_128x64{});
-        }
         // the tile with the least predicted time: the padded outputs (tiles x TM x TP), plus half of
         // the idle slots in the last round of 256 tiles, at the tile's own rate per output
         // (128 x 128 : 128 x 64 : 64 x 64 = 1 : 0.972 : 0.925).  The one-half and the rates are
@@ -66,11 +77,7 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
         if (c12864 <= c64) return f(F32_128x64{});
         return f(F32_64x64{});
     }
-    // direct-to-LDS loads reach the operands through 32-bit buffer offsets, count pixels in 32 bits
-    // and keep a pixel's taps inside the map in two 16-bit masks
-    const bool dma = nhwc && g.C % 64 == 0 && (long long)g.M * g.K * 2 < (1LL << 31) &&
-                     256 + (long long)g.N * g.CHW * 2 < (1LL << 31) && g.P_total < (1LL << 31) && g.R <= 16 &&
-                     g.S <= 16;
+    const bool dma = nhwc && g.C % 64 == 0 && dma_layer(g, 2);
     if (g.M <= 32) return f(BF16_M32{});
     // M <= 64 with 64-channel multiples: direct-to-LDS 64 x 128 (against register-staged loads,
     // VGG-19 v2 384 -> 308 us and ResNet-18 l1 109 -> 90 us for the convolution alone, before the
@@ -96,7 +103,7 @@ void conv_tile_info(const Geom &g, bool nhwc, int out[6]) {
         out[2] = Tt::TK;
         out[3] = Tt::WEAVE_KIND;
         out[4] = nhwc ? 1 : 0;
-        out[5] = (nhwc && g.G > 1 && Tt::WEAVE_KIND != 2 && Tt::WEAVE_KIND != 3) ? 1 : 0;
+        out[5] = (nhwc && g.G > 1 && Tt::WEAVE_KIND != 2) ? 1 : 0;
         return 0;
     });
 }
@@ -106,7 +113,7 @@ int conv_tile_m(const Geom &g, bool nhwc) {
 }
 
 hipError_t launch_conv(const Plan &pl, const void *D, const void *W, void *O, hipStream_t st, const float *bias) {
-    const Epi<0> ep{bias};
+    const Epi<0> ep{bias, {}};
     return with_tile(pl.g, false, [&](auto t) { return decltype(t)::run(pl.g, D, W, O, st, ep); });
 }
 
@@ -190,11 +197,11 @@ hipError_t launch_conv_sums(const Plan &pl, const void *D, const void *W, void *
     const double *cw1 = ck ? ck->cw1 : nullptr, *cw2 = ck ? ck->cw2 : nullptr;
     const float *bias = ck ? ck->bias : nullptr;
     if (nf == 0) {
-        Epi<1> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, src, cw1, cw2, copart, co, co_slices, {}, bias};
+        Epi<1> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, src, cw1, cw2, copart, co, co_slices, {}, bias, {D, W}};
         return with_tile(pl.g, pl.nhwc,
                          [&](auto t) { return decltype(t)::run(pl.g, Dc, Wc, O, st, ep, pl.nhwc, zp, sk_args(pl, ws)); });
     }
-    Epi<2> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, src, cw1, cw2, copart, co, co_slices, {}, bias};
+    Epi<2> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, src, cw1, cw2, copart, co, co_slices, {}, bias, {D, W}};
     for (int i = 0; i < nf; ++i) ep.fl.f[i] = faults[i];
     ep.fl.n = nf;
     return with_tile(pl.g, pl.nhwc,
@@ -207,7 +214,7 @@ hipError_t launch_conv_ws(const Plan &pl, const void *D, const void *W, void *O,
     const hipError_t e = launch_prep(pl, D, W, nullptr, nullptr, ws, st);
     if (e != hipSuccess) return e;
     char *w = static_cast<char *>(ws);
-    const Epi<0> ep{bias};
+    const Epi<0> ep{bias, {D, W}};
     return with_tile(pl.g, true, [&](auto t) {
         return decltype(t)::run(pl.g, w + pl.off_dt, w + pl.off_wt, O, st, ep, true, w + pl.off_zero, sk_args(pl, ws));
     });

@@ -27,6 +27,14 @@ template <int TK_> struct BF16T {
     static constexpr int VEC = 8;
     static constexpr int NP = 1;       // bf16 planes of an operand in the direct-to-LDS loop
 };
+// fp32 layers on split copies (Geom::split): 32-channel chunks of three bf16 planes.
+template <int TK_> struct S3T {
+    using T = float;
+    static constexpr int TK = TK_;
+    static constexpr int LDK = TK_ + 4;
+    static constexpr int VEC = 4;
+    static constexpr int NP = 3;
+};
 
 // DSTAGES > 0: the direct-to-LDS loop with that many stages of (TM + TP) rows of ROWB bytes.
 template <typename Tr, int WM, int WP, int FM, int FP, bool KVEC_ = true, int DSTAGES = 0>
@@ -68,6 +76,10 @@ struct Cfg {
 //               (coc_tile.h), in the last groups, after the tile_groups groups of
 //               tiles, where they fill the slots the tiles' last round leaves.
 struct NoFaults {};
+// D and (dense) W as given, for layers on split copies
+struct Given {
+    const void *d, *w;
+};
 // Stream-K schedule of the channels-last loops (S > 0): the launch has S workgroups (after the
 // extra ones), as many as are resident at once.  The first dp_waves x S tiles run whole, tile
 // r S + w being workgroup w's r-th, so that the workgroups resident together work on neighbouring
@@ -99,9 +111,11 @@ template <int EPI> struct Epi {
     int co_slices;       // Co partial slices this launch writes (recorded in rep->reserved[1])
     typename std::conditional<EPI == 2, FaultList, NoFaults>::type fl;
     const float *bias;   // NULL, or [M] added to every stored value of filter m (Sec. 5.1)
+    Given src_dw;
 };
 template <> struct Epi<0> {
     const float *bias;
+    Given src_dw;
 };
 
 // One tile configuration.  WEAVE: the main loop (0 register-staged, 1 gather woven between the
@@ -114,7 +128,7 @@ template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE> struct Tile {
     static constexpr int WEAVE_KIND = WEAVE;
     static constexpr int NT = Cfg<Tr, WM, WP, FM, FP>::NT;
     static constexpr size_t LDS_BYTES = Cfg<Tr, WM, WP, FM, FP, true, (WEAVE >= 3 ? WEAVE - 1 : 0)>::LDS_BYTES;
-    static constexpr bool SK_FORM = WEAVE != 2 && sizeof(typename Tr::T) == 4;
+    static constexpr bool SK_FORM = WEAVE >= 3 && sizeof(typename Tr::T) == 4;
     // stream-K workgroups of the channels-last form on the current device (0: whole tiles)
     static int stream_k(const Geom &g, int smax);
     // NCHW: D and W as given; NHWC: the channels-last copies Dt and Wt (always aligned, K % VEC == 0)
@@ -131,6 +145,15 @@ using F32_128x128 = Tile<F32T<16>, 2, 2, 2, 2, true>;
 using F32_128x128_K32 = Tile<F32T<32>, 2, 2, 2, 2, true>;   // 32-deep chunks: half the barriers
 using F32_128x64 = Tile<F32T<32>, 2, 2, 2, 1, true>;
 using F32_64x64 = Tile<F32T<32>, 2, 2, 1, 1, true>;
+// fp32 on split copies.  128 x 256: eight waves of 64 x 64, a two-stage ring of 72 KB stages; 128 x 128:
+// eight waves of 64 x 32, three stages of 48 KB (two stages 4-8 % slower: a chunk's loads then have one
+// short chunk to land; VGG-19 v14 149 -> 144 us, Darknet-19 c14 141 -> 133 us); 64 x 64, three stages: layers
+// of few tiles; 64 x 128 and 32 x 128: few filters.
+using S3_128x256 = Tile<S3T<32>, 2, 4, 2, 2, 3>;
+using S3_128x128 = Tile<S3T<32>, 2, 4, 2, 1, 4>;
+using S3_64x64 = Tile<S3T<32>, 2, 2, 1, 1, 4>;
+using S3_64x128 = Tile<S3T<32>, 1, 4, 2, 1, 3>;
+using S3_32x128 = Tile<S3T<32>, 1, 4, 1, 1, 3>;
 using BF16_M32 = Tile<BF16T<32>, 1, 4, 1, 2, 0>;
 using BF16_M64 = Tile<BF16T<32>, 1, 4, 2, 2, 2>;
 using BF16_128x128_K64 = Tile<BF16T<64>, 2, 2, 2, 2, 2>;
@@ -150,14 +173,45 @@ using BF16_DMA_64x128 = Tile<BF16T<64>, 1, 4, 2, 1, 3>;
 // of 128 x 128 (one a SIMD) 5-8 % faster on VGG-19 bf16 v5-v12, which also beat 128 x 128 tiles
 using BF16_DMA_256x256 = Tile<BF16T<64>, 2, 4, 4, 2, 3>;
 
-// Stream-K pays (the partial writes and the last workgroup's sums of a split tile) where a plain
-// grid of whole tiles would leave its last round of S resident workgroups partly idle, and where
-// every workgroup still has a long run of chunks.
-inline bool use_stream_k(long long tiles, int S, int nch) {
-    if (tiles * nch < 32LL * S) return false;   // under 32 chunks a workgroup
-    const long long rounds = (tiles + S - 1) / S;
-    return tiles * 100 < rounds * S * 90;       // the whole-tile grid would use < 90 % of its slots
+// What a split layer's tiles take (us), as measured on one MI355X: chunk_idle + chunk_busy * (share of the
+// chip's slots in use) a chunk, since busy matrix cores lower the clock, `tile` a tile beyond its
+// chunks, and `shared` more where tiles are shared (publishing a workgroup's part and summing a
+// tile's parts).  Fitted to VGG-19 v4..v14, Darknet-19 c9..c14, AlexNet conv2..conv4 and batch-1 layers,
+// where the predictions lie within 10 %.
+struct TileCost {
+    int resident;   // workgroups on the chip at once
+    double chunk_idle, chunk_busy, tile, shared;
+};
+// Stream-K pays where whole tiles leave the last round of workgroups partly idle, or never fill the
+// chip, by more than sharing costs; a workgroup keeps at least kSkMinChunks chunks, and tiles of few
+// chunks are not shared (1 x 1 layers of 128 to 256 channels: 4 to 8 chunks, shared tiles 28-50 % slower).
+constexpr int kSkMinChunks = 16, kSkMinTile = 24;
+inline int stream_k_size(long long tiles, int resident, int nch) {
+    const long long fill = tiles * nch / kSkMinChunks;
+    if (nch < kSkMinTile) return 0;
+    if (fill >= resident) return resident;
+    return fill / 8 * 8 > tiles ? (int)(fill / 8 * 8) : 0;
 }
+inline double whole_cost(const TileCost &t, long long tiles, int resident, int nch) {
+    const long long full = tiles / resident, rem = tiles % resident;
+    const double busy = (double)rem / resident;
+    return full * (nch * (t.chunk_idle + t.chunk_busy) + t.tile) +
+           (rem ? nch * (t.chunk_idle + t.chunk_busy * busy) + t.tile : 0.0);
+}
+inline double shared_cost(const TileCost &t, long long tiles, int resident, int nch, int S) {
+    return (double)(tiles * nch) / S * (t.chunk_idle + t.chunk_busy * S / resident) + t.tile + t.shared;
+}
+// Stream-K workgroups of a layer on this tile, 0 for one workgroup per tile.
+inline int stream_k_workgroups(const TileCost &t, long long tiles, int resident, int nch) {
+    const int S = stream_k_size(tiles, resident, nch);
+    return S > 0 && shared_cost(t, tiles, resident, nch, S) < whole_cost(t, tiles, resident, nch) ? S : 0;
+}
+template <typename Tl> constexpr TileCost tile_cost() { return TileCost{256, 1.0, 0.0, 4.0, 20.0}; }
+template <> constexpr TileCost tile_cost<S3_128x256>() { return TileCost{256, 1.35, 0.85, 4.0, 18.0}; }
+template <> constexpr TileCost tile_cost<S3_128x128>() { return TileCost{256, 0.75, 0.38, 6.0, 25.0}; }
+template <> constexpr TileCost tile_cost<S3_64x64>() { return TileCost{512, 0.60, 0.02, 2.0, 14.0}; }
+template <> constexpr TileCost tile_cost<S3_64x128>() { return TileCost{512, 0.80, 0.20, 2.0, 16.0}; }
+template <> constexpr TileCost tile_cost<S3_32x128>() { return TileCost{512, 0.60, 0.10, 2.0, 14.0}; }
 
 }  // namespace convk
 }  // namespace ftcnn

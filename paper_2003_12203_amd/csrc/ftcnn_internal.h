@@ -25,7 +25,12 @@ struct Geom {
     // meets channels [group_first_channel(m), + Cg).  K = C*R*S is the dense reduction of the
     // block-diagonal expansion of W that the convolution runs on.  G = 1: Cg = C, Kg = K.
     int G, Cg, Mg, Kg;
+    // fp32 layers whose channels-last copies hold every value as three bf16 planes whose sum it is
+    // (split_layer): the convolution multiplies the planes on the bf16 matrix cores
+    int split;
 };
+// bytes of one value in the channels-last copies
+__host__ __device__ inline int copy_bytes(const Geom &g) { return g.dtype == FTCNN_BF16 ? 2 : (g.split ? 6 : 4); }
 __host__ __device__ inline int group_first_channel(const Geom &g, int m) { return (m / g.Mg) * g.Cg; }
 
 // Tiling of the Co5..Co7 products computed by extra workgroups of the
@@ -256,6 +261,25 @@ int conv_stream_k(const Plan &pl);
 // Layers whose convolution reads channels-last copies (pl.nhwc): Ch a multiple of 32 (and
 // kernels of at most 4096 taps, whose weight rows the copy stages in LDS).
 inline bool nhwc_layer(const Geom &g) { return g.C % 32 == 0 && g.R * g.S <= 4096; }
+// Layers the direct-to-LDS loops take: they reach the copies (`bytes` a value) through 32-bit buffer
+// offsets, count pixels in 32 bits and keep a pixel's taps inside the map in two 16-bit masks.
+inline bool dma_layer(const Geom &g, int bytes) {
+    const unsigned long long lim = 1ull << 32;
+    return (unsigned long long)g.M * g.K * bytes < lim && 256 + (unsigned long long)g.N * g.CHW * bytes < lim &&
+           g.P_total < (1LL << 31) && g.R <= 16 && g.S <= 16;
+}
+// The copies of a split layer hold D and W times 2^24, and its convolution's epilogue takes 2^48 out
+// again: the bf16 matrix instruction takes subnormal operands for zero, and with the scale even the last
+// bit of the smallest fp32 value is a normal bf16 number (without, operands below 1e-34 lost bits).
+// What overflows instead (operands from 2e31, sums from 6e23) is redone in fp32 (redo_nonfinite).
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+// The copy of W also holds odd filters negated, and the epilogue negates their accumulators back: the
+// bf16 matrix instruction rounds its sums towards one side, and with every second filter's sums of
+// the other sign the summations over filters and images (So5..So7) do not add that up (VGG-19 v6: So5
+// off by 5e-6 of its norm without, 1e-7 with, as with fp32 instructions).
+__host__ __device__ inline float split_weight_scale(int m) { return m & 1 ? -kSplitScale : kSplitScale; }
+// fp32 channels-last layers whose copies are split into bf16 planes (Geom::split)
+inline bool split_layer(const Geom &g) { return g.dtype == FTCNN_F32 && nhwc_layer(g) && dma_layer(g, 6); }
 // Positions per tile of the channels-last copy (128 bytes of one channel) and channels per
 // tile (64 for bf16 when that still leaves 512 tiles: a stored position is then one 128-byte
 // line).

@@ -51,9 +51,26 @@ template <typename T, int V> union VecT {
     T e[V];
 };
 
+// Eight values split into three bf16 planes whose sum they are: each plane the nearest bf16 of what
+// the ones before left over (8 + 8 + 8 significand bits hold all 24; every difference is exact).
+// Plane pl goes to dst + 32 pl elements.
+__device__ inline void store_split8(const float (&x)[8], uint16_t *dst) {
+    union { uint4 q; uint16_t e[8]; } pl[3];
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        pl[0].e[v] = f32_to_bf16_rne(x[v]);
+        const float r1 = x[v] - bf16_bits_to_f32(pl[0].e[v]);
+        pl[1].e[v] = f32_to_bf16_rne(r1);
+        pl[2].e[v] = f32_to_bf16_rne(r1 - bf16_bits_to_f32(pl[1].e[v]));
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) *reinterpret_cast<uint4 *>(dst + 32 * k) = pl[k].q;
+}
+
 // vec_d / vec_w: D / W is 16-byte aligned (else element loads; the layout is
 // the same with shift 0, which a tile of seven vectors also covers).
-template <typename T, bool ENC, int TC, bool SHIFT>
+// SPLIT (fp32): the copies hold blocks of 32 channels as three bf16 planes of 32 (192 bytes).
+template <typename T, bool ENC, int TC, bool SHIFT, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D, const T *__restrict__ W,
                                                         T *__restrict__ Dt, T *__restrict__ Wt, Geom g,
                                                         double *cd1, double *cd2, long long split_stride,
@@ -140,6 +157,22 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
                 }
             }
             __syncthreads();
+            if constexpr (SPLIT) {
+                // eight channels of one position a thread, two images at a time
+                static_assert(TC == 32 && TH <= 32 && kThreads == 256 && BATCH % 2 == 0, "split store roles");
+                const int cq = threadIdx.x & 3, hp = (threadIdx.x >> 2) & 31, jo = threadIdx.x >> 7;
+                uint16_t *out = reinterpret_cast<uint16_t *>(Dt);
+#pragma unroll
+                for (int j = 0; j < BATCH; j += 2) {
+                    const int n = nb + j + jo;
+                    if (n >= n1 || hp >= TH || p0 + hp >= HW) continue;
+                    float x8[8];
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) x8[v] = kSplitScale * tile[j + jo][cq * 8 + v][hp + sv[v % VEC]];
+                    store_split8(x8, out + (((long long)n * HW + p0 + hp) * g.C + ct * TC) * 3 + cq * 8);
+                }
+                return;
+            }
 #pragma unroll
             for (int j = 0; j < BATCH; ++j) {
                 if (nb + j >= n1) break;
@@ -192,10 +225,11 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
     const int RS = g.R * g.S;
     const T *wm = W + (long long)m * g.K;
     T *wtm = Wt + (long long)m * g.K;
-    if (vec_w && VEC * RS <= P::LDS_ELEMS) {
-        // chunks of a multiple of VEC channels: every chunk starts on a vector of W and of Wt
-        int cch = (P::LDS_ELEMS / RS) / VEC * VEC;
-        cch = cch < VEC ? VEC : (cch > g.C ? g.C : cch);
+    constexpr int CG = SPLIT ? 8 : VEC;   // channels stored as one unit
+    if (vec_w && CG * RS <= P::LDS_ELEMS) {
+        // chunks of a multiple of CG channels: every chunk starts on a vector of W and of Wt
+        int cch = (P::LDS_ELEMS / RS) / CG * CG;
+        cch = cch > g.C ? g.C : cch;
         for (int c0 = 0; c0 < g.C; c0 += cch) {
             const int nc = cch < g.C - c0 ? cch : g.C - c0;
             const int nvec = nc * RS / VEC;
@@ -215,6 +249,19 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
                 }
             }
             __syncthreads();
+            if constexpr (SPLIT) {
+                // C and the chunk are multiples of 8 channels
+                const int c8_n = nc / 8;
+                uint16_t *out = reinterpret_cast<uint16_t *>(Wt) + (long long)m * g.K * 3;
+                for (int o = threadIdx.x; o < RS * c8_n; o += kThreads) {
+                    const int rs = o / c8_n, cl = (o - rs * c8_n) * 8, c = c0 + cl;
+                    float x8[8];
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) x8[v] = split_weight_scale(m) * stage[(cl + v) * RS + rs];
+                    store_split8(x8, out + ((long long)rs * g.C + c / 32 * 32) * 3 + c % 32);
+                }
+                continue;
+            }
             const int cv_n = nc / VEC;
             for (int o = threadIdx.x; o < nvec; o += kThreads) {
                 const int rs = o / cv_n, cv = o - (o / cv_n) * cv_n;
@@ -234,12 +281,24 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
         __syncthreads();
         for (int e = threadIdx.x; e < nc * RS; e += kThreads) {
             const int rs = e / nc, c = e - (e / nc) * nc;
-            wtm[(long long)rs * g.C + c0 + c] = stage[c * RS + rs];
+            if constexpr (SPLIT) {
+                const float x = split_weight_scale(m) * stage[c * RS + rs];
+                const uint16_t hi = f32_to_bf16_rne(x);
+                const float r1 = x - bf16_bits_to_f32(hi);
+                const uint16_t mi = f32_to_bf16_rne(r1);
+                uint16_t *dst = reinterpret_cast<uint16_t *>(Wt) + (long long)m * g.K * 3 +
+                                ((long long)rs * g.C + (c0 + c) / 32 * 32) * 3 + (c0 + c) % 32;
+                dst[0] = hi;
+                dst[32] = mi;
+                dst[64] = f32_to_bf16_rne(r1 - bf16_bits_to_f32(mi));
+            } else {
+                wtm[(long long)rs * g.C + c0 + c] = stage[c * RS + rs];
+            }
         }
     }
 }
 
-template <typename T, int TC, bool SHIFT>
+template <typename T, int TC, bool SHIFT, bool SPLIT>
 hipError_t run_tc(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws, hipStream_t st) {
     using P = PrepT<T, TC, SHIFT>;
     const Geom &g = pl.g;
@@ -269,27 +328,28 @@ hipError_t run_tc(const Plan &pl, const void *D, const void *W, double *cd1, dou
         stride = 2 * g.CHW;
     }
     if (cd1)
-        prep_kernel<T, true, TC, SHIFT><<<(unsigned)grid, kThreads, 0, st>>>(
+        prep_kernel<T, true, TC, SHIFT, SPLIT><<<(unsigned)grid, kThreads, 0, st>>>(
             static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, o1, o2, stride, (int)tr, (int)hw_tiles,
             (int)c_tiles, ns, vec_d, vec_w, zero16, skcnt, skcnt_n);
     else
-        prep_kernel<T, false, TC, SHIFT><<<(unsigned)grid, kThreads, 0, st>>>(
+        prep_kernel<T, false, TC, SHIFT, SPLIT><<<(unsigned)grid, kThreads, 0, st>>>(
             static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, nullptr, nullptr, 0, (int)tr,
             (int)hw_tiles, (int)c_tiles, ns, vec_d, vec_w, zero16, skcnt, skcnt_n);
     return hipGetLastError();
 }
 
-template <typename T, int TC>
+template <typename T, int TC, bool SPLIT = false>
 hipError_t run_shift(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws,
                      hipStream_t st) {
-    if (((long long)pl.g.H * pl.g.W) % (16 / sizeof(T)) == 0) return run_tc<T, TC, false>(pl, D, W, cd1, cd2, ws, st);
-    return run_tc<T, TC, true>(pl, D, W, cd1, cd2, ws, st);
+    if (((long long)pl.g.H * pl.g.W) % (16 / sizeof(T)) == 0) return run_tc<T, TC, false, SPLIT>(pl, D, W, cd1, cd2, ws, st);
+    return run_tc<T, TC, true, SPLIT>(pl, D, W, cd1, cd2, ws, st);
 }
 
 }  // namespace
 
 hipError_t launch_prep(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws,
                        hipStream_t st) {
+    if (pl.g.split) return run_shift<float, 32, true>(pl, D, W, cd1, cd2, ws, st);
     if (pl.g.dtype == FTCNN_F32) return run_shift<float, 32>(pl, D, W, cd1, cd2, ws, st);
     if (prep_tile_channels(pl.g) == 64) return run_shift<uint16_t, 64>(pl, D, W, cd1, cd2, ws, st);
     return run_shift<uint16_t, 32>(pl, D, W, cd1, cd2, ws, st);

@@ -15,15 +15,16 @@ CASES = [
     ("darknet19", "c1", 1, False, 1),     # fp32 32 x 256, gathered from NCHW (3-channel stem)
     ("alexnet", "conv1", 1, False, 1),    # fp32 96 x 128, NCHW, 11x11 stride 4
     ("vgg19", "v1", 1, False, 1),         # fp32 64 x 128, NCHW
-    ("darknet19", "c4", 1, False, 1),     # fp32 64 x 256, channels-last, 1x1
-    ("alexnet", "conv5", 1, False, 1),    # fp32 128 x 64, channels-last, stream-K
-    ("darknet19", "c10", 1, False, 1),    # fp32 64 x 64, channels-last, 1x1
-    ("alexnet", "conv4", 1, False, 1),    # fp32 128 x 64, channels-last
-    ("alexnet", "conv2", 1, False, 1),    # fp32 128 x 128, channels-last (the largest AlexNet layer), stream-K
+    ("darknet19", "c4", 1, False, 1),     # fp32 64 x 128 on split copies, 1x1
+    ("alexnet", "conv5", 1, False, 1),    # fp32 128 x 256 on split copies, stream-K
+    ("darknet19", "c10", 1, False, 1),    # fp32 128 x 128 on split copies, 1x1
+    ("darknet19", "c15", 1, False, 1),    # fp32 64 x 64 on split copies, 1x1
+    ("alexnet", "conv4", 1, False, 1),    # fp32 128 x 128 on split copies
+    ("alexnet", "conv2", 1, False, 1),    # fp32 128 x 256 on split copies (the largest AlexNet layer), stream-K
     ("alexnet", "conv2", 1, True, 1),     # ... with a bias in the epilogue (Sec. 5.1)
-    ("alexnet", "conv2", 2, False, 1),    # fp32 128 x 128, channels-last, grouped channel skip (Sec. 5.2)
-    ("alexnet", "conv4", 2, False, 1),    # fp32 64 x 64, channels-last, grouped channel skip
-    ("vgg19", "v10", 1, True, 1),         # fp32 128 x 128, 32-deep chunks, with a bias, stream-K
+    ("alexnet", "conv2", 2, False, 1),    # fp32 128 x 128 on split copies, grouped channel skip (Sec. 5.2)
+    ("alexnet", "conv4", 2, False, 1),    # fp32 128 x 128 on split copies, grouped channel skip
+    ("vgg19", "v10", 1, True, 1),         # fp32 128 x 256 on split copies, with a bias, stream-K
     ("vgg19_bf16", "v1", 1, False, 1),    # bf16 64 x 256, NCHW
     ("resnet18", "l1.0", 1, False, 1),    # bf16 64 x 128, direct-to-LDS
     ("resnet18", "l3.0", 1, False, 1),    # bf16 128 x 128, direct-to-LDS

@@ -1,6 +1,8 @@
-"""The direct-to-LDS main loop (conv_kernel.h) at the edges of its tiles and of its ring: one, two
-and more chunks of K, ragged filter and pixel tiles, taps outside the map on every side, strides and
-non-square kernels, against eq. (1) in float64 on integer data (every sum exact, so bit for bit)."""
+"""The direct-to-LDS main loop (conv_kernel.h), bf16 and fp32 on split copies, at the edges of its
+tiles and of its ring: one, two and more chunks of K, ragged filter and pixel tiles, taps outside the
+map on every side, strides and non-square kernels, against eq. (1) in float64 on integer data (every
+sum exact, so bit for bit); and what the split must not change: 24-bit operands, the error of long
+sums, and infinite, NaN and overflowing operands."""
 import pytest
 import torch
 
@@ -19,14 +21,16 @@ SHAPES = [
     (1, 64, 24, 24, 70, 17, 3, 1, 3),    # one past it: another loop
     (9, 192, 14, 14, 256, 3, 3, 1, 1),   # several filter and pixel tiles, the last ones ragged
 ]
+# the tiles of few filters, and one of few outputs and many chunks (shared by stream-K workgroups)
+FEW_FILTERS = [(2, 32, 9, 9, 31, 3, 3, 1, 1), (4, 96, 30, 31, 33, 3, 3, 1, 1), (1, 512, 7, 7, 512, 3, 3, 1, 1)]
 
 
 def exact_conv(D, W, stride, pad):
     return torch.nn.functional.conv2d(D.double(), W.double(), stride=stride, padding=pad)
 
 
-@pytest.mark.parametrize("dtype", ["bf16"])
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", SHAPES + FEW_FILTERS, ids=lambda s: "-".join(map(str, s)))
 def test_edges_bit_for_bit(shape, dtype):
     print(f"[direct-to-lds] {dtype} {shape}", flush=True)
     n, ch, h, w, m, r, s, u, p = shape
@@ -48,3 +52,96 @@ def test_edges_bit_for_bit(shape, dtype):
     rep = lay.read_report()
     assert not rep.detected
     assert torch.equal(O.double().cpu(), ref)
+
+
+def run_f32(D, W, u=1, p=1, scale=None):
+    n, ch, h, w = D.shape
+    m, _, r, s = W.shape
+    lay = ft.Layer(n, ch, h, w, m, r, s, u, p, "f32")
+    O = lay.empty_output()
+    lay.conv_ws(D.cuda(), W.cuda(), O)
+    return O.cpu()
+
+
+def test_split_holds_every_bit():
+    # products of 24-bit values by powers of two, one a filter: exact only if all three planes are whole
+    g = torch.Generator().manual_seed(5)
+    D = (torch.randint(1 << 23, 1 << 24, (2, 32, 6, 6), generator=g).float()
+         * torch.where(torch.rand(2, 32, 6, 6, generator=g) < 0.5, -1.0, 1.0))
+    W = torch.zeros(64, 32, 1, 1)
+    for m in range(64):
+        W[m, m % 32] = 2.0 ** (m // 32 - 3)
+    ref = exact_conv(D, W, 1, 0)
+    assert torch.equal(run_f32(D, W, p=0).double(), ref)
+    Wm = torch.randint(1 << 23, 1 << 24, (64, 32, 1, 1), generator=g).float() * (W != 0)
+    one = torch.zeros_like(D)
+    one[:, :, 2, 3] = 4.0
+    assert torch.equal(run_f32(one, Wm, p=0).double(), exact_conv(one, Wm, 1, 0))
+
+
+def test_split_error_is_an_fp32_sum_s():
+    # fp32 accumulation of K terms in any order: below 2^-24 K of the sum of magnitudes, and far below
+    # it in the mean (2^-24 sqrt(K) of the root sum of squares); So5 must not add the errors up
+    g = torch.Generator().manual_seed(6)
+    n, ch, hw, m = 8, 256, 14, 128
+    D, W = torch.rand(n, ch, hw, hw, generator=g), torch.randn(m, ch, 3, 3, generator=g) * 0.03
+    ref = exact_conv(D, W, 1, 1)
+    O = run_f32(D, W).double()
+    mag = exact_conv(D, W.abs(), 1, 1)
+    assert ((O - ref).abs() <= 2.0 ** -24 * ch * 9 * mag).all()
+    rel = ((O - ref).norm() / ref.norm()).item()
+    assert rel <= 2.0 ** -24 * (ch * 9) ** 0.5, rel
+    bias = (O - ref).sum((0, 1)).norm() / ((O - ref).norm() * (n * m) ** 0.5)
+    # independent errors give about (n m)^-1/2 = 0.03; errors of one sign 1
+    assert bias < 0.25, bias
+
+
+@pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan"), 3.4028234e38])
+@pytest.mark.parametrize("where", ["D", "W", "both"])
+def test_nonfinite_operands_give_what_fp32_gives(value, where):
+    g = torch.Generator().manual_seed(7)
+    D, W = torch.rand(2, 64, 9, 9, generator=g) + 0.5, torch.randn(96, 64, 3, 3, generator=g)
+    W = torch.where(W.abs() < 0.1, torch.full_like(W, 0.1), W)
+    if where in ("D", "both"):
+        D[1, 5, 4, 4] = value
+        D[0, 63, 0, 0] = value
+    if where in ("W", "both"):
+        W[17, 40, 1, 1] = value
+        if abs(value) < float("inf") and where == "both":
+            W[17, 5] = W[17, 63] = 0.1   # overflow of both signs in one sum would depend on its order
+    ref = torch.nn.functional.conv2d(D, W, padding=1)
+    O = run_f32(D, W)
+    assert torch.equal(torch.isnan(O), torch.isnan(ref))
+    inf = torch.isinf(ref)
+    assert torch.equal(torch.isinf(O), inf) and torch.equal(O[inf], ref[inf])
+    ok = torch.isfinite(ref)
+    assert ok.any()
+    torch.testing.assert_close(O[ok], ref[ok], rtol=1e-4, atol=1e-4)
+
+
+def test_nonfinite_operands_stay_inside_their_group():
+    # two groups of 48 channels: the middle block of 32 channels holds both groups'
+    g = torch.Generator().manual_seed(8)
+    D, W = torch.rand(1, 96, 5, 5, generator=g) + 0.5, torch.rand(64, 48, 3, 3, generator=g) + 0.1
+    D[0, 40, 2, 2] = float("inf")
+    lay = ft.Layer(1, 96, 5, 5, 64, 3, 3, 1, 1, "f32", groups=2)
+    O = lay.empty_output()
+    lay.conv_ws(D.cuda(), W.cuda(), O)
+    ref = torch.nn.functional.conv2d(D, W, padding=1, groups=2)
+    assert torch.equal(torch.isinf(O.cpu()), torch.isinf(ref)) and not torch.isnan(O).any()
+
+
+@pytest.mark.parametrize("d_exp,w_exp", [(-125, 0), (0, -125), (-140, 0), (-70, -60), (100, 0), (60, 30), (0, 100)])
+def test_split_over_the_range_of_fp32(d_exp, w_exp):
+    # operands down to subnormal numbers and up to where their sums still fit
+    g = torch.Generator().manual_seed(9)
+    D = torch.rand(2, 64, 9, 9, generator=g) * 2.0 ** d_exp
+    W = torch.randn(64, 64, 3, 3, generator=g) * 0.05
+    W = W * 2.0 ** w_exp if w_exp > -126 else W
+    ref = exact_conv(D, W, 1, 1)
+    O = run_f32(D, W).double()
+    # an fp32 sum's error, and half of the smallest subnormal for its rounding
+    bound = 2.0 ** -24 * 576 * exact_conv(D.abs(), W.abs(), 1, 1) + 2.0 ** -149
+    assert ((O - ref).abs() <= bound).all()
+    if ref.abs().max() > 1e-30:
+        assert (O - ref).norm() <= 2.0 ** -24 * 24 * ref.norm()

@@ -70,7 +70,9 @@ int sk_decide(const Geom &g, int smax) {
         const int nch = g.R * g.S * (g.C / C::TK);
         const long long tiles = ((g.P_total + C::TP - 1) / C::TP) * (long long)((g.M + C::TM - 1) / C::TM);
         const int S = sk_workgroups<Tr, WM, WP, FM, FP, WEAVE, KVEC, NHWC>(smax);
-        return S > 0 ? stream_k_workgroups(tile_cost<Tile<Tr, WM, WP, FM, FP, WEAVE>>(), tiles, S, nch) : 0;
+        // the plan's own count, or what the schedule comes to on a device that holds fewer
+        return S == smax || S <= 0 ? S
+                                   : stream_k_workgroups(tile_cost<Tile<Tr, WM, WP, FM, FP, WEAVE>>(), tiles, S, nch);
     }
 }
 

@@ -125,13 +125,12 @@ void conv_sk_space(const Geom &g, bool nhwc, int *smax, size_t *part_bytes, long
     with_tile(g, true, [&](auto t) {
         using Tt = decltype(t);
         if constexpr (Tt::SK_FORM) {
-            // room for every workgroup the LDS of kSkComputeUnits compute units could hold
-            const int waves = Tt::NT / 64;
-            long long per_cu = 160LL * 1024 / (long long)Tt::LDS_BYTES;
-            per_cu = per_cu < 32 / waves ? per_cu : 32 / waves;
-            *smax = (int)(per_cu * kSkComputeUnits / 8 * 8);
+            // as many as the schedule would use on a whole device (none: no scratch)
+            constexpr TileCost c = tile_cost<Tt>();
+            const long long tiles = n_tiles(g, Tt::TM, Tt::TP);
+            *smax = stream_k_workgroups(c, tiles, c.resident, g.R * g.S * (g.C / Tt::TK));
             *part_bytes = (size_t)*smax * 2 * Tt::TM * Tt::TP * sizeof(float);
-            *counters = n_tiles(g, Tt::TM, Tt::TP);
+            *counters = *smax > 0 ? tiles : 0;
         }
         return 0;
     });

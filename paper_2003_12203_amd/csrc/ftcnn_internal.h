@@ -250,9 +250,7 @@ int conv_tile_m(const Geom &g, bool nhwc);
 // Threads per workgroup and dynamic LDS bytes of the convolution chosen for this layer.
 void conv_tile_shape(const Geom &g, bool nhwc, int *threads, size_t *lds_bytes);
 // Stream-K scratch of a layer's channels-last convolution: at most smax workgroups, part_bytes of
-// partial accumulators, one int counter per tile (all zero when its kernel has no stream-K form).
-// Sized for kSkComputeUnits compute units; a device with more runs at most smax workgroups.
-constexpr int kSkComputeUnits = 256;
+// partial accumulators, one int counter per tile (all zero when its tiles are not shared).
 void conv_sk_space(const Geom &g, bool nhwc, int *smax, size_t *part_bytes, long long *counters);
 // Stream-K workgroups the plan's channels-last convolution launches on the current device (0: one
 // workgroup per tile).

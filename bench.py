@@ -295,7 +295,8 @@ def kernel_key(ft, lay, path=1):
 def kernel_label(key, dtype):
     tm, tp, tk, loop, nhwc, skip = key
     kinds = {0: "register-staged", 1: "gather woven between MFMAs", 2: "two chunks in flight", 3: "direct-to-LDS",
-             4: "direct-to-LDS, three stages"}
+             4: "direct-to-LDS, three stages", 5: "direct-to-LDS, packed copies",
+             6: "direct-to-LDS, packed copies, three stages"}
     return (f"conv_kernel {dtype} {tm}x{tp} tile, {tk}-deep chunks, {kinds[loop]}"
             f"{', channels-last' if nhwc else ', NCHW gather'}{', grouped channel skip' if skip else ''}")
 
@@ -830,7 +831,7 @@ def _conv_args(short):
     """(TM, TP, TK, loop, EPI, NHWC, GRP) of a conv_kernel instantiation name, else None."""
     import re
     # the last argument, when present, marks the stream-K form of the same tile
-    m = re.match(r"conv_kernel<(F32T|BF16T)<(\d+)>, (\d+), (\d+), (\d+), (\d+), (\d+|true|false), "
+    m = re.match(r"conv_kernel<(F32T|BF16T|S3T)<(\d+)>, (\d+), (\d+), (\d+), (\d+), (\d+|true|false), "
                  r"(true|false), (\d), (true|false), (true|false)(?:, (?:true|false))?>", short)
     if not m:
         return None

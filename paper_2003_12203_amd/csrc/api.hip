@@ -97,8 +97,14 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     if (pl->ver_splits > part_cap) pl->ver_splits = part_cap > 1 ? (int)part_cap : 1;
     pl->nhwc = allow_nhwc && nhwc_layer(g);
     g.split = pl->nhwc && allow_split && split_layer(g);
+    g.pk = g.prun = g.pcs = g.pw = g.pupt = g.pkk = 0;
+    if (allow_nhwc && !pl->nhwc && (allow_split || d->dtype == FTCNN_BF16)) {
+        pack_geom(g);
+        g.split = g.pk && d->dtype == FTCNN_F32;
+    }
+    pl->copies = pl->nhwc || g.pk;
     // summations fused into the convolution epilogue: one slice per (filter tile, image)
-    pl->sum_splits = (int)(ceil_div(g.M, conv_tile_m(g, pl->nhwc)) * g.N);
+    pl->sum_splits = (int)(ceil_div(g.M, conv_tile_m(g, pl->copies)) * g.N);
     // correction: the standalone launch hands the flagged positions over from at most corr_blocks
     // workgroups; every path leaves the chain to the wide stage, whose scratch is laid out by
     // corr_layout
@@ -125,8 +131,9 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     pl->prep_ns = 1;
     pl->co_in_conv = false;
     pl->co = CocTile{1, 1, 1, 1, 1, 1, 0, 1};
-    if (pl->nhwc) {
-        const long long tiles = (long long)(g.C / prep_tile_channels(g)) * ceil_div((long long)g.H * g.W, prep_tile_positions(g));
+    if (pl->copies) {
+        // (packed copies: the encode is the copy's too, over all images at once)
+        const long long tiles = g.pk ? 1024 : (long long)(g.C / prep_tile_channels(g)) * ceil_div((long long)g.H * g.W, prep_tile_positions(g));
         const int min_imgs = g.dtype == FTCNN_F32 ? 16 : 32;   // a multiple of both image batches
         long long most = g.N / min_imgs;
         most = most > 16 ? 16 : (most < 1 ? 1 : most);
@@ -157,11 +164,11 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     // 256 zero bytes for loads that fall outside the operands (written by the copy), directly in
     // front of Dt: the direct-to-LDS loads reach both through one buffer descriptor
     pl->off_zero = off;
-    off += pl->nhwc ? 256 : 0;
+    off += pl->copies ? 256 : 0;
     pl->off_dt = off;
-    off += pl->nhwc ? align256((size_t)g.N * CHW * cs) : 0;
+    off += pl->nhwc ? align256((size_t)g.N * CHW * cs) : (g.pk ? align256((size_t)g.N * g.H * g.pw * g.pcs * cs) : 0);
     pl->off_wt = off;
-    off += pl->nhwc ? align256((size_t)g.M * K * cs) : 0;
+    off += pl->nhwc ? align256((size_t)g.M * K * cs) : (g.pk ? align256((size_t)g.M * g.pkk * cs) : 0);
     pl->off_encp = off;
     off += pl->prep_ns > 1 ? align256(2ull * pl->prep_ns * CHW * sizeof(double)) : 0;
     pl->off_copart = off;
@@ -434,7 +441,7 @@ int ftcnn_conv_tile(const ftcnn_conv_desc *desc, int32_t path, int32_t out[6]) {
     if (!out) return fail(FTCNN_E_ARG, "conv_tile: null output");
     if (path != 0 && path != 1) return fail(FTCNN_E_ARG, "conv_tile: path %d (0 or 1)", path);
     int o[6];
-    conv_tile_info(pl.g, path == 1 && pl.nhwc, o);
+    conv_tile_info(pl.g, path == 1 && pl.copies, o);
     for (int i = 0; i < 6; ++i) out[i] = o[i];
     return FTCNN_OK;
 }

@@ -484,7 +484,7 @@ __device__ inline unsigned tap_mask(const Geom &g, int ih0, int iw0) {
 // 125 us; so it takes 110 us, 1075 TFLOP/s on 77 % of the compute units (torch.mm on 8192^3 random
 // bf16 operands: 1205 TFLOP/s).  Spreading a chunk's loads over two or three steps: 107-111 us there,
 // 1-5 % slower on the 128 x 128 and smaller tiles.
-template <typename C, int NP, int STAGES, int FM, int FP>
+template <typename C, int NP, int STAGES, bool PACK, int FM, int FP>
 __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, int m0, long long p0,
                                     const unsigned char *zp_dt, unsigned char *smem, floatx16 (&acc)[FM][FP],
                                     int tid, int arow0, int brow0, int k0, int kn, int c_lo, int c_hi) {
@@ -502,21 +502,52 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the unit of row r that LDS position c holds (the map is its own inverse)
     auto unit = [](int r, int c) { return NP == 1 ? c ^ ((r >> 1) & 7) : c ^ ((r >> 2) & 3); };
-    const __amdgpu_buffer_rsrc_t rw = buffer_rsrc(Wt, (unsigned)g.M * (unsigned)g.K * EB);
-    const __amdgpu_buffer_rsrc_t rd = buffer_rsrc(zp_dt, 256u + (unsigned)g.N * (unsigned)g.CHW * EB);
+    const unsigned kk = PACK ? (unsigned)g.pkk : (unsigned)g.K;   // values of a filter's row
+    const unsigned px_v = PACK ? (unsigned)g.pcs : (unsigned)g.C;  // values of a pixel, a row, an image
+    const unsigned row_v = (PACK ? (unsigned)g.pw : (unsigned)g.W) * px_v;
+    const unsigned img_v = PACK ? (unsigned)g.H * row_v : (unsigned)g.CHW;
+    const __amdgpu_buffer_rsrc_t rw = buffer_rsrc(Wt, (unsigned)g.M * kk * EB);
+    const __amdgpu_buffer_rsrc_t rd = buffer_rsrc(zp_dt, 256u + (unsigned)g.N * img_v * EB);
     unsigned a_off[NIA];
 #pragma unroll
     for (int j = 0; j < NIA; ++j) {
         const int s = (j * NW + w) * 64 + lane, row = s / ROWL;
         const int m = m0 + row < g.M ? m0 + row : g.M - 1;   // rows past M are never stored
-        a_off[j] = (unsigned)m * (unsigned)g.K * EB + 16u * (unsigned)unit(row, s % ROWL);
+        a_off[j] = (unsigned)m * kk * EB + 16u * (unsigned)unit(row, s % ROWL);
     }
+    // packed copies: a slot's unit of eight channels of a chunk belongs to a tap of its own, so every
+    // slot walks the taps (r, s) and the units o of a tap by itself, UPC units a chunk: d_r kernel rows,
+    // d_s columns and d_o units (taps past the last have no bit in the mask)
+    constexpr int UPC = CH / 8;
+    const int p_s = PACK ? (g.prun ? 1 : g.S) : 1;
+    const int d_t = PACK ? UPC / g.pupt : 0, d_o = PACK ? UPC - d_t * g.pupt : 0, d_r = PACK ? d_t / p_s : 0,
+              d_s = PACK ? d_t - d_r * p_s : 0;
+    int w_o[PACK ? NIB : 1], w_r[PACK ? NIB : 1], w_s[PACK ? NIB : 1];
     // load j of a chunk: the weight slots, then the input slots
     unsigned b_off[NIB], b_tap[NIB];
-    auto issue = [&](const TapWalk &t, unsigned char *base, int j) {
+    struct Walk {
+        TapWalk t;
+        unsigned k;   // packed: the chunk's first byte in a filter's row
+    };
+    auto issue = [&](const Walk &wk, unsigned char *base, int j) {
+        const TapWalk &t = wk.t;
         if (j < NIA) {
             if (NLA % NW != 0 && j * NW + w >= NLA) return;
-            buffer_load_lds16(rw, base + (j * NW + w) * 1024, a_off[j], EB * (unsigned)t.kb(g));
+            buffer_load_lds16(rw, base + (j * NW + w) * 1024, a_off[j], PACK ? wk.k : EB * (unsigned)t.kb(g));
+        } else if constexpr (PACK) {
+            const int i = j - NIA;
+            const int in = __builtin_amdgcn_sbfe((int)b_tap[i], w_r[i], 1) &
+                           __builtin_amdgcn_sbfe((int)b_tap[i], w_s[i] + 16, 1);
+            const unsigned tap = EB * ((unsigned)w_r[i] * row_v + (unsigned)w_s[i] * px_v + 8u * (unsigned)w_o[i]);
+            buffer_load_lds16(rd, base + STAGE_A + (i * NW + w) * 1024, (b_off[i] + tap) & (unsigned)in, 0u);
+            w_o[i] += d_o;
+            const int c_o = w_o[i] >= g.pupt;
+            w_o[i] -= c_o ? g.pupt : 0;
+            w_s[i] += d_s + c_o;
+            const int c_s = w_s[i] >= p_s;
+            w_s[i] -= c_s ? p_s : 0;
+            w_r[i] += d_r + c_s;
+            w_r[i] = w_r[i] < 15 ? w_r[i] : 15;   // bit 15 is never set: R <= 15
         } else {
             const int i = j - NIA;
             const unsigned tap = EB * (unsigned)((t.r * g.W + t.s) * g.C + t.c0);
@@ -524,31 +555,46 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
             buffer_load_lds16(rd, base + STAGE_A + (i * NW + w) * 1024, (b_off[i] + tap) & (unsigned)in, 0u);
         }
     };
-    const int nch = kn >= 0 ? kn : g.R * g.S * ((c_hi - c_lo) / CH);
-    TapWalk ti = tap_at(g, k0, CH);   // the chunk whose loads are issued next
-    ti.c0 += c_lo;
+    auto advance = [&](Walk &wk) {
+        if constexpr (PACK) wk.k += CH * EB;
+        else wk.t.next(g, CH);
+    };
+    const int nch = kn >= 0 ? kn : (PACK ? g.pkk / CH : g.R * g.S * ((c_hi - c_lo) / CH));
+    Walk ti{PACK ? TapWalk{0, 0, 0} : tap_at(g, k0, CH), 0u};   // the chunk whose loads are issued next
+    ti.t.c0 += c_lo;
     // the first chunk's weights are on their way while the pixels are worked out
 #pragma unroll
     for (int j = 0; j < NIA; ++j) issue(ti, smem, j);
 #pragma unroll
     for (int j = 0; j < NIB; ++j) {
-        const int s = (j * NW + w) * 64 + lane, row = s / ROWL;
+        const int s = (j * NW + w) * 64 + lane, row = s / ROWL, u = unit(row, s % ROWL);
         // columns past the end are never stored; P_total < 2^31 on these layers
         const unsigned pg = (unsigned)p0 + row < (unsigned)g.P_total ? (unsigned)p0 + row : (unsigned)g.P_total - 1;
         const unsigned n = pg / (unsigned)g.EF, pix = pg - n * (unsigned)g.EF;
         const unsigned x = pix / (unsigned)g.F, y = pix - x * (unsigned)g.F;
-        const int ih0 = g.U * (int)x - g.P, iw0 = g.U * (int)y - g.P;
+        const int ih0 = g.U * (int)x - g.P;
+        int iw0 = g.U * (int)y - g.P;
         b_tap[j] = tap_mask(g, ih0, iw0);
+        if constexpr (PACK) {
+            if (g.prun) {   // the copy has the padding's columns
+                iw0 = g.U * (int)y;
+                b_tap[j] = (b_tap[j] & 0xFFFFu) | 0x10000u;
+            }
+            const int t = u / NP, tp = t / g.pupt;   // the slot's unit of the first chunk
+            w_o[j] = t - tp * g.pupt;
+            w_r[j] = tp / p_s;
+            w_s[j] = tp - w_r[j] * p_s;
+        }
         // 32-bit wrap-around arithmetic: the sum with a valid tap's offset is the element's offset
-        b_off[j] = 256u + EB * (n * (unsigned)g.CHW + (unsigned)(ih0 * g.W + iw0) * (unsigned)g.C) +
-                   16u * (unsigned)unit(row, s % ROWL);
+        b_off[j] = 256u + EB * (n * img_v + (unsigned)ih0 * row_v + (unsigned)iw0 * px_v) +
+                   16u * (unsigned)(PACK ? u % NP : u);
     }
 #pragma unroll
     for (int st = 0; st < STAGES; ++st)
         if (st < nch) {
 #pragma unroll
             for (int j = st == 0 ? NIA : 0; j < NI; ++j) issue(ti, smem + st * STAGE, j);
-            ti.next(g, CH);
+            advance(ti);
         }
     // (a wave with fewer weight loads than NIA must not leave one of its first chunk's behind)
     if (nch >= STAGES) wait_vmcnt<(STAGES - 1) * (NLA % NW ? NI - 1 : NI)>();
@@ -556,11 +602,17 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     lds_barrier();
     // fragment reads: lanes 0-31 take the first half of the chunk's units of a plane, lanes 32-63 the second
     const int l32 = lane & 31, h = lane >> 5;
-    constexpr int PU = ROWL / NP;                     // units per plane
+    constexpr int PU = ROWL / NP;                     // groups of eight channels, NP units (planes) each
     const int sw = NP == 1 ? (l32 >> 1) & 7 : (l32 >> 2) & 3;
-    int fpos[Q];
+    int fpos[Q][NP];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) fpos[q] = (((PU / 2) * h + q) ^ sw) * 16;
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int pl = 0; pl < NP; ++pl) {
+            // split blocks hold plane after plane, packed ones group after group
+            const int grp = (PU / 2) * h + q;
+            fpos[q][pl] = ((PACK ? grp * NP + pl : pl * PU + grp) ^ sw) * 16;
+        }
     const int arow = (arow0 + l32) * C::ROWB, brow = STAGE_A + (brow0 + l32) * C::ROWB;
     bf16x8 fa[2][NP][FM], fb[2][NP][FP];
     constexpr int NR = NP * (FM + FP);                // reads per step, planes outer (high first)
@@ -568,10 +620,10 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
         const int pl = i / (FM + FP), k = i % (FM + FP);
         if (k < FP)
             fb[set][pl][k] = __builtin_bit_cast(
-                bf16x8, *reinterpret_cast<const u16x8 *>(stage + brow + fpos[q] + k * 32 * C::ROWB + pl * PU * 16));
+                bf16x8, *reinterpret_cast<const u16x8 *>(stage + brow + fpos[q][pl] + k * 32 * C::ROWB));
         else
             fa[set][pl][k - FP] = __builtin_bit_cast(
-                bf16x8, *reinterpret_cast<const u16x8 *>(stage + arow + fpos[q] + (k - FP) * 32 * C::ROWB + pl * PU * 16));
+                bf16x8, *reinterpret_cast<const u16x8 *>(stage + arow + fpos[q][pl] + (k - FP) * 32 * C::ROWB));
     };
     // the products of one step: all of bf16; of a split layer the six whose planes' orders sum to at
     // most two (the other three are below 2^-24 of the product)
@@ -610,7 +662,7 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (MORE) ti.next(g, CH);
+        if (MORE) advance(ti);
     };
     using std::integral_constant;
     using yes = integral_constant<bool, true>;
@@ -630,13 +682,15 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     wait_lgkm0();
 }
 
-// The outputs of a split tile that came out non-finite, again in fp32 from D and W as given (eq. (1),
-// the filter's own channels): an infinite, NaN or nearly overflowing operand has no split whose planes
+// The outputs of a split or packed tile that came out non-finite, again in fp32 from D and W as given
+// (eq. (1), the filter's own channels).  On packed copies the zeros that fill a filter's row meet input
+// values beyond the tap, which must not count even when they are infinite.  On split copies an infinite, NaN or nearly overflowing operand has no split whose planes
 // multiply to what fp32 gives (its lower planes are NaN or of either sign), so such an output says only
 // that it must be redone.  The accumulators pass through LDS so that the loop over them is not unrolled;
 // a finite tile pays one multiply-add an accumulator and a barrier.
 template <typename C, int FM, int FP>
-__device__ inline void redo_nonfinite(const Geom &g, const float *__restrict__ D, const float *__restrict__ W, int m0,
+__device__ inline void redo_nonfinite(const Geom &g, const typename C::T *__restrict__ D,
+                                      const typename C::T *__restrict__ W, int m0,
                                       long long p0, unsigned char *smem, floatx16 (&acc)[FM][FP], int tid, int arow0,
                                       int brow0) {
     constexpr int NA = FM * FP * 16;
@@ -667,10 +721,10 @@ __device__ inline void redo_nonfinite(const Geom &g, const float *__restrict__ D
         for (int c = c0; c < c0 + g.Cg && !isnan(s); ++c)   // NaN stays NaN
             for (int r = 0; r < g.R; ++r) {
                 if ((unsigned)(ih0 + r) >= (unsigned)g.H) continue;
-                const float *d = D + n * g.CHW + ((long long)c * g.H + ih0 + r) * g.W;
-                const float *w = W + ((long long)m * g.C + c) * (g.R * g.S) + r * g.S;
+                const auto *d = D + n * g.CHW + ((long long)c * g.H + ih0 + r) * g.W;
+                const auto *w = W + ((long long)m * g.C + c) * (g.R * g.S) + r * g.S;
                 for (int q = 0; q < g.S; ++q)
-                    if ((unsigned)(iw0 + q) < (unsigned)g.W) s = fmaf(d[iw0 + q], w[q], s);
+                    if ((unsigned)(iw0 + q) < (unsigned)g.W) s = fmaf(Elem<typename C::T>::load(d, iw0 + q), Elem<typename C::T>::load(w, q), s);
             }
         mine[k * C::NT] = s;
     }
@@ -698,7 +752,7 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
                                                             typename Tr::T *__restrict__ O, Geom g,
                                                             int tiles_m, int tiles_total, int m_major,
                                                             const void *zp, Epi<EPI> ep, SkArgs sk) {
-    using C = Cfg<Tr, WM, WP, FM, FP, KVEC, (WEAVE >= 3 ? WEAVE - 1 : 0)>;
+    using C = Cfg<Tr, WM, WP, FM, FP, KVEC, dma_stages(WEAVE)>;
     using T = typename C::T;
     extern __shared__ __align__(16) unsigned char smem[];
     T *As0 = reinterpret_cast<T *>(smem);
@@ -880,7 +934,7 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
         const int mlast = (m0 + C::TM < g.M ? m0 + C::TM : g.M) - 1;
         const int c_lo = group_first_channel(g, m0) / C::TK * C::TK;
         const int c_hi = (group_first_channel(g, mlast) + g.Cg + C::TK - 1) / C::TK * C::TK;
-        dma_mainloop<C, Tr::NP, WEAVE - 1, FM, FP>(Wt, g, m0, p0, static_cast<const unsigned char *>(zp), smem, acc, tid, arow0,
+        dma_mainloop<C, Tr::NP, dma_stages(WEAVE), (WEAVE >= 5), FM, FP>(Wt, g, m0, p0, static_cast<const unsigned char *>(zp), smem, acc, tid, arow0,
                                         brow0, k0, kn, c_lo, c_hi);
     } else if constexpr (NHWC && WEAVE == 2) {
         // channels-last, two chunks in flight: chunk kc + 2 is loaded into one register set
@@ -1080,9 +1134,10 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
             for (int j = 0; j < FP; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] *= e & 1 ? -kSplitUnscale : kSplitUnscale;
-        redo_nonfinite<C, FM, FP>(g, static_cast<const float *>(ep.src_dw.d), static_cast<const float *>(ep.src_dw.w),
-                                  m0, p0, smem, acc, tid, arow0, brow0);
     }
+    if constexpr (DMA && (Tr::NP == 3 || WEAVE >= 5))
+        redo_nonfinite<C, FM, FP>(g, static_cast<const T *>(ep.src_dw.d), static_cast<const T *>(ep.src_dw.w), m0, p0,
+                                  smem, acc, tid, arow0, brow0);
 
     // epilogue: lane owns pixel (lane & 31) of each 32-wide block; register e of
     // block (i, j) is row 8*(e/4) + 4*(lane/32) + e%4 of that block

@@ -11,7 +11,7 @@ namespace convk {
 // plain twin split K at the same places and store the same bits), at most smax, a multiple of 8.
 template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE, bool KVEC, bool NHWC>
 int sk_workgroups(int smax) {
-    using C = Cfg<Tr, WM, WP, FM, FP, KVEC, (WEAVE >= 3 ? WEAVE - 1 : 0)>;
+    using C = Cfg<Tr, WM, WP, FM, FP, KVEC, dma_stages(WEAVE)>;
     static const int per_cu = [] {
         int lo = 1 << 30;
         const void *k[3] = {
@@ -62,8 +62,8 @@ int sk_workgroups(int smax) {
 // 256 x 256 tile (eight waves, at most 256 registers each) spills in that form.
 template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE, bool KVEC, bool NHWC>
 int sk_decide(const Geom &g, int smax) {
-    using C = Cfg<Tr, WM, WP, FM, FP, KVEC, (WEAVE >= 3 ? WEAVE - 1 : 0)>;
-    if constexpr (!(NHWC && WEAVE >= 3 && sizeof(typename C::T) == 4)) {
+    using C = Cfg<Tr, WM, WP, FM, FP, KVEC, dma_stages(WEAVE)>;
+    if constexpr (!(NHWC && (WEAVE == 3 || WEAVE == 4) && sizeof(typename C::T) == 4)) {
         return 0;
     } else {
         if (smax <= 0 || g.G > 1) return 0;
@@ -79,7 +79,7 @@ int sk_decide(const Geom &g, int smax) {
 template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE, bool KVEC, int EPI, bool NHWC, bool GRP = false>
 hipError_t launch_one(const Geom &g, const void *D, const void *W, void *O, hipStream_t st, int m_major,
                       const void *zp, const Epi<EPI> &ep, const SkArgs &skin) {
-    using C = Cfg<Tr, WM, WP, FM, FP, KVEC, (WEAVE >= 3 ? WEAVE - 1 : 0)>;
+    using C = Cfg<Tr, WM, WP, FM, FP, KVEC, dma_stages(WEAVE)>;
     using T = typename C::T;
     static_assert(EPI == 0 || (size_t)WM * 3 * C::TP * sizeof(double) <= C::LDS_BYTES, "epilogue fold fits LDS");
     const int tiles_m = (g.M + C::TM - 1) / C::TM;
@@ -87,7 +87,7 @@ hipError_t launch_one(const Geom &g, const void *D, const void *W, void *O, hipS
     const long long total = tiles_p * tiles_m;
     Epi<EPI> e = ep;
     SkArgs sk{nullptr, nullptr, 0, 0, 0};
-    constexpr bool SKF = NHWC && WEAVE >= 3 && sizeof(T) == 4;   // has a stream-K form
+    constexpr bool SKF = NHWC && (WEAVE == 3 || WEAVE == 4) && sizeof(T) == 4;   // has a stream-K form
     if constexpr (SKF) {
         if (skin.S > 0 && skin.part && skin.cnt) {
             const int S = sk_decide<Tr, WM, WP, FM, FP, WEAVE, KVEC, NHWC>(g, skin.S);
@@ -173,7 +173,8 @@ hipError_t Tile<Tr, WM, WP, FM, FP, WEAVE>::run(const Geom &g, const void *D, co
         // behind the zero page (one buffer descriptor reaches both)
         if (!nhwc || !zp || static_cast<const char *>(zp) + 256 != static_cast<const char *>(D))
             return hipErrorInvalidValue;
-        return launch_one<Tr, WM, WP, FM, FP, WEAVE, true, EPI, true>(g, D, W, O, st, 0, zp, ep, sk);
+        // (the kernel's D is the input as given, for the encode workgroups)
+        return launch_one<Tr, WM, WP, FM, FP, WEAVE, true, EPI, true>(g, ep.src_dw.d, W, O, st, 0, zp, ep, sk);
     } else {
         if constexpr (WEAVE != 2) {
             if (nhwc && g.G > 1)   // grouped: the loop that skips other groups' channels

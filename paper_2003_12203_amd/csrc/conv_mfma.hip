@@ -28,6 +28,16 @@ long long n_tiles(const Geom &g, int tm, int tp) {
 // channels-last copies).
 template <typename Fn>
 auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
+    if (nhwc && g.pk) {
+        if (g.dtype == FTCNN_BF16) {
+            if (g.M <= 64) return n_tiles(g, 64, 256) >= 512 ? f(BF16P_64x256{}) : f(BF16P_64x128{});
+            return n_tiles(g, 128, 128) >= 256 ? f(BF16P_128x128{}) : f(BF16P_64x64{});
+        }
+        if (g.M <= 32) return f(S3P_32x128{});
+        if (g.M <= 64) return f(S3P_64x128{});
+        if (g.M <= 96 && n_tiles(g, 96, 256) >= 256) return f(S3P_96x256{});
+        return n_tiles(g, 128, 128) >= 128 ? f(S3P_128x128{}) : f(S3P_64x64{});
+    }
     if (nhwc && g.split) {
         if (g.M <= 32) return f(S3_32x128{});
         // the tile with the least predicted time, on whole tiles or shared ones
@@ -103,7 +113,7 @@ void conv_tile_info(const Geom &g, bool nhwc, int out[6]) {
         out[2] = Tt::TK;
         out[3] = Tt::WEAVE_KIND;
         out[4] = nhwc ? 1 : 0;
-        out[5] = (nhwc && g.G > 1 && Tt::WEAVE_KIND != 2) ? 1 : 0;
+        out[5] = (nhwc && g.G > 1 && Tt::WEAVE_KIND != 2 && Tt::WEAVE_KIND < 5) ? 1 : 0;
         return 0;
     });
 }
@@ -163,13 +173,13 @@ hipError_t launch_conv_sums(const Plan &pl, const void *D, const void *W, void *
     char *w = static_cast<char *>(ws);
     double *cd1 = ck ? ck->cd1 : nullptr, *cd2 = ck ? ck->cd2 : nullptr;
     const void *Dc = D, *Wc = W;
-    const void *zp = pl.nhwc ? w + pl.off_zero : nullptr;   // zeroed by the channels-last copy
+    const void *zp = pl.copies ? w + pl.off_zero : nullptr;   // zeroed by the copy
     int aux_kind = 0, aux_blocks = 0, co_slices = 0;
     CdSrc src{cd1, cd2, 0, 1};
-    if (pl.nhwc) {
-        // channels-last copies; the copy of D also encodes Cd1, Cd2 (if asked and not given)
-        const hipError_t e = cd_given ? launch_prep(pl, D, W, nullptr, nullptr, ws, st)
-                                      : launch_prep(pl, D, W, cd1, cd2, ws, st);
+    if (pl.copies) {
+        // the copy of D also encodes Cd1, Cd2 (if asked and not given)
+        double *e1 = cd_given ? nullptr : cd1, *e2 = cd_given ? nullptr : cd2;
+        const hipError_t e = pl.nhwc ? launch_prep(pl, D, W, e1, e2, ws, st) : launch_pack(pl, D, W, e1, e2, ws, st);
         if (e != hipSuccess) return e;
         Dc = w + pl.off_dt;
         Wc = w + pl.off_wt;
@@ -190,27 +200,27 @@ hipError_t launch_conv_sums(const Plan &pl, const void *D, const void *W, void *
         aux_kind = 1;   // encode workgroups; their count follows the tile's threads
     }
     CocTile co = pl.co;
-    if (!(pl.nhwc && pl.prep_ns > 1) || cd_given) co.comb_blocks = 0;
+    if (pl.prep_ns == 1 || cd_given) co.comb_blocks = 0;
     double *part = reinterpret_cast<double *>(w + pl.off_sums);
     double *copart = reinterpret_cast<double *>(w + pl.off_copart);
     const double *cw1 = ck ? ck->cw1 : nullptr, *cw2 = ck ? ck->cw2 : nullptr;
     const float *bias = ck ? ck->bias : nullptr;
     if (nf == 0) {
         Epi<1> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, src, cw1, cw2, copart, co, co_slices, {}, bias, {D, W}};
-        return with_tile(pl.g, pl.nhwc,
-                         [&](auto t) { return decltype(t)::run(pl.g, Dc, Wc, O, st, ep, pl.nhwc, zp, sk_args(pl, ws)); });
+        return with_tile(pl.g, pl.copies,
+                         [&](auto t) { return decltype(t)::run(pl.g, Dc, Wc, O, st, ep, pl.copies, zp, sk_args(pl, ws)); });
     }
     Epi<2> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, src, cw1, cw2, copart, co, co_slices, {}, bias, {D, W}};
     for (int i = 0; i < nf; ++i) ep.fl.f[i] = faults[i];
     ep.fl.n = nf;
-    return with_tile(pl.g, pl.nhwc,
-                     [&](auto t) { return decltype(t)::run(pl.g, Dc, Wc, O, st, ep, pl.nhwc, zp, sk_args(pl, ws)); });
+    return with_tile(pl.g, pl.copies,
+                     [&](auto t) { return decltype(t)::run(pl.g, Dc, Wc, O, st, ep, pl.copies, zp, sk_args(pl, ws)); });
 }
 
 hipError_t launch_conv_ws(const Plan &pl, const void *D, const void *W, void *O, void *ws, hipStream_t st,
                           const float *bias) {
-    if (!pl.nhwc) return launch_conv(pl, D, W, O, st, bias);
-    const hipError_t e = launch_prep(pl, D, W, nullptr, nullptr, ws, st);
+    if (!pl.copies) return launch_conv(pl, D, W, O, st, bias);
+    const hipError_t e = pl.nhwc ? launch_prep(pl, D, W, nullptr, nullptr, ws, st) : launch_pack(pl, D, W, nullptr, nullptr, ws, st);
     if (e != hipSuccess) return e;
     char *w = static_cast<char *>(ws);
     const Epi<0> ep{bias, {D, W}};

@@ -118,6 +118,9 @@ template <> struct Epi<0> {
     Given src_dw;
 };
 
+// Main loops from 3 on load straight to LDS: 3 and 4 through a ring of two and three stages, 5 and 6 the
+// same on packed copies (Geom::pk).
+constexpr int dma_stages(int weave) { return weave >= 5 ? weave - 3 : (weave >= 3 ? weave - 1 : 0); }
 // One tile configuration.  WEAVE: the main loop (0 register-staged, 1 gather woven between the
 // MFMAs, 2 two chunks in flight, 3 direct-to-LDS).  run() and stream_k() are instantiated per tile
 // in the conv_*.hip files.
@@ -127,8 +130,8 @@ template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE> struct Tile {
     static constexpr int TK = Tr::TK;
     static constexpr int WEAVE_KIND = WEAVE;
     static constexpr int NT = Cfg<Tr, WM, WP, FM, FP>::NT;
-    static constexpr size_t LDS_BYTES = Cfg<Tr, WM, WP, FM, FP, true, (WEAVE >= 3 ? WEAVE - 1 : 0)>::LDS_BYTES;
-    static constexpr bool SK_FORM = WEAVE >= 3 && sizeof(typename Tr::T) == 4;
+    static constexpr size_t LDS_BYTES = Cfg<Tr, WM, WP, FM, FP, true, dma_stages(WEAVE)>::LDS_BYTES;
+    static constexpr bool SK_FORM = (WEAVE == 3 || WEAVE == 4) && sizeof(typename Tr::T) == 4;
     // stream-K workgroups of the channels-last form on the current device (0: whole tiles)
     static int stream_k(const Geom &g, int smax);
     // NCHW: D and W as given; NHWC: the channels-last copies Dt and Wt (always aligned, K % VEC == 0)
@@ -154,6 +157,16 @@ using S3_128x128 = Tile<S3T<32>, 2, 4, 2, 1, 4>;
 using S3_64x64 = Tile<S3T<32>, 2, 2, 1, 1, 4>;
 using S3_64x128 = Tile<S3T<32>, 1, 4, 2, 1, 3>;
 using S3_32x128 = Tile<S3T<32>, 1, 4, 1, 1, 3>;
+// packed copies
+using S3P_32x128 = Tile<S3T<32>, 1, 4, 1, 1, 5>;
+using S3P_64x128 = Tile<S3T<32>, 1, 4, 2, 1, 5>;
+using S3P_96x256 = Tile<S3T<32>, 1, 8, 3, 1, 5>;
+using S3P_128x128 = Tile<S3T<32>, 2, 4, 2, 1, 6>;
+using S3P_64x64 = Tile<S3T<32>, 2, 2, 1, 1, 6>;
+using BF16P_64x128 = Tile<BF16T<64>, 1, 4, 2, 1, 5>;
+using BF16P_64x256 = Tile<BF16T<64>, 1, 8, 2, 1, 5>;
+using BF16P_128x128 = Tile<BF16T<64>, 2, 2, 2, 2, 5>;
+using BF16P_64x64 = Tile<BF16T<64>, 2, 2, 1, 1, 5>;
 using BF16_M32 = Tile<BF16T<32>, 1, 4, 1, 2, 0>;
 using BF16_M64 = Tile<BF16T<32>, 1, 4, 2, 2, 2>;
 using BF16_128x128_K64 = Tile<BF16T<64>, 2, 2, 2, 2, 2>;

@@ -28,6 +28,13 @@ struct Geom {
     // fp32 layers whose channels-last copies hold every value as three bf16 planes whose sum it is
     // (split_layer): the convolution multiplies the planes on the bf16 matrix cores
     int split;
+    // Packed layers (pk; channels not a multiple of 32, the 3-channel stems among them): the copy of D
+    // is [N][H][pw][pcs] with its rows' units of eight values on 16-byte (split: 48-byte) boundaries,
+    // and a filter's row of the copy of W is the taps' units one after the other, pupt units a tap, pkk
+    // values in all (zeros up to whole chunks).  prun = 0: a tap is one (r, s), pcs the channels rounded
+    // up to eight.  prun = 1: a tap is a whole kernel row, its S columns of pcs (4 or 8) channels run on
+    // in memory, and the copy carries the zero columns of the padding.
+    int pk, prun, pcs, pw, pupt, pkk;
 };
 // bytes of one value in the channels-last copies
 __host__ __device__ inline int copy_bytes(const Geom &g) { return g.dtype == FTCNN_BF16 ? 2 : (g.split ? 6 : 4); }
@@ -62,6 +69,7 @@ struct Plan {
     int corr_blocks;                  // workgroups of the standalone correction kernel
     int sum_splits;                   // partial-sum slices written by the convolution epilogue
     bool nhwc;                        // the convolution reads channels-last copies of D and W
+    bool copies;                      // ... those, or packed ones (Geom::pk)
     int prep_ns;                      // image ranges of the encode fused into the channels-last copy
     bool co_in_conv;                  // Co5..Co7 partials computed by workgroups of the convolution launch
     CocTile co;                       // their tiling (co_in_conv)
@@ -259,12 +267,45 @@ int conv_stream_k(const Plan &pl);
 // Layers whose convolution reads channels-last copies (pl.nhwc): Ch a multiple of 32 (and
 // kernels of at most 4096 taps, whose weight rows the copy stages in LDS).
 inline bool nhwc_layer(const Geom &g) { return g.C % 32 == 0 && g.R * g.S <= 4096; }
+constexpr double kPackFlops = 1e7;
 // Layers the direct-to-LDS loops take: they reach the copies (`bytes` a value) through 32-bit buffer
 // offsets, count pixels in 32 bits and keep a pixel's taps inside the map in two 16-bit masks.
 inline bool dma_layer(const Geom &g, int bytes) {
     const unsigned long long lim = 1ull << 32;
     return (unsigned long long)g.M * g.K * bytes < lim && 256 + (unsigned long long)g.N * g.CHW * bytes < lim &&
            g.P_total < (1LL << 31) && g.R <= 16 && g.S <= 16;
+}
+// The packed form of a layer that has no 32-channel blocks (Geom::pk), or pk = 0 where it has none.
+inline void pack_geom(Geom &g) {
+    const int np = g.dtype == FTCNN_BF16 ? 1 : 3, chunk = g.dtype == FTCNN_BF16 ? 64 : 32;
+    g.pk = 0;
+    if (g.C % 32 == 0 || g.R > 15 || g.S > 15 || g.P_total >= (1LL << 31)) return;
+    g.prun = g.C <= 8;
+    if (g.prun) {
+        // a run starts at column U y: on a unit when the stride is even (four channels a column) or a
+        // column is a whole unit
+        g.pcs = g.C <= 4 && g.U % 2 == 0 ? 4 : 8;
+        g.pupt = (g.S * g.pcs + 7) / 8;
+        const long long pw = ((long long)g.U * (g.F - 1) + g.pupt * 8 / g.pcs + 1) / 2 * 2;
+        if (pw > (1 << 24)) return;
+        g.pw = (int)pw;
+    } else {
+        g.pcs = (g.C + 7) / 8 * 8;
+        g.pupt = g.pcs / 8;
+        g.pw = g.W;
+    }
+    const long long units = (long long)g.pupt * g.R * (g.prun ? 1 : g.S);
+    const long long kk = (units * 8 + chunk - 1) / chunk * chunk;
+    const unsigned long long lim = 1ull << 32;
+    if ((unsigned long long)g.M * kk * 2 * np >= lim ||
+        256 + (unsigned long long)g.N * g.H * g.pw * g.pcs * 2 * np >= lim)
+        return;
+    g.pkk = (int)kk;
+    // Short sums stay on the gather: their tiles are all prologue and stores (VGG-19 v1, K = 27: 166 us on
+    // the gather, 279 us packed; with K = 75 even, ResNet-18's stem, K = 147: 262 us against 193 us); so do
+    // small layers, where another launch costs more than it saves.
+    if (g.K < 72 || 2.0 * g.M * (double)g.P_total * g.K < kPackFlops) return;
+    g.pk = 1;
 }
 // The copies of a split layer hold D and W times 2^24, and its convolution's epilogue takes 2^48 out
 // again: the bf16 matrix instruction takes subnormal operands for zero, and with the scale even the last
@@ -296,6 +337,10 @@ inline int prep_tile_channels(const Geom &g) {
 // (directly when pl.prep_ns == 1, else as image-split partials at pl.off_encp
 // that the convolution launch combines into cd1 and cd2).
 hipError_t launch_prep(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws,
+                       hipStream_t st);
+// The copies of a packed layer (Geom::pk) into the workspace (pl.off_dt, pl.off_wt); with cd1 and cd2 set,
+// extra workgroups of the launch encode them from D.
+hipError_t launch_pack(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws,
                        hipStream_t st);
 // The convolution alone through the path ftcnn_conv_fwd_sums takes (channels-last
 // copies for pl.nhwc layers): O bitwise equal to that of launch_conv_sums.

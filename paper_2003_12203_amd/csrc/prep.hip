@@ -19,6 +19,7 @@
 // starts s elements into its first vector (s depends on the channel and the
 // tile, not on the image, because Ch*H*W is a multiple of the vector) and the
 // tile is seven vectors wide, the eighth covering the shift.
+#include "encode_block.h"
 #include "ftcnn_internal.h"
 
 namespace ftcnn {
@@ -53,8 +54,8 @@ template <typename T, int V> union VecT {
 
 // Eight values split into three bf16 planes whose sum they are: each plane the nearest bf16 of what
 // the ones before left over (8 + 8 + 8 significand bits hold all 24; every difference is exact).
-// Plane pl goes to dst + 32 pl elements.
-__device__ inline void store_split8(const float (&x)[8], uint16_t *dst) {
+// Plane pl goes to dst + STEP pl.
+template <int STEP> __device__ inline void store_split8(const float (&x)[8], uint16_t *dst) {
     union { uint4 q; uint16_t e[8]; } pl[3];
 #pragma unroll
     for (int v = 0; v < 8; ++v) {
@@ -64,12 +65,13 @@ __device__ inline void store_split8(const float (&x)[8], uint16_t *dst) {
         pl[2].e[v] = f32_to_bf16_rne(r1 - bf16_bits_to_f32(pl[1].e[v]));
     }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) *reinterpret_cast<uint4 *>(dst + 32 * k) = pl[k].q;
+    for (int k = 0; k < 3; ++k) *reinterpret_cast<uint4 *>(dst + STEP * k) = pl[k].q;
 }
 
 // vec_d / vec_w: D / W is 16-byte aligned (else element loads; the layout is
 // the same with shift 0, which a tile of seven vectors also covers).
-// SPLIT (fp32): the copies hold blocks of 32 channels as three bf16 planes of 32 (192 bytes).
+// SPLIT (fp32): the copies hold blocks of 32 channels as three bf16 planes of 32 (192 bytes): four
+// threads then store 64 bytes that run on (groups of eight channels, plane after plane: Darknet-19 1x1 13.6 -> 17.8 us).
 template <typename T, bool ENC, int TC, bool SHIFT, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D, const T *__restrict__ W,
                                                         T *__restrict__ Dt, T *__restrict__ Wt, Geom g,
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
                     float x8[8];
 #pragma unroll
                     for (int v = 0; v < 8; ++v) x8[v] = kSplitScale * tile[j + jo][cq * 8 + v][hp + sv[v % VEC]];
-                    store_split8(x8, out + (((long long)n * HW + p0 + hp) * g.C + ct * TC) * 3 + cq * 8);
+                    store_split8<32>(x8, out + (((long long)n * HW + p0 + hp) * g.C + ct * TC) * 3 + cq * 8);
                 }
                 return;
             }
@@ -258,7 +260,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
                     float x8[8];
 #pragma unroll
                     for (int v = 0; v < 8; ++v) x8[v] = split_weight_scale(m) * stage[(cl + v) * RS + rs];
-                    store_split8(x8, out + ((long long)rs * g.C + c / 32 * 32) * 3 + c % 32);
+                    store_split8<32>(x8, out + ((long long)rs * g.C + c / 32 * 32) * 3 + c % 32);
                 }
                 continue;
             }
@@ -345,7 +347,118 @@ hipError_t run_shift(const Plan &pl, const void *D, const void *W, double *cd1, 
     return run_tc<T, TC, true, SPLIT>(pl, D, W, cd1, cd2, ws, st);
 }
 
+// The copies of a packed layer (Geom::pk): a thread a group of eight values.  D: 32 columns by eight
+// groups a workgroup (prun: 256 groups of a row run), so that the lines it writes are whole and its
+// loads of a channel run along the row; W: a workgroup a filter; then enc_blocks workgroups that encode
+// Cd1, Cd2 (they read D beside the others).
+template <typename T>
+__global__ __launch_bounds__(kThreads) void pack_kernel(const T *__restrict__ D, const T *__restrict__ W,
+                                                        uint16_t *__restrict__ Dt, uint16_t *__restrict__ Wt, Geom g,
+                                                        int d_blocks, int pos_blocks, int enc_blocks, int enc_vec,
+                                                        double *cd1, double *cd2, uint4 *__restrict__ zero16) {
+    constexpr int NP = sizeof(T) == 4 ? 3 : 1;
+    auto put = [&](const T (&x)[8], float scale, uint16_t *dst) {
+        if constexpr (NP == 3) {
+            float y[8];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) y[v] = scale * x[v];
+            store_split8<8>(y, dst);   // packed copies: groups of eight channels, plane after plane
+        } else {
+            VecT<uint16_t, 8> y;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) y.e[v] = x[v];
+            *reinterpret_cast<uint4 *>(dst) = y.q;
+        }
+    };
+    int b = blockIdx.x;
+    const int t = threadIdx.x;
+    // the encode first: its workgroups walk all images
+    if (b < enc_blocks) {
+        if (enc_vec) encode_block<T, kThreads, kEncVec>(D, g, b, cd1, cd2);
+        else encode_block<T, kThreads, 1>(D, g, b, cd1, cd2);
+        return;
+    }
+    b -= enc_blocks;
+    T x[8];
+    if (b < d_blocks) {
+        if (g.prun) {
+            const int upr = g.pw * g.pcs / 8;                    // groups of a row
+            const long long i = (long long)b * kThreads + t, rows = (long long)g.N * g.H;
+            if (i >= rows * upr) return;
+            const long long row = i / upr;                       // n H + h
+            const int u = (int)(i - row * upr), n = (int)(row / g.H), h = (int)(row - (long long)n * g.H);
+            const int col0 = u * 8 / g.pcs - g.P;
+            const T *src = D + n * g.CHW + (long long)h * g.W;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                const int c = v & (g.pcs - 1), col = col0 + v / g.pcs;   // pcs is 4 or 8
+                const bool ok = c < g.C && (unsigned)col < (unsigned)g.W;
+                const T val = src[ok ? (long long)c * g.H * g.W + col : 0];
+                x[v] = ok ? val : T(0);
+            }
+            put(x, kSplitScale, Dt + i * 8 * NP);
+            return;
+        }
+        const int HW = g.H * g.W;
+        const int pb = b % pos_blocks, ub = b / pos_blocks;
+        const long long pos = (long long)pb * 32 + (t & 31), all = (long long)g.N * HW;
+        const int u = ub * 8 + (t >> 5);
+        if (pos >= all || u >= g.pupt) return;
+        const int n = (int)(pos / HW), q = (int)(pos - (long long)n * HW);
+        const T *src = D + n * g.CHW + q;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const int c = u * 8 + v;
+            const T val = src[c < g.C ? (long long)c * HW : 0];
+            x[v] = c < g.C ? val : T(0);
+        }
+        put(x, kSplitScale, Dt + (pos * g.pcs + u * 8) * NP);
+        return;
+    }
+    const int m = b - d_blocks;
+    if (m == 0 && t < 16) zero16[t] = make_uint4(0, 0, 0, 0);
+    const int p_s = g.prun ? 1 : g.S, taps = g.R * p_s;
+    const T *wm = W + (long long)m * g.K;
+    for (int i = t; i < g.pkk / 8; i += kThreads) {
+        const int tap = i / g.pupt, o = i - tap * g.pupt, r = tap / p_s;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const int e = o * 8 + v;                             // value of the tap's run
+            const int c = g.prun ? e & (g.pcs - 1) : e, s = g.prun ? e / g.pcs : tap - r * p_s;
+            const bool ok = tap < taps && c < g.C && s < g.S;
+            const T val = wm[ok ? ((long long)c * g.R + r) * g.S + s : 0];
+            x[v] = ok ? val : T(0);
+        }
+        put(x, split_weight_scale(m), Wt + ((long long)m * g.pkk + i * 8) * NP);
+    }
+}
+
+template <typename T>
+hipError_t run_pack(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws, hipStream_t st) {
+    const Geom &g = pl.g;
+    char *w = static_cast<char *>(ws);
+    const long long all = (long long)g.N * g.H * g.W;
+    const long long pos_blocks = (all + 31) / 32;
+    const long long d_blocks = g.prun ? ((long long)g.N * g.H * (g.pw * g.pcs / 8) + kThreads - 1) / kThreads
+                                      : pos_blocks * ((g.pupt + 7) / 8);
+    const int enc_vec = g.CHW % kEncVec == 0 && reinterpret_cast<uintptr_t>(D) % (kEncVec * sizeof(T)) == 0;
+    const long long per = (long long)kThreads * (enc_vec ? kEncVec : 1);
+    const long long enc_blocks = cd1 ? (g.CHW + per - 1) / per : 0;
+    if (enc_blocks + d_blocks + g.M > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+    pack_kernel<T><<<(unsigned)(enc_blocks + d_blocks + g.M), kThreads, 0, st>>>(
+        static_cast<const T *>(D), static_cast<const T *>(W), reinterpret_cast<uint16_t *>(w + pl.off_dt),
+        reinterpret_cast<uint16_t *>(w + pl.off_wt), g, (int)d_blocks, (int)pos_blocks,
+        (int)enc_blocks, enc_vec, cd1, cd2, reinterpret_cast<uint4 *>(w + pl.off_zero));
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_pack(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws,
+                       hipStream_t st) {
+    return pl.g.dtype == FTCNN_F32 ? run_pack<float>(pl, D, W, cd1, cd2, ws, st)
+                                   : run_pack<uint16_t>(pl, D, W, cd1, cd2, ws, st);
+}
 
 hipError_t launch_prep(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws,
                        hipStream_t st) {

@@ -13,7 +13,8 @@ import workloads as wl
 CASES = [
     # path 1: the protected convolution (epilogue with the CoC-D sums) and its plain twin
     ("darknet19", "c1", 1, False, 1),     # fp32 32 x 256, gathered from NCHW (3-channel stem)
-    ("alexnet", "conv1", 1, False, 1),    # fp32 96 x 128, NCHW, 11x11 stride 4
+    ("alexnet", "conv1", 1, False, 1),    # fp32 96 x 256 on packed copies, 11x11 stride 4
+    ("resnet18", "stem", 1, False, 1),    # bf16 64 x 256 on packed copies, 7x7 stride 2
     ("vgg19", "v1", 1, False, 1),         # fp32 64 x 128, NCHW
     ("darknet19", "c4", 1, False, 1),     # fp32 64 x 128 on split copies, 1x1
     ("alexnet", "conv5", 1, False, 1),    # fp32 128 x 256 on split copies, stream-K
@@ -32,6 +33,7 @@ CASES = [
     ("vgg19_bf16", "v10", 1, False, 1),   # bf16 256 x 256, direct-to-LDS
     ("vgg19_bf16", "v10", 1, True, 1),    # ... with a bias
     # path 0: ftcnn_conv_fwd on the layers whose kernel differs from path 1's
+    ("alexnet", "conv1", 1, False, 0),    # fp32 96 x 128, NCHW, 11x11 stride 4
     ("alexnet", "conv5", 1, False, 0),    # fp32 64 x 64, NCHW
     ("alexnet", "conv4", 1, False, 0),    # fp32 128 x 64, NCHW
     ("alexnet", "conv2", 1, False, 0),    # fp32 128 x 128, NCHW

@@ -23,6 +23,13 @@ SHAPES = [
 ]
 # the tiles of few filters, and one of few outputs and many chunks (shared by stream-K workgroups)
 FEW_FILTERS = [(2, 32, 9, 9, 31, 3, 3, 1, 1), (4, 96, 30, 31, 33, 3, 3, 1, 1), (1, 512, 7, 7, 512, 3, 3, 1, 1)]
+# packed copies: stems (a kernel row a tap; four or eight channels a column by the stride), channels that
+# fill no block of eight, kernels up to the largest, units that end inside a chunk
+PACKED = [(2, 3, 40, 41, 40, 7, 7, 2, 3), (2, 3, 43, 40, 96, 11, 11, 4, 0), (3, 3, 40, 41, 130, 3, 3, 1, 1),
+          (4, 5, 30, 31, 33, 5, 3, 3, 2), (4, 8, 30, 31, 65, 3, 3, 2, 1), (8, 1, 40, 40, 70, 5, 5, 1, 6),
+          (16, 3, 97, 97, 96, 3, 3, 1, 0), (2, 17, 29, 28, 100, 3, 3, 1, 1), (3, 100, 25, 26, 70, 3, 3, 2, 1),
+          (6, 105, 22, 23, 200, 1, 1, 1, 0), (2, 9, 20, 20, 64, 15, 15, 1, 7), (8, 40, 17, 19, 300, 2, 3, 1, 1),
+          (1, 65, 24, 24, 65, 16, 3, 1, 3)]
 
 
 def exact_conv(D, W, stride, pad):
@@ -30,7 +37,7 @@ def exact_conv(D, W, stride, pad):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("shape", SHAPES + FEW_FILTERS, ids=lambda s: "-".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES + FEW_FILTERS + PACKED, ids=lambda s: "-".join(map(str, s)))
 def test_edges_bit_for_bit(shape, dtype):
     print(f"[direct-to-lds] {dtype} {shape}", flush=True)
     n, ch, h, w, m, r, s, u, p = shape
@@ -94,6 +101,23 @@ def test_split_error_is_an_fp32_sum_s():
     bias = (O - ref).sum((0, 1)).norm() / ((O - ref).norm() * (n * m) ** 0.5)
     # independent errors give about (n m)^-1/2 = 0.03; errors of one sign 1
     assert bias < 0.25, bias
+
+
+@pytest.mark.parametrize("ch,dtype", [(3, "f32"), (3, "bf16"), (40, "f32")])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_packed_padding_meets_no_infinite_value(value, ch, dtype):
+    # a run of a kernel row reads on past its last column, against zero weights
+    g = torch.Generator().manual_seed(10)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    D, W = torch.rand(4, ch, 30, 30, generator=g) + 0.5, torch.rand(96, ch, 3, 3, generator=g) + 0.1
+    D[1, 2, 10, 10] = value
+    D[0, 0, 0, 29] = value
+    lay = ft.Layer(4, ch, 30, 30, 96, 3, 3, 1, 1, dtype)
+    O = lay.empty_output()
+    lay.conv_ws(D.to(dt).cuda(), W.to(dt).cuda(), O)
+    ref = torch.nn.functional.conv2d(D, W, padding=1)
+    assert torch.equal(torch.isfinite(O.cpu()), torch.isfinite(ref))
+    assert torch.equal(torch.isnan(O.cpu()), torch.isnan(ref))
 
 
 @pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan"), 3.4028234e38])

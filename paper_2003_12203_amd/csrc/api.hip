@@ -95,13 +95,10 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     const long long part_cap = part_budget / (32 * EF);
     pl->ver_splits = row_splits(rows_o, ceil_div(cols_v, ctt), 1024, 32);
     if (pl->ver_splits > part_cap) pl->ver_splits = part_cap > 1 ? (int)part_cap : 1;
-    pl->nhwc = allow_nhwc && nhwc_layer(g);
-    g.split = pl->nhwc && allow_split && split_layer(g);
-    g.pk = g.prun = g.pcs = g.pw = g.pupt = g.pkk = 0;
-    if (allow_nhwc && !pl->nhwc && (allow_split || d->dtype == FTCNN_BF16)) {
-        pack_geom(g);
-        g.split = g.pk && d->dtype == FTCNN_F32;
-    }
+    g.split = g.pk = g.prun = g.pcs = g.pw = g.pupt = g.pkk = 0;
+    if (allow_nhwc && (allow_split || g.dtype == FTCNN_BF16)) pack_geom(g);
+    pl->nhwc = allow_nhwc && nhwc_layer(g) && !g.pk;
+    if (g.dtype == FTCNN_F32) g.split = g.pk || (pl->nhwc && allow_split && split_layer(g));
     pl->copies = pl->nhwc || g.pk;
     // summations fused into the convolution epilogue: one slice per (filter tile, image)
     pl->sum_splits = (int)(ceil_div(g.M, conv_tile_m(g, pl->copies)) * g.N);

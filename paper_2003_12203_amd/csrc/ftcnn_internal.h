@@ -279,7 +279,7 @@ inline bool dma_layer(const Geom &g, int bytes) {
 inline void pack_geom(Geom &g) {
     const int np = g.dtype == FTCNN_BF16 ? 1 : 3, chunk = g.dtype == FTCNN_BF16 ? 64 : 32;
     g.pk = 0;
-    if (g.C % 32 == 0 || g.R > 15 || g.S > 15 || g.P_total >= (1LL << 31)) return;
+    if (g.C % chunk == 0 || (g.C % 32 == 0 && g.G > 1) || g.R > 15 || g.S > 15 || g.P_total >= (1LL << 31)) return;
     g.prun = g.C <= 8;
     if (g.prun) {
         // a run starts at column U y: on a unit when the stride is even (four channels a column) or a

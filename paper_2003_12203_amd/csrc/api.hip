@@ -100,6 +100,7 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     pl->nhwc = allow_nhwc && nhwc_layer(g) && !g.pk;
     if (g.dtype == FTCNN_F32) g.split = g.pk || (pl->nhwc && allow_split && split_layer(g));
     pl->copies = pl->nhwc || g.pk;
+    pl->enc_apart = false;
     // summations fused into the convolution epilogue: one slice per (filter tile, image)
     pl->sum_splits = (int)(ceil_div(g.M, conv_tile_m(g, pl->copies)) * g.N);
     // correction: the standalone launch hands the flagged positions over from at most corr_blocks
@@ -135,19 +136,32 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
         long long most = g.N / min_imgs;
         most = most > 16 ? 16 : (most < 1 ? 1 : most);
         pl->prep_ns = clampi(ceil_div(1024, tiles), 1, most);
+        // Where the copying workgroups are few (the images would be split into ranges of partial sums, or, in
+        // bf16, less than one a compute unit walks all images), the encode has workgroups of its own in
+        // the same launch, reading D a second time, and every round of images of the copy is a
+        // workgroup: bf16 VGG-19 v14 67 -> 61 us a protected layer, ResNet-18 l3 64.5 -> 60.5, its projection
+        // 36 -> 32.6 us; fp32 VGG-19 v14 170 -> 165 us.  With many, one pass over D is the better one (VGG-19 v6 bf16
+        // 158 against 161 us, Darknet-19 1x1 fp32 46 against 49 us).
+        pl->enc_apart = pl->nhwc && (pl->prep_ns > 1 || (g.dtype == FTCNN_BF16 && tiles < 256));
+        if (pl->enc_apart) pl->prep_ns = 1;
         // Co5..Co7 in extra workgroups of the convolution launch, in its threads and LDS, where
         // they hide behind the matrix-core tiles: on layers with many taps to evaluate (E*F*K of
         // at least 1M; one pass per image range when the input checksums come split) and on
         // every layer whose input checksums are whole.  On the others (small and split) the
         // final launch evaluates the taps itself.
-        int nt = 0;
-        size_t lds = 0;
+        int nt = 0, sk_smax = 0;
+        size_t lds = 0, sk_bytes = 0;
+        long long sk_counters = 0;
         conv_tile_shape(g, true, &nt, &lds);
+        if (allow_sk && !g.pk) conv_sk_space(g, true, &sk_smax, &sk_bytes, &sk_counters);
         CocTile &co = pl->co;
         co.tx = g.F >= 24 ? 32 : (g.F >= 12 ? 16 : 8);
         co.ty = nt / co.tx < g.E ? nt / co.tx : g.E;
         while (co.ty > 1 && coc_channel_bytes(g, co.ty, co.tx) > lds) co.ty /= 2;
-        if ((pl->prep_ns == 1 || EF * K >= (1LL << 20)) && coc_channel_bytes(g, co.ty, co.tx) <= lds) {
+        // (whole tiles that take a compute unit each leave them no slot until the last round ends:
+        // AlexNet conv4 156 us with the taps in the final launch, 161 us with them)
+        const bool behind = pl->enc_apart && 2 * lds > (160u << 10) && sk_smax == 0;
+        if (((pl->prep_ns == 1 && !behind) || EF * K >= (1LL << 20)) && coc_channel_bytes(g, co.ty, co.tx) <= lds) {
             pl->co_in_conv = true;
             const size_t cc = lds / coc_channel_bytes(g, co.ty, co.tx);
             co.cc = (int)(cc < 8 ? cc : 8);

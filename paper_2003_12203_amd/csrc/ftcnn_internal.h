@@ -70,6 +70,7 @@ struct Plan {
     int sum_splits;                   // partial-sum slices written by the convolution epilogue
     bool nhwc;                        // the convolution reads channels-last copies of D and W
     bool copies;                      // ... those, or packed ones (Geom::pk)
+    bool enc_apart;                   // the encode in workgroups of the copy's launch that do not copy
     int prep_ns;                      // image ranges of the encode fused into the channels-last copy
     bool co_in_conv;                  // Co5..Co7 partials computed by workgroups of the convolution launch
     CocTile co;                       // their tiling (co_in_conv)

@@ -78,11 +78,20 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
                                                         double *cd1, double *cd2, long long split_stride,
                                                         int tr_blocks, int hw_tiles, int c_tiles, int ns, int vec_d,
                                                         int vec_w, uint4 *__restrict__ zero16, int *__restrict__ skcnt,
-                                                        int skcnt_n) {
+                                                        int skcnt_n, int enc_blocks, int enc_vec) {
     using P = PrepT<T, TC, SHIFT>;
     constexpr int VEC = P::VEC, TH = P::TH, LDT = P::LDT, RPT = P::RPT, BATCH = P::BATCH;
     __shared__ T tile[BATCH][TC][LDT];
     int b = blockIdx.x;
+    if constexpr (!ENC) {
+        // the encode in workgroups of its own (pl.enc_apart), first: they walk all images
+        if (b < enc_blocks) {
+            if (enc_vec) encode_block<T, kThreads, kEncVec>(D, g, b, cd1, cd2);
+            else encode_block<T, kThreads, 1>(D, g, b, cd1, cd2);
+            return;
+        }
+        b -= enc_blocks;
+    }
     const int HW = g.H * g.W;
     if (b < tr_blocks) {
         const int tiles = hw_tiles * c_tiles;
@@ -313,30 +322,34 @@ hipError_t run_tc(const Plan &pl, const void *D, const void *W, double *cd1, dou
     const int skcnt_n = (int)pl.sk_counters;
     const long long HW = (long long)g.H * g.W;
     const long long hw_tiles = (HW + P::TH - 1) / P::TH, c_tiles = g.C / TC;
-    // without the encode every round of images is a workgroup of its own
-    const int ns = cd1 ? pl.prep_ns : (g.N + P::BATCH - 1) / P::BATCH;
+    // without the encode in the copying workgroups every round of images is a workgroup of its own
+    const bool apart = cd1 && pl.enc_apart;
+    const int ns = cd1 && !apart ? pl.prep_ns : (g.N + P::BATCH - 1) / P::BATCH;
+    const int enc_vec = reinterpret_cast<uintptr_t>(D) % (kEncVec * sizeof(T)) == 0;
+    const long long per = (long long)kThreads * (enc_vec ? kEncVec : 1);
+    const long long enc_blocks = apart ? (g.CHW + per - 1) / per : 0;
     // Ch*H*W and K are multiples of 32 on these layers, so aligned bases keep every vector aligned
     const int vec_d = reinterpret_cast<uintptr_t>(D) % 16 == 0;
     const int vec_w = reinterpret_cast<uintptr_t>(W) % 16 == 0;
     const long long tr = (long long)ns * c_tiles * hw_tiles;
-    const long long grid = tr + g.M;
+    const long long grid = enc_blocks + tr + g.M;
     if (grid > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     double *o1 = cd1, *o2 = cd2;
     long long stride = 0;
-    if (cd1 && ns > 1) {
+    if (cd1 && !apart && ns > 1) {
         // image-split partials [ns][2][Ch*H*W], combined by the convolution launch
         o1 = reinterpret_cast<double *>(w + pl.off_encp);
         o2 = o1 + g.CHW;
         stride = 2 * g.CHW;
     }
-    if (cd1)
+    if (cd1 && !apart)
         prep_kernel<T, true, TC, SHIFT, SPLIT><<<(unsigned)grid, kThreads, 0, st>>>(
             static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, o1, o2, stride, (int)tr, (int)hw_tiles,
-            (int)c_tiles, ns, vec_d, vec_w, zero16, skcnt, skcnt_n);
+            (int)c_tiles, ns, vec_d, vec_w, zero16, skcnt, skcnt_n, 0, 0);
     else
         prep_kernel<T, false, TC, SHIFT, SPLIT><<<(unsigned)grid, kThreads, 0, st>>>(
-            static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, nullptr, nullptr, 0, (int)tr,
-            (int)hw_tiles, (int)c_tiles, ns, vec_d, vec_w, zero16, skcnt, skcnt_n);
+            static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, cd1, cd2, 0, (int)tr,
+            (int)hw_tiles, (int)c_tiles, ns, vec_d, vec_w, zero16, skcnt, skcnt_n, (int)enc_blocks, enc_vec);
     return hipGetLastError();
 }
 

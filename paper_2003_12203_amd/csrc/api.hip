@@ -158,9 +158,13 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
         co.tx = g.F >= 24 ? 32 : (g.F >= 12 ? 16 : 8);
         co.ty = nt / co.tx < g.E ? nt / co.tx : g.E;
         while (co.ty > 1 && coc_channel_bytes(g, co.ty, co.tx) > lds) co.ty /= 2;
-        // (whole tiles that take a compute unit each leave them no slot until the last round ends:
-        // AlexNet conv4 156 us with the taps in the final launch, 161 us with them)
-        const bool behind = pl->enc_apart && 2 * lds > (160u << 10) && sk_smax == 0;
+        // (where whole tiles take a compute unit each and their last round leaves next to none free, they
+        // come after it: AlexNet conv4, 255 tiles, 156 us with the taps in the final launch, 161 us with
+        // them)
+        int tile[6];
+        conv_tile_info(g, true, tile);
+        const long long last = ceil_div(g.P_total, tile[1]) * ceil_div(g.M, tile[0]) % 256;
+        const bool behind = pl->enc_apart && 2 * lds > (160u << 10) && sk_smax == 0 && (last == 0 || last > 224);
         if (((pl->prep_ns == 1 && !behind) || EF * K >= (1LL << 20)) && coc_channel_bytes(g, co.ty, co.tx) <= lds) {
             pl->co_in_conv = true;
             const size_t cc = lds / coc_channel_bytes(g, co.ty, co.tx);

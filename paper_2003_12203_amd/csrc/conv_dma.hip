@@ -5,7 +5,8 @@ namespace ftcnn {
 namespace convk {
 
 FTCNN_CONV_TILE(BF16_DMA_128x128)
-FTCNN_CONV_TILE(BF16_DMA_128x64)
+FTCNN_CONV_TILE(BF16_DMA_128x128_3)
+FTCNN_CONV_TILE(BF16_DMA_64x64_3)
 FTCNN_CONV_TILE(BF16_DMA_64x128)
 FTCNN_CONV_TILE(BF16_DMA_256x256)
 

@@ -172,11 +172,14 @@ using BF16_M64 = Tile<BF16T<32>, 1, 4, 2, 2, 2>;
 using BF16_128x128_K64 = Tile<BF16T<64>, 2, 2, 2, 2, 2>;
 using BF16_256x256 = Tile<BF16T<32>, 2, 2, 4, 4, 2>;
 using BF16_DMA_128x128 = Tile<BF16T<64>, 2, 2, 2, 2, 3>;
-// four waves of 64 x 32, a 48 KB ring (three workgroups a compute unit): for layers with fewer
-// 128 x 128 tiles than compute units (VGG-19 v13-v16 and ResNet-18 layer4, 196 tiles: 63.5 -> 55.5
-// us a layer unprotected); where it only adds a partly filled round it is slower (ResNet-18 l3
-// 49 -> 62 us, l2 62 -> 65 us)
-using BF16_DMA_128x64 = Tile<BF16T<64>, 2, 2, 2, 1, 3>;
+// Three stages, for layers whose tiles are about one a compute unit, where a chunk's loads have only the
+// tile's own matrix work to land behind: eight waves of 64 x 32 (against the 128 x 64 tile of four waves
+// and two stages that these layers ran: VGG-19 v14 46.7 -> 41.5 us for the convolution, ResNet-18 l4
+// 47.4 -> 42.0, VGG-19 v10 at batch 8 46.6 -> 40.7; with two tiles a compute unit two stages are the
+// faster, ResNet-18 l3 39.0 against 45.6), and 64 x 64 where even those are few (VGG-19 v14 at batch 8
+// 41.6 -> 26.5 us, at batch 1 41.6 -> 25.0; shared by stream-K workgroups at batch 8 32.4).
+using BF16_DMA_128x128_3 = Tile<BF16T<64>, 2, 4, 2, 1, 4>;
+using BF16_DMA_64x64_3 = Tile<BF16T<64>, 2, 2, 1, 1, 4>;
 // M <= 64: four waves of 64 x 32, a 48 KB ring, three workgroups a compute unit (against 64 x 256
 // tiles of four 64 x 64 waves, two a compute unit: ResNet-18 l1 89 -> 79 us, VGG-19 v2 299 -> 287 us
 // with the channels-last copy; 64 x 64 tiles of two waves, 64 x 128 of two waves and deeper rings

@@ -21,6 +21,10 @@ SHAPES = [
     (1, 64, 24, 24, 70, 17, 3, 1, 3),    # one past it: another loop
     (9, 192, 14, 14, 256, 3, 3, 1, 1),   # several filter and pixel tiles, the last ones ragged
 ]
+# enough outputs for the larger tiles, the last ones ragged both ways
+SHAPES += [(5, 64, 50, 51, 130, 3, 3, 1, 1), (5, 64, 50, 51, 130, 1, 1, 1, 0), (11, 64, 50, 51, 150, 1, 2, 1, 0),
+           (10, 64, 50, 50, 257, 1, 1, 1, 0), (14, 64, 50, 51, 61, 1, 3, 1, 1), (31, 96, 50, 51, 130, 3, 1, 1, 1),
+           (16, 3, 60, 61, 40, 5, 5, 1, 2)]
 # the tiles of few filters, and one of few outputs and many chunks (shared by stream-K workgroups)
 FEW_FILTERS = [(2, 32, 9, 9, 31, 3, 3, 1, 1), (4, 96, 30, 31, 33, 3, 3, 1, 1), (1, 512, 7, 7, 512, 3, 3, 1, 1)]
 # packed copies: stems (a kernel row a tap; four or eight channels a column by the stride), channels that

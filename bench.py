@@ -39,6 +39,12 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 MFMA_PEAK = {"f32": 157.3, "bf16": 2516.6}   # TFLOP/s, MI355X dense matrix peaks
+
+
+def kernel_peak(key, dtype):
+    """The matrix peak of a convolution kernel (kernel_key) in the layer's own flops: an fp32 layer on
+    the direct-to-LDS loops multiplies bf16 planes, six products a term."""
+    return MFMA_PEAK["bf16"] / 6 if dtype == "f32" and key[3] >= 3 else MFMA_PEAK[dtype]
 HBM_PEAK_TBS = 8.0                            # TB/s, MI355X HBM3E
 # Additive corruption of one output element per step.  The outputs of these layers have an rms
 # near 0.8, and the CoC location ratios (Sec. 3.6) resolve to the right block once a fault exceeds
@@ -518,7 +524,7 @@ def main():
         plain = q(lay_ms["unprotected"][li], 50)
         cprot = q(cold["error_free"][li], 50)
         cplain = q(cold["unprotected"][li], 50)
-        _, bound, roof = layer_roof(r.spec, r.flops, r.groups, dtype, peak)
+        _, bound, roof = layer_roof(r.spec, r.flops, r.groups, dtype, kernel_peak(keys[li], dtype))
         per_layer.append({
             "layer": r.name, "gflop": round(r.flops / 1e9, 3), "kernel": "x".join(map(str, keys[li][:2])),
             "conv_ms": round(plain, 4), "conv_tflops": round(r.flops / plain / 1e9, 2),
@@ -539,6 +545,7 @@ def main():
     n_launch = len(dom_launch_ms)
     dom_layers = [runs[li].name for li in sorted(dom_set)]
     traffic = measured_traffic(args.workload, dom_key, dtype)
+    peak = round(kernel_peak(dom_key, dtype), 1)
     roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                 "frac": round(achieved / peak, 4),
                 "traffic": None if traffic is None else round(traffic, 0),
@@ -876,6 +883,7 @@ def summarize_profile(args):
         key_flops[k] = key_flops.get(k, 0.0) + fl
     dom_key = max(key_flops, key=key_flops.get)
     dom_layers = [li for li in range(nl) if keys1[li] == dom_key]
+    peak = round(kernel_peak(dom_key, dtype), 1)
 
     trace, counters = None, {}
     for d in args.summarize:
@@ -949,7 +957,7 @@ def summarize_profile(args):
                 dom_n += len(p1)
                 dom_fl += flops[li] * len(p1)
             emit(f"| {specs[li].name} | {flops[li] / 1e9:.2f} | {keys1[li][0]}x{keys1[li][1]} | {a1:.1f} | "
-                 f"{flops[li] / a1 / 1e6:.1f} | {flops[li] / a1 / 1e6 / peak:.3f} | {a0:.1f} | {flops[li] / a0 / 1e6:.1f} |")
+                 f"{flops[li] / a1 / 1e6:.1f} | {flops[li] / a1 / 1e6 / kernel_peak(keys1[li], dtype):.3f} | {a0:.1f} | {flops[li] / a0 / 1e6:.1f} |")
         if dom_n:
             emit("")
             emit(f"Dominant kernel ({kernel_label(dom_key, dtype)}; layers "

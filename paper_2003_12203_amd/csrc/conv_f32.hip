@@ -9,7 +9,6 @@ FTCNN_CONV_TILE(F32_M64)
 FTCNN_CONV_TILE(F32_64x256)
 FTCNN_CONV_TILE(F32_M96)
 FTCNN_CONV_TILE(F32_128x128)
-FTCNN_CONV_TILE(F32_128x128_K32)
 FTCNN_CONV_TILE(F32_128x64)
 FTCNN_CONV_TILE(F32_64x64)
 

@@ -18,9 +18,9 @@ namespace {
 // bf16 channels-last layers with 64-channel multiples take direct-to-LDS loads (WEAVE 3): 64 x 128 tiles
 // for M <= 64, 256 x 256 tiles (eight waves of 128 x 64) for M >= 256 where there are enough of them,
 // 128 x 128 elsewhere, through three stages where they would not fill the compute units, and 64 x 64
-// where those are few; the other
-// channels-last layers keep two chunks in flight (WEAVE 2), and the rest take 64 x 256, 256 x 256 or
-// 128 x 128 tiles with register-staged loads.
+// where those are few; layers of other channel counts run on packed copies through the same loop, and
+// the rest (short sums, small layers, copies past 32-bit offsets) take 64 x 256, 256 x 256 or 128 x 128
+// tiles with register-staged loads, two chunks in flight (WEAVE 2).
 long long n_tiles(const Geom &g, int tm, int tp) {
     return ((g.P_total + tp - 1) / tp) * (long long)((g.M + tm - 1) / tm);
 }
@@ -90,11 +90,11 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
     }
     const bool dma = nhwc && g.C % 64 == 0 && dma_layer(g, 2);
     if (g.M <= 32) return f(BF16_M32{});
+    // at most two 64 x 64 tiles a compute unit: nothing larger would fill it
+    if (dma && n_tiles(g, 64, 64) <= 512) return f(BF16_DMA_64x64_3{});
     // M <= 64 with 64-channel multiples: direct-to-LDS 64 x 128 (against register-staged loads,
     // VGG-19 v2 384 -> 308 us and ResNet-18 l1 109 -> 90 us for the convolution alone, before the
     // tile went from 64 x 256 to 64 x 128)
-    // at most two 64 x 64 tiles a compute unit: nothing larger would fill it
-    if (dma && n_tiles(g, 64, 64) <= 512) return f(BF16_DMA_64x64_3{});
     if (g.M <= 64) return dma ? f(BF16_DMA_64x128{}) : f(BF16_M64{});
     if (dma) {
         // 256 x 256 where M is large and there are enough such tiles

@@ -145,7 +145,6 @@ using F32_M64 = Tile<F32T<16>, 2, 2, 1, 2, true>;
 using F32_64x256 = Tile<F32T<16>, 1, 4, 2, 2, true>;   // channels-last M <= 64: 64 x 64 a wave
 using F32_M96 = Tile<F32T<16>, 1, 4, 3, 1, true>;   // 96 x 128: AlexNet conv1 gets 1513 tiles, 3 full rounds
 using F32_128x128 = Tile<F32T<16>, 2, 2, 2, 2, true>;
-using F32_128x128_K32 = Tile<F32T<32>, 2, 2, 2, 2, true>;   // 32-deep chunks: half the barriers
 using F32_128x64 = Tile<F32T<32>, 2, 2, 2, 1, true>;
 using F32_64x64 = Tile<F32T<32>, 2, 2, 1, 1, true>;
 // fp32 on split copies.  128 x 256: eight waves of 64 x 64, a two-stage ring of 72 KB stages; 128 x 128:

@@ -497,7 +497,7 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     constexpr int NIA = (NLA + NW - 1) / NW, NIB = NLB / NW, NI = NIA + NIB;
     static_assert(C::TM * ROWL % 64 == 0 && NLB % NW == 0 && STAGES * NI < 64, "DMA tile shape");
     static_assert(STAGES == 2 || NLA % NW == 0, "every wave counts the same loads");
-    static_assert(Q % 2 == 0, "fragment sets alternate");
+    static_assert(Q % 2 == 0 && (NP == 1 || Q == 2), "fragment sets alternate");
     constexpr int STAGE_A = C::TM * C::ROWB, STAGE = (C::TM + C::TP) * C::ROWB;
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the unit of row r that LDS position c holds (the map is its own inverse)
@@ -515,18 +515,21 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
         const int m = m0 + row < g.M ? m0 + row : g.M - 1;   // rows past M are never stored
         a_off[j] = (unsigned)m * kk * EB + 16u * (unsigned)unit(row, s % ROWL);
     }
-    // packed copies: a slot's unit of eight channels of a chunk belongs to a tap of its own, so every
-    // slot walks the taps (r, s) and the units o of a tap by itself, UPC units a chunk: d_r kernel rows,
-    // d_s columns and d_o units (taps past the last have no bit in the mask)
+    // packed copies: a slot's unit of eight channels of a chunk belongs to a tap of its own.  The walk holds
+    // the chunk's first unit (unit o of tap (r, s)), and a slot counts on from it by its own unit of the
+    // chunk (unit0, four bits a slot), with carries by multiplication (exact: pack_geom)
     constexpr int UPC = CH / 8;
     const int p_s = PACK ? (g.prun ? 1 : g.S) : 1;
     const int d_t = PACK ? UPC / g.pupt : 0, d_o = PACK ? UPC - d_t * g.pupt : 0, d_r = PACK ? d_t / p_s : 0,
               d_s = PACK ? d_t - d_r * p_s : 0;
-    int w_o[PACK ? NIB : 1], w_r[PACK ? NIB : 1], w_s[PACK ? NIB : 1];
+    const unsigned inv_o = PACK ? ((1u << kUnitShift) + g.pupt - 1) / g.pupt : 0u,
+                   inv_s = PACK ? ((1u << kUnitShift) + p_s - 1) / p_s : 0u;
+    unsigned unit0 = 0;
+    static_assert(!PACK || (NIB <= 8 && UPC <= 8), "four bits a slot");
     // load j of a chunk: the weight slots, then the input slots
     unsigned b_off[NIB], b_tap[NIB];
     struct Walk {
-        TapWalk t;
+        TapWalk t;    // packed: c0 is the unit o
         unsigned k;   // packed: the chunk's first byte in a filter's row
     };
     auto issue = [&](const Walk &wk, unsigned char *base, int j) {
@@ -536,18 +539,14 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
             buffer_load_lds16(rw, base + (j * NW + w) * 1024, a_off[j], PACK ? wk.k : EB * (unsigned)t.kb(g));
         } else if constexpr (PACK) {
             const int i = j - NIA;
-            const int in = __builtin_amdgcn_sbfe((int)b_tap[i], w_r[i], 1) &
-                           __builtin_amdgcn_sbfe((int)b_tap[i], w_s[i] + 16, 1);
-            const unsigned tap = EB * ((unsigned)w_r[i] * row_v + (unsigned)w_s[i] * px_v + 8u * (unsigned)w_o[i]);
+            const unsigned x = (unsigned)t.c0 + __builtin_amdgcn_ubfe(unit0, 4 * i, 3);
+            const unsigned co = __umul24(x, inv_o) >> kUnitShift, o = x - __umul24(co, (unsigned)g.pupt);
+            const unsigned xs = (unsigned)t.s + co;
+            const unsigned cs = __umul24(xs, inv_s) >> kUnitShift, ts = xs - __umul24(cs, (unsigned)p_s);
+            const unsigned tr = min((unsigned)t.r + cs, 15u);   // taps past the last: bit 15 is never set, R <= 15
+            const int in = __builtin_amdgcn_sbfe((int)b_tap[i], tr, 1) & __builtin_amdgcn_sbfe((int)b_tap[i], ts + 16, 1);
+            const unsigned tap = EB * (tr * row_v + ts * px_v + 8u * o);
             buffer_load_lds16(rd, base + STAGE_A + (i * NW + w) * 1024, (b_off[i] + tap) & (unsigned)in, 0u);
-            w_o[i] += d_o;
-            const int c_o = w_o[i] >= g.pupt;
-            w_o[i] -= c_o ? g.pupt : 0;
-            w_s[i] += d_s + c_o;
-            const int c_s = w_s[i] >= p_s;
-            w_s[i] -= c_s ? p_s : 0;
-            w_r[i] += d_r + c_s;
-            w_r[i] = w_r[i] < 15 ? w_r[i] : 15;   // bit 15 is never set: R <= 15
         } else {
             const int i = j - NIA;
             const unsigned tap = EB * (unsigned)((t.r * g.W + t.s) * g.C + t.c0);
@@ -556,12 +555,23 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
         }
     };
     auto advance = [&](Walk &wk) {
-        if constexpr (PACK) wk.k += CH * EB;
-        else wk.t.next(g, CH);
+        if constexpr (PACK) {
+            TapWalk &t = wk.t;
+            wk.k += CH * EB;
+            t.c0 += d_o;
+            const int co = t.c0 >= g.pupt;
+            t.c0 -= co ? g.pupt : 0;
+            t.s += d_s + co;
+            const int cs = t.s >= p_s;
+            t.s -= cs ? p_s : 0;
+            t.r += d_r + cs;
+        } else {
+            wk.t.next(g, CH);
+        }
     };
     const int nch = kn >= 0 ? kn : (PACK ? g.pkk / CH : g.R * g.S * ((c_hi - c_lo) / CH));
     Walk ti{PACK ? TapWalk{0, 0, 0} : tap_at(g, k0, CH), 0u};   // the chunk whose loads are issued next
-    ti.t.c0 += c_lo;
+    if constexpr (!PACK) ti.t.c0 += c_lo;
     // the first chunk's weights are on their way while the pixels are worked out
 #pragma unroll
     for (int j = 0; j < NIA; ++j) issue(ti, smem, j);
@@ -580,10 +590,7 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
                 iw0 = g.U * (int)y;
                 b_tap[j] = (b_tap[j] & 0xFFFFu) | 0x10000u;
             }
-            const int t = u / NP, tp = t / g.pupt;   // the slot's unit of the first chunk
-            w_o[j] = t - tp * g.pupt;
-            w_r[j] = tp / p_s;
-            w_s[j] = tp - w_r[j] * p_s;
+            unit0 |= (unsigned)(u / NP) << (4 * j);
         }
         // 32-bit wrap-around arithmetic: the sum with a valid tap's offset is the element's offset
         b_off[j] = 256u + EB * (n * img_v + (unsigned)ih0 * row_v + (unsigned)iw0 * px_v) +
@@ -615,23 +622,60 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
         }
     const int arow = (arow0 + l32) * C::ROWB, brow = STAGE_A + (brow0 + l32) * C::ROWB;
     bf16x8 fa[2][NP][FM], fb[2][NP][FP];
-    constexpr int NR = NP * (FM + FP);                // reads per step, planes outer (high first)
+    // reads per step: bf16 the input fragments, then the weights'; split a fragment's planes one after the
+    // other, input and weight fragments in turn, so that the first block's come first
+    constexpr int NR = NP * (FM + FP), NPAIR = NP == 1 ? 0 : (FM < FP ? FM : FP);
     auto read = [&](const unsigned char *stage, int q, int set, int i) {
-        const int pl = i / (FM + FP), k = i % (FM + FP);
-        if (k < FP)
+        const int pl = i % NP, f = i / NP;
+        const bool input = f < 2 * NPAIR ? f % 2 == 0 : (NP == 1 ? f < FP : FP > FM);
+        const int k = f < 2 * NPAIR ? f / 2 : (NP == 1 ? (input ? f : f - FP) : f - NPAIR);
+        if (input)
             fb[set][pl][k] = __builtin_bit_cast(
                 bf16x8, *reinterpret_cast<const u16x8 *>(stage + brow + fpos[q][pl] + k * 32 * C::ROWB));
         else
-            fa[set][pl][k - FP] = __builtin_bit_cast(
-                bf16x8, *reinterpret_cast<const u16x8 *>(stage + arow + fpos[q][pl] + (k - FP) * 32 * C::ROWB));
+            fa[set][pl][k] = __builtin_bit_cast(
+                bf16x8, *reinterpret_cast<const u16x8 *>(stage + arow + fpos[q][pl] + k * 32 * C::ROWB));
     };
     // the products of one step: all of bf16; of a split layer the six whose planes' orders sum to at
     // most two (the other three are below 2^-24 of the product)
-    constexpr int NPROD = NP == 1 ? 1 : 6, NM = NPROD * FM * FP;
-    auto mfma = [&](int set, int k) {
-        constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
-        const int pr = k / (FM * FP), i = k % (FM * FP) / FP, j = k % FP;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][PA[pr]][i], fb[set][PB[pr]][j], acc[i][j], 0, 0, 0);
+    constexpr int NPROD = NP == 1 ? 1 : 6, NB = FM * FP, NM = NPROD * NB;
+    // A split layer's step starts every block's six products from zero, the smallest first, and adds their
+    // sum to the accumulator with ordinary (nearest) additions.  The matrix instruction drops its addends'
+    // bits far below the largest one's, towards one side: adding the products to the accumulators
+    // themselves left errors of up to 9.8e-7 of the norm (K = 4608, one filter; fp32 instructions 8.7e-7), all
+    // leaning to one side.  So: 3.0e-7 there, VGG-19 v6 at batch 32 2.1e-7 (before 7.1e-7, fp32 instructions
+    // 7.9e-7), means within 2e-9 (the weights' signs, split_weight_scale).  It costs 4 to 8 % of a split
+    // layer's time (protected, one box: v6 639 -> 675 us, v2 1002 -> 1083, AlexNet conv4 165 -> 173, conv1
+    // 161 -> 169, Darknet-19 1x1 43.9 -> 45.5).
+    // part holds NBUF blocks' sums in turn; with two, a block's additions go between the next one's products
+    // (one: 2 % slower; three filter blocks a wave leave no registers for two).
+    constexpr int NBUF = NP == 1 ? 1 : (FM > 2 ? 1 : 2);
+    floatx16 part[NBUF];
+    if constexpr (NBUF > 1)
+        for (int e = 0; e < 16; ++e) part[1][e] = 0.0f;   // nothing before the first block
+    // step q's part of block b; its sign follows the weights' (split_weight_scale)
+    auto add = [&](int q, int b, int from, int to) {
+#pragma unroll
+        for (int e = from; e < to; ++e) {
+            const float v = part[(q * NB + b) % NBUF][e];
+            if ((q + e) & 1) acc[b / FP][b % FP][e] -= v;
+            else acc[b / FP][b % FP][e] += v;
+        }
+    };
+    auto mfma = [&](int q, int k) {
+        const int set = q & 1;
+        if constexpr (NP == 1) {
+            const int i = k / FP, j = k % FP;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][0][i], fb[set][0][j], acc[i][j], 0, 0, 0);
+        } else {
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+            const floatx16 zero = {};
+            const int b = k / 6, pr = k % 6, i = b / FP, j = b % FP, buf = (q * NB + b) % NBUF;
+            part[buf] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][PA[pr]][i], fb[set][PB[pr]][j],
+                                                                pr ? part[buf] : zero, 0, 0, 0);
+            if (NBUF == 1 && pr == 5) add(q, b, 0, 16);
+            if (NBUF == 2 && pr) add(b ? q : (q + 1) % 2, b ? b - 1 : NB - 1, (pr - 1) * 16 / 5, pr * 16 / 5);
+        }
     };
 
 #pragma unroll
@@ -653,7 +697,7 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
             const int nside = last ? (NEXT ? NR + (MORE ? NI : 0) : 0) : NR;
 #pragma unroll
             for (int k = 0; k < NM; ++k) {
-                mfma(q & 1, k);
+                mfma(q, k);
 #pragma unroll
                 for (int e = k * nside / NM; e < (k + 1) * nside / NM; ++e) {
                     if (e < NR) read(last ? oth : cur, last ? 0 : q + 1, (q + 1) & 1, e);
@@ -679,6 +723,7 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
         cur = after(cur);
     }
     chunk(cur, cur, no{}, no{});
+    if constexpr (NBUF > 1) add(1, NB - 1, 0, 16);
     wait_lgkm0();
 }
 
@@ -1126,14 +1171,13 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
     }
 
     if constexpr (DMA && Tr::NP == 3) {
-        // the copies' scale out, and odd filters' sums negated back (split_weight_scale): an accumulator's
-        // filter has its index's parity
+        // the copies' scale out
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FP; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] *= e & 1 ? -kSplitUnscale : kSplitUnscale;
+                for (int e = 0; e < 16; ++e) acc[i][j][e] *= kSplitUnscale;
     }
     if constexpr (DMA && (Tr::NP == 3 || WEAVE >= 5))
         redo_nonfinite<C, FM, FP>(g, static_cast<const T *>(ep.src_dw.d), static_cast<const T *>(ep.src_dw.w), m0, p0,

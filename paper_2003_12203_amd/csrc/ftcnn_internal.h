@@ -269,6 +269,8 @@ int conv_stream_k(const Plan &pl);
 // kernels of at most 4096 taps, whose weight rows the copy stages in LDS).
 inline bool nhwc_layer(const Geom &g) { return g.C % 32 == 0 && g.R * g.S <= 4096; }
 constexpr double kPackFlops = 1e7;
+// The loop divides unit numbers below pupt + 8 by pupt as x ceil(2^20 / pupt) >> 20, exact while x pupt < 2^20.
+constexpr int kUnitShift = 20, kMaxUnits = 1000;
 // Layers the direct-to-LDS loops take: they reach the copies (`bytes` a value) through 32-bit buffer
 // offsets, count pixels in 32 bits and keep a pixel's taps inside the map in two 16-bit masks.
 inline bool dma_layer(const Geom &g, int bytes) {
@@ -295,6 +297,7 @@ inline void pack_geom(Geom &g) {
         g.pupt = g.pcs / 8;
         g.pw = g.W;
     }
+    if (g.pupt > kMaxUnits) return;
     const long long units = (long long)g.pupt * g.R * (g.prun ? 1 : g.S);
     const long long kk = (units * 8 + chunk - 1) / chunk * chunk;
     const unsigned long long lim = 1ull << 32;
@@ -313,11 +316,13 @@ inline void pack_geom(Geom &g) {
 // bit of the smallest fp32 value is a normal bf16 number (without, operands below 1e-34 lost bits).
 // What overflows instead (operands from 2e31, sums from 6e23) is redone in fp32 (redo_nonfinite).
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
-// The copy of W also holds odd filters negated, and the epilogue negates their accumulators back: the
-// bf16 matrix instruction rounds its sums towards one side, and with every second filter's sums of
-// the other sign the summations over filters and images (So5..So7) do not add that up (VGG-19 v6: So5
-// off by 5e-6 of its norm without, 1e-7 with, as with fp32 instructions).
-__host__ __device__ inline float split_weight_scale(int m) { return m & 1 ? -kSplitScale : kSplitScale; }
+// The bf16 matrix instruction drops its addends' bits far below the largest one's, towards one side, so
+// the copy of W holds every second group of eight values of a filter's row negated (the two steps of a
+// chunk take the even and the odd groups), the odd filters the other ones, and the convolution subtracts
+// those steps' sums: the errors cancel within an output, and over filters.
+__host__ __device__ inline float split_weight_scale(int m, int group) {
+    return (m + group) & 1 ? -kSplitScale : kSplitScale;
+}
 // fp32 channels-last layers whose copies are split into bf16 planes (Geom::split)
 inline bool split_layer(const Geom &g) { return g.dtype == FTCNN_F32 && nhwc_layer(g) && dma_layer(g, 6); }
 // Positions per tile of the channels-last copy (128 bytes of one channel) and channels per

@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
                     const int rs = o / c8_n, cl = (o - rs * c8_n) * 8, c = c0 + cl;
                     float x8[8];
 #pragma unroll
-                    for (int v = 0; v < 8; ++v) x8[v] = split_weight_scale(m) * stage[(cl + v) * RS + rs];
+                    for (int v = 0; v < 8; ++v) x8[v] = split_weight_scale(m, c / 8) * stage[(cl + v) * RS + rs];
                     store_split8<32>(x8, out + ((long long)rs * g.C + c / 32 * 32) * 3 + c % 32);
                 }
                 continue;
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
         for (int e = threadIdx.x; e < nc * RS; e += kThreads) {
             const int rs = e / nc, c = e - (e / nc) * nc;
             if constexpr (SPLIT) {
-                const float x = split_weight_scale(m) * stage[c * RS + rs];
+                const float x = split_weight_scale(m, (c0 + c) / 8) * stage[c * RS + rs];
                 const uint16_t hi = f32_to_bf16_rne(x);
                 const float r1 = x - bf16_bits_to_f32(hi);
                 const uint16_t mi = f32_to_bf16_rne(r1);
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const T *__restrict__ D,
             const T val = wm[ok ? ((long long)c * g.R + r) * g.S + s : 0];
             x[v] = ok ? val : T(0);
         }
-        put(x, split_weight_scale(m), Wt + ((long long)m * g.pkk + i * 8) * NP);
+        put(x, split_weight_scale(m, i), Wt + ((long long)m * g.pkk + i * 8) * NP);
     }
 }
 

@@ -107,6 +107,47 @@ def test_split_error_is_an_fp32_sum_s():
     assert bias < 0.25, bias
 
 
+# long sums of few and of many filters, the first AlexNet layer, 1x1, packed channels
+ERROR_SHAPES = [(8, 512, 14, 14, 1, 3, 3, 1, 1), (8, 256, 14, 14, 128, 3, 3, 1, 1), (4, 3, 115, 115, 96, 11, 11, 4, 0),
+                (4, 512, 26, 26, 64, 1, 1, 1, 0), (4, 105, 28, 28, 128, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("weights", ["random", "positive", "one parity"])
+@pytest.mark.parametrize("shape", ERROR_SHAPES, ids=lambda s: "-".join(map(str, s)))
+def test_split_is_no_further_from_float64_than_fp32_instructions(shape, weights):
+    n, ch, h, w, m, r, s, u, p = shape
+    g = torch.Generator().manual_seed(11)
+    D, W = torch.rand(n, ch, h, w, generator=g), torch.randn(m, ch, r, s, generator=g) * 0.03
+    if weights == "positive":
+        W = W.abs()
+    if weights == "one parity":
+        W[1::2] = 0
+    lay = ft.Layer(*shape, "f32")
+    assert ft.conv_tile(lay.desc, 1)["loop"] >= 3 and ft.conv_tile(lay.desc, 0)["loop"] < 3
+    Dd, Wd, O, O32 = D.cuda(), W.cuda(), lay.empty_output(), lay.empty_output()
+    lay.encode_weights(Wd)
+    lay.protected(Dd, Wd, O)
+    lay.conv(Dd, Wd, O32)
+    ref = exact_conv(D, W, u, p)
+    err, err32 = O.double().cpu() - ref, O32.double().cpu() - ref
+    assert err.norm() <= err32.norm(), (err.norm(), err32.norm())
+    # the errors of the outputs that are not zero must not lean to one side: their mean is that of
+    # independent ones, below 6 deviations of rms / sqrt(count)
+    live = err[:, ::2] if weights == "one parity" else err
+    lean = (live.mean().abs() / live.square().mean().sqrt() * live.numel() ** 0.5).item()
+    assert lean < 6, lean
+
+
+def test_split_zeros_are_positive():
+    # as the fp32 instructions give them: the sign of a filter's copy must not reach its outputs
+    for ch, k in ((64, 3), (3, 7)):
+        lay = ft.Layer(8, ch, 30, 30, 64, k, k, 1, k // 2, "f32")
+        assert ft.conv_tile(lay.desc, 1)["loop"] >= 3
+        D, W, O = torch.zeros(8, ch, 30, 30).cuda(), torch.ones(64, ch, k, k).cuda(), lay.empty_output()
+        lay.conv_ws(D, W, O)
+        assert not torch.signbit(O).any()
+
+
 @pytest.mark.parametrize("ch,dtype", [(3, "f32"), (3, "bf16"), (40, "f32")])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 def test_packed_padding_meets_no_infinite_value(value, ch, dtype):

@@ -765,11 +765,13 @@ __device__ inline void redo_nonfinite(const Geom &g, const typename C::T *__rest
         float s = 0.0f;
         for (int c = c0; c < c0 + g.Cg && !isnan(s); ++c)   // NaN stays NaN
             for (int r = 0; r < g.R; ++r) {
-                if ((unsigned)(ih0 + r) >= (unsigned)g.H) continue;
-                const auto *d = D + n * g.CHW + ((long long)c * g.H + ih0 + r) * g.W;
+                const auto *d = D + n * g.CHW + ((long long)c * g.H + ih0 + r) * g.W + iw0;
                 const auto *w = W + ((long long)m * g.C + c) * (g.R * g.S) + r * g.S;
-                for (int q = 0; q < g.S; ++q)
-                    if ((unsigned)(iw0 + q) < (unsigned)g.W) s = fmaf(Elem<typename C::T>::load(d, iw0 + q), Elem<typename C::T>::load(w, q), s);
+                for (int q = 0; q < g.S; ++q) {
+                    // a tap in the padding is a product with zero, NaN for an infinite weight
+                    const bool in = (unsigned)(ih0 + r) < (unsigned)g.H && (unsigned)(iw0 + q) < (unsigned)g.W;
+                    s = fmaf(in ? Elem<typename C::T>::load(d, q) : 0.0f, Elem<typename C::T>::load(w, q), s);
+                }
             }
         mine[k * C::NT] = s;
     }

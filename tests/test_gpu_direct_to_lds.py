@@ -188,6 +188,25 @@ def test_nonfinite_operands_give_what_fp32_gives(value, where):
     torch.testing.assert_close(O[ok], ref[ok], rtol=1e-4, atol=1e-4)
 
 
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("ch,k,dtype", [(64, 3, "f32"), (64, 3, "bf16"), (3, 7, "f32"), (3, 7, "bf16"), (40, 3, "bf16")])
+def test_nonfinite_weight_meets_the_padding(ch, k, dtype, value):
+    # zero padding is zeros that the filter multiplies: an infinite tap gives NaN there, as the gather does
+    g = torch.Generator().manual_seed(12)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    D, W = torch.rand(4, ch, 30, 30, generator=g) + 0.5, torch.rand(96, ch, k, k, generator=g) + 0.1
+    W[17, 1, 0, 0] = value
+    W[18, 2, k - 1, 1] = value
+    lay = ft.Layer(4, ch, 30, 30, 96, k, k, 1, k // 2, dtype)
+    assert ft.conv_tile(lay.desc, 1)["loop"] >= 3 and ft.conv_tile(lay.desc, 0)["loop"] < 3
+    Dd, Wd, O, Og = D.to(dt).cuda(), W.to(dt).cuda(), lay.empty_output(), lay.empty_output()
+    lay.conv_ws(Dd, Wd, O)
+    lay.conv(Dd, Wd, Og)
+    ref = torch.nn.functional.conv2d(torch.nn.functional.pad(D, (k // 2,) * 4), W)
+    for got in (O.cpu(), Og.cpu()):
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
+
+
 def test_nonfinite_operands_stay_inside_their_group():
     # two groups of 48 channels: the middle block of 32 channels holds both groups'
     g = torch.Generator().manual_seed(8)

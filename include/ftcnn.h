@@ -284,8 +284,10 @@ int ftcnn_verify_correct(const ftcnn_conv_desc *desc, const void *D, const void 
  * O may differ from ftcnn_conv_fwd's in the last bits (both are eq. (1) with
  * fp32 accumulation; fp32 copies hold every value as three bf16 planes whose sum it
  * is, six of whose nine products the matrix cores add up, the other three being below
- * an fp32 rounding of the product).  O is bitwise that of ftcnn_conv_fwd_sums.  Other layers
- * take ftcnn_conv_fwd's kernel.  Needs the workspace of ftcnn_workspace_bytes. */
+ * an fp32 rounding of the product; outputs that this leaves non-finite, which besides
+ * infinities and NaN are those of operands from 2e31 or sums from 1.2e24, are computed again
+ * from D and W with fp32 products, at about a quarter of the speed).  O is bitwise that of
+ * ftcnn_conv_fwd_sums.  Other layers take ftcnn_conv_fwd's kernel.  Needs the workspace of ftcnn_workspace_bytes. */
 int ftcnn_conv_fwd_ws(const ftcnn_conv_desc *desc, const void *D, const void *W, void *O,
                       void *workspace, hipStream_t stream);
 

@@ -727,12 +727,100 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     wait_lgkm0();
 }
 
-// The outputs of a split or packed tile that came out non-finite, again in fp32 from D and W as given
-// (eq. (1), the filter's own channels).  On packed copies the zeros that fill a filter's row meet input
-// values beyond the tap, which must not count even when they are infinite.  On split copies an infinite, NaN or nearly overflowing operand has no split whose planes
+// One 32 x 32 block of outputs from D and W as given (W dense, [M][K]): filters m_lo .. m_lo + 31 (past
+// the last: any) at the pixel of this lane, over channels [c0, c0 + g.Cg), the accumulators laid out as the
+// main loops'.  Each half of the wave takes eight consecutive k of a 16-deep step, straight from memory,
+// the next step's while the matrix cores work on this one's.
+template <typename T>
+__device__ inline floatx16 block_as_given(const Geom &g, const T *__restrict__ D, const T *__restrict__ W, int m_lo,
+                                          long long pg, int c0, int lane) {
+    const int h = lane >> 5, m = min(m_lo + (lane & 31), g.M - 1), RS = g.R * g.S, HW = g.H * g.W;
+    const bool pvalid = pg < g.P_total;
+    int n = 0, x = 0, y = 0;
+    if (pvalid) {
+        n = (int)(pg / g.EF);
+        const int pix = (int)(pg - (long long)n * g.EF);
+        x = pix / g.F;
+        y = pix - x * g.F;
+    }
+    const int ih0 = g.U * x - g.P, iw0 = g.U * y - g.P;
+    const T *d = D + n * g.CHW + (long long)c0 * HW;
+    const T *w = W + (long long)m * g.K + (long long)c0 * RS;
+    const int kn = g.Cg * RS;
+    // this lane's k of a step: element (r, s) of the channel at offset off, eight a step, then eight past
+    // the other half's
+    const int c8 = 8 / RS, r8 = (8 - c8 * RS) / g.S, s8 = 8 - c8 * RS - r8 * g.S;
+    int r = 0, s = 0, off = 0, k = 0;   // off: the channel's first element
+    auto skip8 = [&] {
+        s += s8;
+        r += r8 + (s >= g.S ? 1 : 0);
+        s -= s >= g.S ? g.S : 0;
+        off += (c8 + (r >= g.R ? 1 : 0)) * HW;
+        r -= r >= g.R ? g.R : 0;
+        k += 8;
+    };
+    if (h) skip8();
+    T a[8], b[8];
+    auto fetch = [&](bool whole) {   // whole: both halves' k lie below kn
+        // a filter's eight values in 16-byte loads, where value by value the loads of 64 rows' lines bound the
+        // step (VGG-19 v6 with one value of 3e38: 1.77 ms, so 1.21 ms)
+        if (whole) __builtin_memcpy(a, w + k, sizeof(a));
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const bool ok = k + v < kn;   // past the last k: zeros on both sides
+            const int ih = ih0 + r, iw = iw0 + s;
+            const bool in = ok & pvalid & ((unsigned)ih < (unsigned)g.H) & ((unsigned)iw < (unsigned)g.W);
+            const T dv = d[in ? off + ih * g.W + iw : 0];
+            b[v] = in ? dv : T(0);        // a tap in the padding is a product with zero
+            if (!whole) {
+                const T wv = w[ok ? k + v : 0];
+                a[v] = ok ? wv : T(0);
+            }
+            const bool ws = ++s == g.S;
+            s = ws ? 0 : s;
+            r += ws ? 1 : 0;
+            const bool wr = r == g.R;
+            r = wr ? 0 : r;
+            off += wr ? HW : 0;
+        }
+        k += 8;
+        skip8();
+    };
+    floatx16 acc = {};
+    fetch(kn >= 16);
+    for (int kb = 0; kb < kn; kb += 16) {
+        T ca[8], cb[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            ca[v] = a[v];
+            cb[v] = b[v];
+        }
+        if (kb + 16 < kn) fetch(kb + 32 <= kn);
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ca[v], cb[v], acc, 0, 0, 0);
+        } else {
+            u16x8 va, vb;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                va[v] = ca[v];
+                vb[v] = cb[v];
+            }
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, vb),
+                                                          acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
+// The outputs of a split or packed tile that came out non-finite, again from D and W as given, on the
+// instructions of the operands' own type (eq. (1), the filter's own channels).  On packed copies the zeros
+// that fill a filter's row meet input values beyond the tap, which must not count even when they are
+// infinite.  On split copies an infinite, NaN or nearly overflowing operand has no split whose planes
 // multiply to what fp32 gives (its lower planes are NaN or of either sign), so such an output says only
-// that it must be redone.  The accumulators pass through LDS so that the loop over them is not unrolled;
-// a finite tile pays one multiply-add an accumulator and a barrier.
+// that it must be redone.  A wave redoes its 32 x 32 blocks that hold such outputs, one after another.  The
+// accumulators pass through LDS so that the loop over them is not unrolled; a finite tile pays one
+// multiply-add an accumulator and a barrier.
 template <typename C, int FM, int FP>
 __device__ inline void redo_nonfinite(const Geom &g, const typename C::T *__restrict__ D,
                                       const typename C::T *__restrict__ W, int m0,
@@ -752,28 +840,23 @@ __device__ inline void redo_nonfinite(const Geom &g, const typename C::T *__rest
     float *mine = reinterpret_cast<float *>(smem) + tid;
 #pragma unroll
     for (int k = 0; k < NA; ++k) mine[k * C::NT] = acc[k / 16 / FP][k / 16 % FP][k % 16];
-    const int l32 = tid & 31, h = (tid >> 5) & 1;
-    for (int k = 0; k < NA; ++k) {
-        if (isfinite(mine[k * C::NT])) continue;
-        const int e = k % 16, j = k / 16 % FP, i = k / 16 / FP;
-        const int m = m0 + arow0 + i * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-        const long long pg = p0 + brow0 + j * 32 + l32;
-        if (m >= g.M || pg >= g.P_total) continue;
-        const int n = (int)(pg / g.EF), pix = (int)(pg - (long long)n * g.EF);
-        const int x = pix / g.F, y = pix - x * g.F, c0 = group_first_channel(g, m);
-        const int ih0 = g.U * x - g.P, iw0 = g.U * y - g.P;
-        float s = 0.0f;
-        for (int c = c0; c < c0 + g.Cg && !isnan(s); ++c)   // NaN stays NaN
-            for (int r = 0; r < g.R; ++r) {
-                const auto *d = D + n * g.CHW + ((long long)c * g.H + ih0 + r) * g.W + iw0;
-                const auto *w = W + ((long long)m * g.C + c) * (g.R * g.S) + r * g.S;
-                for (int q = 0; q < g.S; ++q) {
-                    // a tap in the padding is a product with zero, NaN for an infinite weight
-                    const bool in = (unsigned)(ih0 + r) < (unsigned)g.H && (unsigned)(iw0 + q) < (unsigned)g.W;
-                    s = fmaf(in ? Elem<typename C::T>::load(d, q) : 0.0f, Elem<typename C::T>::load(w, q), s);
-                }
-            }
-        mine[k * C::NT] = s;
+    const int lane = tid & 63, h = lane >> 5;
+    for (int b = 0; b < FM * FP; ++b) {
+        float *blk = mine + b * 16 * C::NT;
+        const int m_lo = __builtin_amdgcn_readfirstlane(m0 + arow0) + b / FP * 32;
+        const long long pg = p0 + brow0 + b % FP * 32 + (lane & 31);
+        bool bad = false;   // an output of this lane that is not finite
+        for (int e = 0; e < 16; ++e)
+            bad |= !isfinite(blk[e * C::NT]) && m_lo + 8 * (e >> 2) + 4 * h + (e & 3) < g.M && pg < g.P_total;
+        if (__ballot(bad) == 0) continue;
+        const int g_hi = min(m_lo + 31, g.M - 1) / g.Mg;
+        for (int gi = m_lo / g.Mg; gi <= g_hi; ++gi) {
+            const floatx16 v = block_as_given(g, D, W, m_lo, pg, gi * g.Cg, lane);
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (!isfinite(blk[e * C::NT]) && (m_lo + 8 * (e >> 2) + 4 * h + (e & 3)) / g.Mg == gi)
+                    blk[e * C::NT] = v[e];
+        }
     }
 #pragma unroll
     for (int k = 0; k < NA; ++k) acc[k / 16 / FP][k / 16 % FP][k % 16] = mine[k * C::NT];

@@ -219,6 +219,65 @@ def test_nonfinite_operands_stay_inside_their_group():
     assert torch.equal(torch.isinf(O.cpu()), torch.isinf(ref)) and not torch.isnan(O).any()
 
 
+# (shape, groups): ragged tiles of several waves, groups that share a block of filters, strides, packed
+# stems and channels, sums that end inside a step of the redo (bf16: on packed copies)
+REDO_SHAPES = [((3, 64, 19, 21, 150, 3, 3, 1, 1), 1), ((2, 96, 20, 20, 48, 3, 3, 1, 1), 4), ((9, 192, 14, 14, 256, 3, 3, 2, 1), 1),
+               ((4, 32, 45, 45, 33, 5, 2, 2, 3), 1), ((4, 3, 40, 41, 130, 7, 7, 2, 3), 1), ((6, 105, 22, 23, 200, 1, 1, 1, 0), 1),
+               ((4, 3, 60, 60, 96, 11, 11, 4, 0), 1), ((4, 42, 24, 24, 60, 3, 3, 1, 1), 2)]
+
+
+REDO_CASES = [(s, g, d) for s, g in REDO_SHAPES for d in ("f32", "bf16") if d == "f32" or s[1] % 64 and not (s[1] % 32 == 0 and g > 1)]
+
+
+@pytest.mark.parametrize("shape,groups,dtype", REDO_CASES, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_redone_outputs(shape, groups, dtype):
+    # beside infinities and NaN, values whose outputs are finite but past the split copies' scale
+    n, ch, h, w, m, r, s, u, p = shape
+    g = torch.Generator().manual_seed(13)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    D, W = torch.rand(n, ch, h, w, generator=g) + 0.5, torch.rand(m, ch // groups, r, s, generator=g) + 0.1
+    D[0] *= 2.0 ** 104
+    D[n - 1, ch - 1, h - 1, w - 1] = float("inf")
+    D[n - 1, 0, 0, 0] = float("nan")
+    W[m - 1, 0, r // 2, s // 2] = -float("inf")
+    D, W = D.to(dt).float(), W.to(dt).float()
+    lay = ft.Layer(*shape, dtype, groups=groups)
+    assert ft.conv_tile(lay.desc, 1)["loop"] >= 3, ft.conv_tile(lay.desc, 1)
+    O = lay.empty_output()
+    lay.conv_ws(D.to(dt).cuda(), W.to(dt).cuda(), O)
+    Dp = torch.nn.functional.pad(D, (p,) * 4).double()
+    ref = torch.nn.functional.conv2d(Dp, W.double(), stride=u, groups=groups)
+    got = O.double().cpu()
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    assert torch.equal(torch.isinf(got), torch.isinf(ref)) and torch.equal(got[torch.isinf(ref)], ref[torch.isinf(ref)])
+    ok = torch.isfinite(ref)
+    # positive terms: an fp32 sum of them is within 2^-24 of itself a term; bf16 outputs round once more
+    K = ch // groups * r * s
+    torch.testing.assert_close(got[ok], ref[ok], rtol=2.0 ** -24 * K + (2.0 ** -8 if dtype == "bf16" else 0.0), atol=0.0)
+
+
+def test_one_large_value_costs_a_few_blocks():
+    # 9 x 256 outputs are redone, all in few tiles: one lane an output took 110 times the clean layer here
+    lay = ft.Layer(4, 256, 28, 28, 256, 3, 3, 1, 1, "f32")
+    g = torch.Generator().manual_seed(14)
+    D, W, O = torch.rand(4, 256, 28, 28, generator=g).cuda(), torch.randn(256, 256, 3, 3, generator=g).cuda(), lay.empty_output()
+
+    def best():
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        ts = []
+        for _ in range(6):
+            e0.record()
+            lay.conv_ws(D, W, O)
+            e1.record()
+            e1.synchronize()
+            ts.append(e0.elapsed_time(e1))
+        return min(ts)
+
+    clean = best()
+    D[1, 2, 10, 10] = 3e38
+    assert best() < 20 * clean
+
+
 @pytest.mark.parametrize("d_exp,w_exp", [(-125, 0), (0, -125), (-140, 0), (-70, -60), (100, 0), (60, 30), (0, 100)])
 def test_split_over_the_range_of_fp32(d_exp, w_exp):
     # operands down to subnormal numbers and up to where their sums still fit

@@ -181,8 +181,8 @@ const char *ftcnn_last_error(void);
  * ...).  out[0] = filters (rows of W) per workgroup tile, out[1] = output pixels per tile,
  * out[2] = k per LDS chunk, out[3] = main loop (0 register-staged gather, 1 gather woven
  * between the matrix-core instructions, 2 two chunks in flight, 3 direct-to-LDS loads,
- * 4 the same with three stages, 5 and 6 like 3 and 4 from packed copies; an fp32 layer
- * on 3 to 6 multiplies bf16 planes),
+ * 4 the same with three stages, 5 and 6 like 3 and 4 from packed copies, 7 like 3 for
+ * kernels above 32 rows or columns; an fp32 layer on 3 to 7 multiplies bf16 planes),
  * out[4] = 1 when the convolution reads channels-last copies, out[5] = 1 when its tiles
  * skip the channels of other groups (grouped layers).  Lets a test check that it covers
  * every kernel a set of layers runs. */

@@ -27,6 +27,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 // A 16-byte unit, or zeros: the selects work on whole 32-bit words.
 __device__ inline uint4 keep_or_zero(bool ok, uint4 v) {
@@ -455,15 +456,20 @@ __device__ inline void buffer_load_lds16(__amdgpu_buffer_rsrc_t r, unsigned char
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t *)lds, 16, voff, soff, 0, 0);
 }
 
-// The taps of one output pixel that fall inside the map: bit r of the low half for kernel rows,
-// bit s of the high half for kernel columns (R, S <= 16).
-__device__ inline unsigned tap_mask(const Geom &g, int ih0, int iw0) {
-    auto run = [](int first, int extent, int taps) -> unsigned {
-        const int lo = first < 0 ? -first : 0;
-        const int hi = extent - first < taps ? extent - first : taps;
-        return lo < hi ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
-    };
-    return run(ih0, g.H, g.R) | (run(iw0, g.W, g.S) << 16);
+// The taps (at most 32) of one output pixel along one side of the map that fall inside it: bit t for the tap at
+// row or column first + t.
+__device__ inline unsigned tap_mask(int first, int extent, int taps) {
+    const int lo = first < 0 ? -first : 0;
+    const int hi = extent - first < taps ? extent - first : taps;
+    return lo < hi ? (~0u >> (32 - hi)) & ~((1u << lo) - 1u) : 0u;
+}
+
+// The same for any kernel the copies take (at most 4096 taps): the run's first tap and its last one's distance
+// from it, or a first one past them all.
+__device__ inline uint2 tap_run(int first, int extent, int taps) {
+    const int lo = first < 0 ? -first : 0;
+    const int hi = extent - first < taps ? extent - first : taps;
+    return lo < hi ? make_uint2(lo, hi - 1 - lo) : make_uint2(taps, 0);
 }
 
 // The K loop of one tile (or of chunks [k0, k0 + kn) of it; kn < 0: all), through a ring of STAGES LDS
@@ -476,15 +482,17 @@ __device__ inline unsigned tap_mask(const Geom &g, int ih0, int iw0) {
 //  - the loads of the chunk after next are issued between the MFMAs of that last step, into the
 //    stage whose last fragments every wave has just read, and have a whole chunk to land;
 //  - a load costs five vector instructions (an input slot) or none (a weight slot): each slot keeps
-//    one byte offset and one mask of its pixel's taps inside the map, the tap's own offset is
-//    scalar, and a tap in the padding reads offset 0, the 256-byte zero page in front of the input
-//    (no branch, no select).
+//    one byte offset and the masks of its pixel's taps inside the map, the tap's own offset is scalar,
+//    and a tap in the padding reads offset 0, the 256-byte zero page in front of the input (no branch,
+//    no select).  Masks hold 32 rows and columns; kernels past that test runs of taps by saturating 16-bit
+//    differences (WIDE), one instruction more: on all layers VGG-19 bf16 v10 128.3 -> 130.2 us, ResNet-18
+//    l3 56.0 -> 57.2.
 // With bounds tests (branches) at every load, all of them before a chunk's first read and the reads
 // after the barrier, the convolution kernel of VGG-19 bf16 v10 (256 x 256 tiles, 196 of them) took
 // 125 us; so it takes 110 us, 1075 TFLOP/s on 77 % of the compute units (torch.mm on 8192^3 random
 // bf16 operands: 1205 TFLOP/s).  Spreading a chunk's loads over two or three steps: 107-111 us there,
 // 1-5 % slower on the 128 x 128 and smaller tiles.
-template <typename C, int NP, int STAGES, bool PACK, int FM, int FP>
+template <typename C, int NP, int STAGES, bool PACK, bool WIDE, int FM, int FP>
 __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, int m0, long long p0,
                                     const unsigned char *zp_dt, unsigned char *smem, floatx16 (&acc)[FM][FP],
                                     int tid, int arow0, int brow0, int k0, int kn, int c_lo, int c_hi) {
@@ -526,8 +534,10 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
                    inv_s = PACK ? ((1u << kUnitShift) + p_s - 1) / p_s : 0u;
     unsigned unit0 = 0;
     static_assert(!PACK || (NIB <= 8 && UPC <= 8), "four bits a slot");
-    // load j of a chunk: the weight slots, then the input slots
-    unsigned b_off[NIB], b_tap[NIB];
+    // load j of a chunk: the weight slots, then the input slots.  b_row, b_col: the masks of a pixel's rows
+    // and columns of taps inside the map (packed copies: both in b_row, 16 bits each; WIDE: the runs' first
+    // row and column, 16 bits each, and their lengths less one)
+    unsigned b_off[NIB], b_row[NIB], b_col[PACK ? 1 : NIB];
     struct Walk {
         TapWalk t;    // packed: c0 is the unit o
         unsigned k;   // packed: the chunk's first byte in a filter's row
@@ -544,14 +554,21 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
             const unsigned xs = (unsigned)t.s + co;
             const unsigned cs = __umul24(xs, inv_s) >> kUnitShift, ts = xs - __umul24(cs, (unsigned)p_s);
             const unsigned tr = min((unsigned)t.r + cs, 15u);   // taps past the last: bit 15 is never set, R <= 15
-            const int in = __builtin_amdgcn_sbfe((int)b_tap[i], tr, 1) & __builtin_amdgcn_sbfe((int)b_tap[i], ts + 16, 1);
+            const int in = __builtin_amdgcn_sbfe((int)b_row[i], tr, 1) & __builtin_amdgcn_sbfe((int)b_row[i], ts + 16, 1);
             const unsigned tap = EB * (tr * row_v + ts * px_v + 8u * o);
             buffer_load_lds16(rd, base + STAGE_A + (i * NW + w) * 1024, (b_off[i] + tap) & (unsigned)in, 0u);
         } else {
             const int i = j - NIA;
             const unsigned tap = EB * (unsigned)((t.r * g.W + t.s) * g.C + t.c0);
-            const int in = __builtin_amdgcn_sbfe((int)b_tap[i], t.r, 1) & __builtin_amdgcn_sbfe((int)b_tap[i], t.s + 16, 1);
-            buffer_load_lds16(rd, base + STAGE_A + (i * NW + w) * 1024, (b_off[i] + tap) & (unsigned)in, 0u);
+            unsigned in;
+            if constexpr (WIDE) {
+                // a tap outside its runs leaves something of a saturating difference
+                const u16x2 at = __builtin_bit_cast(u16x2, (unsigned)t.r | (unsigned)t.s << 16) - __builtin_bit_cast(u16x2, b_row[i]);
+                in = min(__builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(at, __builtin_bit_cast(u16x2, b_col[i]))), 1u) - 1u;
+            } else {
+                in = (unsigned)(__builtin_amdgcn_sbfe((int)b_row[i], t.r, 1) & __builtin_amdgcn_sbfe((int)b_col[i], t.s, 1));
+            }
+            buffer_load_lds16(rd, base + STAGE_A + (i * NW + w) * 1024, (b_off[i] + tap) & in, 0u);
         }
     };
     auto advance = [&](Walk &wk) {
@@ -584,13 +601,17 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
         const unsigned x = pix / (unsigned)g.F, y = pix - x * (unsigned)g.F;
         const int ih0 = g.U * (int)x - g.P;
         int iw0 = g.U * (int)y - g.P;
-        b_tap[j] = tap_mask(g, ih0, iw0);
-        if constexpr (PACK) {
-            if (g.prun) {   // the copy has the padding's columns
-                iw0 = g.U * (int)y;
-                b_tap[j] = (b_tap[j] & 0xFFFFu) | 0x10000u;
-            }
+        if constexpr (WIDE) {
+            const uint2 rows = tap_run(ih0, g.H, g.R), cols = tap_run(iw0, g.W, g.S);
+            b_row[j] = rows.x | cols.x << 16;
+            b_col[j] = rows.y | cols.y << 16;
+        } else if constexpr (PACK) {
+            b_row[j] = tap_mask(ih0, g.H, g.R) | (g.prun ? 1u : tap_mask(iw0, g.W, g.S)) << 16;
+            if (g.prun) iw0 += g.P;   // the copy has the padding's columns
             unit0 |= (unsigned)(u / NP) << (4 * j);
+        } else {
+            b_row[j] = tap_mask(ih0, g.H, g.R);
+            b_col[j] = tap_mask(iw0, g.W, g.S);
         }
         // 32-bit wrap-around arithmetic: the sum with a valid tap's offset is the element's offset
         b_off[j] = 256u + EB * (n * img_v + (unsigned)ih0 * row_v + (unsigned)iw0 * px_v) +
@@ -1064,7 +1085,7 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
         const int mlast = (m0 + C::TM < g.M ? m0 + C::TM : g.M) - 1;
         const int c_lo = group_first_channel(g, m0) / C::TK * C::TK;
         const int c_hi = (group_first_channel(g, mlast) + g.Cg + C::TK - 1) / C::TK * C::TK;
-        dma_mainloop<C, Tr::NP, dma_stages(WEAVE), (WEAVE >= 5), FM, FP>(Wt, g, m0, p0, static_cast<const unsigned char *>(zp), smem, acc, tid, arow0,
+        dma_mainloop<C, Tr::NP, dma_stages(WEAVE), packed_loop(WEAVE), WEAVE == 7, FM, FP>(Wt, g, m0, p0, static_cast<const unsigned char *>(zp), smem, acc, tid, arow0,
                                         brow0, k0, kn, c_lo, c_hi);
     } else if constexpr (NHWC && WEAVE == 2) {
         // channels-last, two chunks in flight: chunk kc + 2 is loaded into one register set
@@ -1264,7 +1285,7 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] *= kSplitUnscale;
     }
-    if constexpr (DMA && (Tr::NP == 3 || WEAVE >= 5))
+    if constexpr (DMA && (Tr::NP == 3 || packed_loop(WEAVE)))
         redo_nonfinite<C, FM, FP>(g, static_cast<const T *>(ep.src_dw.d), static_cast<const T *>(ep.src_dw.w), m0, p0,
                                   smem, acc, tid, arow0, brow0);
 

@@ -39,7 +39,9 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
         if (g.M <= 96 && n_tiles(g, 96, 256) >= 256) return f(S3P_96x256{});
         return n_tiles(g, 128, 128) >= 128 ? f(S3P_128x128{}) : f(S3P_64x64{});
     }
+    const bool wide = g.R > 32 || g.S > 32;
     if (nhwc && g.split) {
+        if (wide) return g.M <= 64 ? f(S3W_64x128{}) : f(S3W_128x128{});
         if (g.M <= 32) return f(S3_32x128{});
         // the tile with the least predicted time, on whole tiles or shared ones
         auto cost = [&](auto t) {
@@ -90,6 +92,7 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
     }
     const bool dma = nhwc && g.C % 64 == 0 && dma_layer(g, 2);
     if (g.M <= 32) return f(BF16_M32{});
+    if (dma && wide) return g.M <= 64 ? f(BF16W_64x128{}) : f(BF16W_128x128{});
     // at most two 64 x 64 tiles a compute unit: nothing larger would fill it
     if (dma && n_tiles(g, 64, 64) <= 512) return f(BF16_DMA_64x64_3{});
     // M <= 64 with 64-channel multiples: direct-to-LDS 64 x 128 (against register-staged loads,
@@ -116,7 +119,7 @@ void conv_tile_info(const Geom &g, bool nhwc, int out[6]) {
         out[2] = Tt::TK;
         out[3] = Tt::WEAVE_KIND;
         out[4] = nhwc ? 1 : 0;
-        out[5] = (nhwc && g.G > 1 && Tt::WEAVE_KIND != 2 && Tt::WEAVE_KIND < 5) ? 1 : 0;
+        out[5] = (nhwc && g.G > 1 && Tt::WEAVE_KIND != 2 && !packed_loop(Tt::WEAVE_KIND)) ? 1 : 0;
         return 0;
     });
 }

@@ -119,10 +119,11 @@ template <> struct Epi<0> {
 };
 
 // Main loops from 3 on load straight to LDS: 3 and 4 through a ring of two and three stages, 5 and 6 the
-// same on packed copies (Geom::pk).
-constexpr int dma_stages(int weave) { return weave >= 5 ? weave - 3 : (weave >= 3 ? weave - 1 : 0); }
+// same on packed copies (Geom::pk), 7 as 3 for kernels above 32 rows or columns.
+constexpr bool packed_loop(int weave) { return weave == 5 || weave == 6; }
+constexpr int dma_stages(int weave) { return weave >= 3 ? (weave == 4 || weave == 6 ? 3 : 2) : 0; }
 // One tile configuration.  WEAVE: the main loop (0 register-staged, 1 gather woven between the
-// MFMAs, 2 two chunks in flight, 3 direct-to-LDS).  run() and stream_k() are instantiated per tile
+// MFMAs, 2 two chunks in flight, 3 to 7 direct-to-LDS).  run() and stream_k() are instantiated per tile
 // in the conv_*.hip files.
 template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE> struct Tile {
     static constexpr int TM = WM * FM * 32;
@@ -156,6 +157,11 @@ using S3_128x128 = Tile<S3T<32>, 2, 4, 2, 1, 4>;
 using S3_64x64 = Tile<S3T<32>, 2, 2, 1, 1, 4>;
 using S3_64x128 = Tile<S3T<32>, 1, 4, 2, 1, 3>;
 using S3_32x128 = Tile<S3T<32>, 1, 4, 1, 1, 3>;
+// kernels above 32 rows or columns
+using S3W_64x128 = Tile<S3T<32>, 1, 4, 2, 1, 7>;
+using S3W_128x128 = Tile<S3T<32>, 2, 4, 2, 1, 7>;
+using BF16W_64x128 = Tile<BF16T<64>, 1, 4, 2, 1, 7>;
+using BF16W_128x128 = Tile<BF16T<64>, 2, 2, 2, 2, 7>;
 // packed copies
 using S3P_32x128 = Tile<S3T<32>, 1, 4, 1, 1, 5>;
 using S3P_64x128 = Tile<S3T<32>, 1, 4, 2, 1, 5>;

@@ -272,11 +272,11 @@ constexpr double kPackFlops = 1e7;
 // The loop divides unit numbers below pupt + 8 by pupt as x ceil(2^20 / pupt) >> 20, exact while x pupt < 2^20.
 constexpr int kUnitShift = 20, kMaxUnits = 1000;
 // Layers the direct-to-LDS loops take: they reach the copies (`bytes` a value) through 32-bit buffer
-// offsets, count pixels in 32 bits and keep a pixel's taps inside the map in two 16-bit masks.
+// offsets and count pixels in 32 bits.
 inline bool dma_layer(const Geom &g, int bytes) {
     const unsigned long long lim = 1ull << 32;
     return (unsigned long long)g.M * g.K * bytes < lim && 256 + (unsigned long long)g.N * g.CHW * bytes < lim &&
-           g.P_total < (1LL << 31) && g.R <= 16 && g.S <= 16;
+           g.P_total < (1LL << 31);
 }
 // The packed form of a layer that has no 32-channel blocks (Geom::pk), or pk = 0 where it has none.
 inline void pack_geom(Geom &g) {

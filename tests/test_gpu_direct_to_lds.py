@@ -17,8 +17,13 @@ SHAPES = [
     (3, 64, 8, 8, 130, 1, 3, 1, 1),      # three chunks
     (2, 64, 11, 13, 96, 3, 3, 2, 1),     # stride, odd map
     (2, 64, 12, 10, 257, 5, 2, 3, 4),    # padding beyond the kernel's reach: whole windows of zeros
-    (1, 64, 20, 20, 70, 16, 16, 1, 3),   # the largest kernel of the tap masks
-    (1, 64, 24, 24, 70, 17, 3, 1, 3),    # one past it: another loop
+    (1, 64, 20, 20, 70, 16, 16, 1, 3),   # large kernels
+    (1, 64, 24, 24, 70, 17, 3, 1, 3),
+    (1, 64, 40, 33, 40, 32, 3, 1, 9),    # the largest kernel of the tap masks
+    (2, 64, 9, 40, 66, 3, 37, 2, 18),    # past them: wider than the map, few and many filters
+    (1, 64, 70, 66, 64, 33, 33, 1, 20),
+    (2, 128, 50, 7, 130, 48, 1, 1, 11),
+    (1, 64, 1, 70000, 64, 1, 9, 3, 4),   # a map wider than 16 bits
     (9, 192, 14, 14, 256, 3, 3, 1, 1),   # several filter and pixel tiles, the last ones ragged
 ]
 # enough outputs for the larger tiles, the last ones ragged both ways
@@ -63,6 +68,13 @@ def test_edges_bit_for_bit(shape, dtype):
     rep = lay.read_report()
     assert not rep.detected
     assert torch.equal(O.double().cpu(), ref)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
+def test_layers_take_the_loop(shape, dtype):
+    packed, wide = shape[1] % (64 if dtype == "bf16" else 32) != 0, max(shape[5:7]) > 32
+    assert ft.conv_tile(ft.make_desc(*shape, dtype), 1)["loop"] in ((5, 6) if packed else (7,) if wide else (3, 4))
 
 
 def run_f32(D, W, u=1, p=1, scale=None):

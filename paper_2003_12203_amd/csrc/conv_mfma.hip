@@ -1,5 +1,7 @@
 // The layer's convolution, eq. (1): the choice of its tile, and its launches (the kernel is in
 // conv_kernel.h, its tiles in conv_tiles.h, their instantiations in the conv_*.hip files).
+#include <algorithm>
+
 #include "conv_tiles.h"
 
 namespace ftcnn {
@@ -25,6 +27,34 @@ long long n_tiles(const Geom &g, int tm, int tp) {
     return ((g.P_total + tp - 1) / tp) * (long long)((g.M + tm - 1) / tm);
 }
 
+// The predicted time of a split layer's convolution on a tile, on whole tiles or shared ones; with_fetch: no less
+// than its operands take to arrive.
+template <typename Tl> double split_cost(const Geom &g, bool with_fetch) {
+    constexpr TileCost c = tile_cost<Tl>();
+    const long long tiles = n_tiles(g, Tl::TM, Tl::TP);
+    // a tile walks the channel blocks that its filters' groups reach into
+    const int spans = g.G > 1 ? (Tl::TM + g.Mg - 1) / g.Mg : 1;
+    const int ch = g.G > 1 && spans * g.Cg + 32 < g.C ? spans * g.Cg + 32 : g.C;
+    const int nch = g.R * g.S * ((ch + 31) / 32);
+    const double whole = whole_cost(c, tiles, c.resident, nch);
+    const int S = g.G > 1 ? 0 : stream_k_size(tiles, c.resident, nch);
+    if (S <= 0) return whole;
+    double shared = shared_cost(c, tiles, c.resident, nch, S);
+    if (with_fetch) {
+        // Workgroups that share tiles are at chunks of their own, and no L2 serves two of them: the operands' bytes
+        // bound the shared tiles, at about 14 TB/s from the Infinity Cache and half of that past its size, and
+        // such a layer takes a larger tile (protected, 16 x 512 x 14^2, 512 filters of 3 x 3: 64 x 64 tiles 141 us,
+        // 128 x 256 117; 3 x 608 x 43^2, 448 of 11 x 11 at stride 4: 438 and 376; 9 x 352 x 74^2, 320 of 11 x 11 at
+        // stride 4: 1031 and 697)
+        const long long waves = (tiles + S - 1) / S, rest = tiles - (waves > 2 ? waves - 2 : 0) * S;
+        const double copies = 6.0 * ((double)g.N * (double)g.CHW + (double)g.M * g.K);
+        const double fetch = (double)rest * nch * (Tl::TM + Tl::TP) * 192 / (copies < 128e6 ? 14e6 : 7e6);
+        const double busy = (double)rest * nch / S * (c.chunk_idle + c.chunk_busy * S / c.resident);
+        shared += std::max(fetch - busy, 0.0);
+    }
+    return std::min(whole, shared);
+}
+
 // Calls f(TileType{}) for the tile this layer uses (nhwc: the launch reads the
 // channels-last copies).
 template <typename Fn>
@@ -43,20 +73,8 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
     if (nhwc && g.split) {
         if (wide) return g.M <= 64 ? f(S3W_64x128{}) : f(S3W_128x128{});
         if (g.M <= 32) return f(S3_32x128{});
-        // the tile with the least predicted time, on whole tiles or shared ones
-        auto cost = [&](auto t) {
-            using Tl = decltype(t);
-            constexpr TileCost c = tile_cost<Tl>();
-            const long long tiles = n_tiles(g, Tl::TM, Tl::TP);
-            // a tile walks the channel blocks that its filters' groups reach into
-            const int spans = g.G > 1 ? (Tl::TM + g.Mg - 1) / g.Mg : 1;
-            const int ch = g.G > 1 && spans * g.Cg + 32 < g.C ? spans * g.Cg + 32 : g.C;
-            const int nch = g.R * g.S * ((ch + 31) / 32);
-            const double whole = whole_cost(c, tiles, c.resident, nch);
-            const int S = g.G > 1 ? 0 : stream_k_size(tiles, c.resident, nch);
-            const double shared = S > 0 ? shared_cost(c, tiles, c.resident, nch, S) : whole;
-            return shared < whole ? shared : whole;
-        };
+        // the tile with the least predicted time
+        auto cost = [&](auto t) { return split_cost<decltype(t)>(g, true); };
         const double c64 = cost(S3_64x64{});
         if (g.M <= 64) return c64 <= cost(S3_64x128{}) ? f(S3_64x64{}) : f(S3_64x128{});
         const double c128 = cost(S3_128x128{}), c256 = cost(S3_128x256{});

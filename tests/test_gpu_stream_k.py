@@ -24,9 +24,9 @@ from test_gpu_workflow import _pattern_faults, compare, run_gpu
 
 pytestmark = pytest.mark.gpu
 
-# (workload config, layer index whose generators seed the data, shape): VGG-19 v13 at batch 16
-# (64 x 64 tiles, 392 of them for 1024 resident workgroups) and Darknet-19 c9 at 25 x 25 (128 x 64
-# tiles, the last pixel tile a quarter full)
+# (workload config, layer index whose generators seed the data, shape): VGG-19 v13 at batch 16 (128 x 256
+# tiles, 52 of them for 256 workgroups, the last pixel tile a quarter full) and Darknet-19 c9 at 25 x 25 (128 x 256
+# tiles, the last pixel tile holding 16 pixels)
 CASES = {
     "v13-b16": (2, 12, wl.LayerSpec("v13-b16", 16, 512, 14, 14, 512, 3, 3, 1, 1, "f32")),
     "c9-25x25": (4, 8, wl.LayerSpec("c9-25x25", 16, 256, 25, 25, 512, 3, 3, 1, 1, "f32")),

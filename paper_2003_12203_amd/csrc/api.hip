@@ -97,8 +97,12 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     if (pl->ver_splits > part_cap) pl->ver_splits = part_cap > 1 ? (int)part_cap : 1;
     g.split = g.pk = g.prun = g.pcs = g.pw = g.pupt = g.pkk = 0;
     if (allow_nhwc && (allow_split || g.dtype == FTCNN_BF16)) pack_geom(g);
+    if (g.pk) {
+        g.split = g.dtype == FTCNN_F32;
+        if (!pack_pays(g)) g.pk = g.split = 0;
+    }
     pl->nhwc = allow_nhwc && nhwc_layer(g) && !g.pk;
-    if (g.dtype == FTCNN_F32) g.split = g.pk || (pl->nhwc && allow_split && split_layer(g));
+    if (!g.pk) g.split = pl->nhwc && allow_split && split_layer(g);
     pl->copies = pl->nhwc || g.pk;
     pl->enc_apart = false;
     // summations fused into the convolution epilogue: one slice per (filter tile, image)

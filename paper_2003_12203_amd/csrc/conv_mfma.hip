@@ -129,6 +129,58 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
 
 }  // namespace
 
+namespace {
+// What a protected layer takes (us) on a route is a sum of these, with coefficients fitted to layers drawn over the
+// workloads' ranges (373 of other counts in each type; 200 bf16 ones of 32,
+// 96, ...), batch 1 to 128: rms 8 to 14 % for the copies, 19 to 32 % for the gathers.
+struct Work {
+    double d, w, o, cd;  // MB of D, W and O as given, and of Cd1 and Cd2
+    double mac;          // 10^9 multiply-adds of the padded tiles
+    double fetch;        // 10^6 input values, once a filter tile
+    double cols;         // 10^6 output pixels, once a filter tile
+    double k;            // terms a tile walks
+};
+Work work_of(const Geom &g, bool nhwc, double k) {
+    const double es = g.dtype == FTCNN_F32 ? 4e-6 : 2e-6;
+    Work w{es * g.N * (double)g.CHW, es * g.M * (double)g.K, es * g.M * (double)g.P_total, 16e-6 * (double)g.CHW, 0, 0, 0, k};
+    with_tile(g, nhwc, [&](auto t) {
+        using Tl = decltype(t);
+        const double tiles = (double)n_tiles(g, Tl::TM, Tl::TP);
+        w.mac = 1e-9 * tiles * Tl::TM * Tl::TP * k;
+        w.fetch = 1e-6 * tiles * Tl::TP * k;
+        w.cols = 1e-6 * (double)g.P_total * ((g.M + Tl::TM - 1) / Tl::TM);
+        return 0;
+    });
+    return w;
+}
+}  // namespace
+
+bool pack_pays(const Geom &g) {
+    Geom as_given = g;
+    as_given.pk = as_given.split = 0;
+    // (bf16 layers of 32-channel blocks go back to channels-last copies instead of D and W as given)
+    const bool nhwc = nhwc_layer(g), one = g.R * g.S == 1;
+    const Work p = work_of(g, true, g.pkk), q = work_of(as_given, nhwc, g.K);
+    const auto most = [](double matrix, double chain) { return std::max(matrix, chain); };   // throughput, or one tile's K
+    if (g.dtype == FTCNN_F32) {
+        const double copy = 6e-6 * g.N * (double)g.H * g.pw * g.pcs;
+        const double packed = 15.1 + 0.13 * copy + 0.78 * p.d + 0.51 * p.cd + 119 * p.cols + most(13.0 * p.mac, 0.0198 * p.k);
+        const double gather = 10.5 + 0.37 * q.d + 0.42 * q.o + 0.61 * q.cd + (one ? 0.16 : 0.97) * q.fetch +
+                              most(15.4 * q.mac, 0.082 * q.k);
+        // (small layers come out up to 8 us either side of the fit)
+        return packed < (gather < 45.0 ? 0.75 : 0.95) * gather;
+    }
+    if (nhwc) {
+        const double packed = 13.2 + 0.70 * p.d + 0.10 * p.o + 0.53 * p.cd + 38.3 * p.cols + most(3.67 * p.mac, 0.0085 * p.k);
+        const double copies = 14.4 + 0.43 * q.d + 0.70 * q.o + 1.05 * q.cd + most(2.86 * q.mac, 0.0162 * q.k);
+        return packed < 1.05 * copies;
+    }
+    const double packed = 15.1 + 0.72 * p.d + 0.19 * p.o + 0.51 * p.cd + 58 * p.cols + most(2.50 * p.mac, 0.0081 * p.k);
+    const double gather = 14.6 + 0.22 * q.d + 0.63 * q.o + 0.63 * q.cd + (one ? 0.0 : 0.56) * q.fetch +
+                          most(8.84 * q.mac, 0.0655 * q.k);
+    return packed < 0.95 * gather;
+}
+
 void conv_tile_info(const Geom &g, bool nhwc, int out[6]) {
     with_tile(g, nhwc, [&](auto t) {
         using Tt = decltype(t);

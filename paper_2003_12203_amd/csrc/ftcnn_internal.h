@@ -311,6 +311,8 @@ inline void pack_geom(Geom &g) {
     if (g.K < 72 || 2.0 * g.M * (double)g.P_total * g.K < kPackFlops) return;
     g.pk = 1;
 }
+// Whether a layer that has a packed form is the faster on it (its tile's work counted; conv_mfma.hip).
+bool pack_pays(const Geom &g);
 // The copies of a split layer hold D and W times 2^24, and its convolution's epilogue takes 2^48 out
 // again: the bf16 matrix instruction takes subnormal operands for zero, and with the scale even the last
 // bit of the smallest fp32 value is a normal bf16 number (without, operands below 1e-34 lost bits).

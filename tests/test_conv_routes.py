@@ -19,3 +19,55 @@ SHARED_TILES = [
 def test_shared_tiles_count_the_bytes_they_fetch(shape, tm, tp):
     t = ft.conv_tile(ft.make_desc(*shape, "f32"), 1)
     assert (t["tm"], t["tp"]) == (tm, tp), t
+
+
+def _loop(shape, dtype, groups=1):
+    return ft.conv_tile(ft.make_desc(*shape, dtype, groups=groups), 1)
+
+
+# padded copies that cost more than they saved: the gather, or in bf16 channels-last copies
+NOT_PACKED = [
+    ((32, 1, 256, 256, 32, 9, 9, 1, 4), "f32"),       # eight values a column: 632, 301
+    ((8, 1, 256, 256, 96, 9, 9, 1, 4), "f32"),        # 316, 154
+    ((8, 1, 128, 128, 128, 15, 15, 1, 7), "f32"),     # 252, 123
+    ((32, 2, 112, 112, 64, 7, 7, 1, 3), "f32"),       # 133, 103
+    ((32, 3, 112, 112, 96, 5, 5, 1, 2), "f32"),       # 142, 108
+    ((32, 100, 28, 28, 100, 1, 1, 1, 0), "f32"),      # 30.5, 25.7
+    ((46, 87, 85, 85, 144, 1, 1, 1, 0), "f32"),       # 354, 258
+    ((32, 1, 256, 256, 32, 9, 9, 1, 4), "bf16"),      # 285, 194
+    ((24, 143, 151, 151, 32, 1, 1, 1, 0), "bf16"),    # 228, 140
+    ((54, 32, 199, 199, 7, 3, 3, 1, 1), "bf16"),      # 339, 270
+    ((36, 288, 80, 80, 144, 1, 1, 1, 0), "bf16"),     # 231, 192
+]
+# ... and those that pay
+STAY_PACKED = [
+    ((64, 3, 227, 227, 96, 11, 11, 4, 0), "f32"),     # AlexNet conv1: gather 192, 157
+    ((32, 105, 56, 56, 128, 3, 3, 1, 1), "f32"),      # 423, 210
+    ((128, 3, 224, 224, 64, 7, 7, 2, 3), "bf16"),     # ResNet-18 stem: 261, 161
+    ((64, 160, 28, 28, 320, 1, 1, 1, 0), "bf16"),     # 72, 49
+    ((32, 96, 28, 28, 128, 3, 3, 1, 1), "bf16"),      # 41, 30
+]
+
+
+@pytest.mark.parametrize("shape,dtype", NOT_PACKED + STAY_PACKED, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_packed_copies_where_they_pay(shape, dtype):
+    assert (_loop(shape, dtype)["loop"] in (5, 6)) == ((shape, dtype) in STAY_PACKED)
+
+
+def test_loop_test_shapes_run_their_loops():
+    """The shapes of test_gpu_direct_to_lds.py run what their lists say."""
+    import test_gpu_direct_to_lds as t
+    for s in t.SHAPES:
+        for dtype in ("f32", "bf16"):
+            assert _loop(s, dtype)["loop"] in ((7,) if max(s[5:7]) > 32 else (3, 4)), (s, dtype)
+    for s, tiles in t.PACKED.items():
+        for dtype, want in zip(("f32", "bf16"), tiles):
+            got = _loop(s, dtype)
+            assert (got["loop"] in (5, 6)) == (want is not None), (s, dtype, got)
+            assert want is None or want == f"{got['tm']}x{got['tp']}", (s, dtype, got)
+    for s in t.GATHERED:
+        assert _loop(s, "f32")["loop"] < 3 and _loop(s, "bf16")["loop"] < 3 and not _loop(s, "f32")["nhwc"], s
+    # every packed tile has a shape
+    have = {(d, w) for tiles in t.PACKED.values() for d, w in zip(("f32", "bf16"), tiles) if w}
+    assert have == {("f32", w) for w in ("32x128", "64x128", "96x256", "128x128", "64x64")} | \
+                   {("bf16", w) for w in ("64x128", "64x256", "128x128", "64x64")}

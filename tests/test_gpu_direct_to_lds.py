@@ -27,18 +27,41 @@ SHAPES = [
     (9, 192, 14, 14, 256, 3, 3, 1, 1),   # several filter and pixel tiles, the last ones ragged
 ]
 # enough outputs for the larger tiles, the last ones ragged both ways
-SHAPES += [(5, 64, 50, 51, 130, 3, 3, 1, 1), (5, 64, 50, 51, 130, 1, 1, 1, 0), (11, 64, 50, 51, 150, 1, 2, 1, 0),
-           (10, 64, 50, 50, 257, 1, 1, 1, 0), (14, 64, 50, 51, 61, 1, 3, 1, 1), (31, 96, 50, 51, 130, 3, 1, 1, 1),
-           (16, 3, 60, 61, 40, 5, 5, 1, 2)]
+SHAPES += [(5, 64, 50, 51, 130, 3, 3, 1, 1), (5, 64, 50, 51, 130, 2, 2, 1, 0), (11, 64, 50, 51, 150, 1, 2, 1, 0),
+           (10, 64, 50, 50, 257, 1, 3, 1, 0), (14, 64, 50, 51, 61, 1, 3, 1, 1)]
 # the tiles of few filters, and one of few outputs and many chunks (shared by stream-K workgroups)
 FEW_FILTERS = [(2, 32, 9, 9, 31, 3, 3, 1, 1), (4, 96, 30, 31, 33, 3, 3, 1, 1), (1, 512, 7, 7, 512, 3, 3, 1, 1)]
-# packed copies: stems (a kernel row a tap; four or eight channels a column by the stride), channels that
-# fill no block of eight, kernels up to the largest, units that end inside a chunk
-PACKED = [(2, 3, 40, 41, 40, 7, 7, 2, 3), (2, 3, 43, 40, 96, 11, 11, 4, 0), (3, 3, 40, 41, 130, 3, 3, 1, 1),
-          (4, 5, 30, 31, 33, 5, 3, 3, 2), (4, 8, 30, 31, 65, 3, 3, 2, 1), (8, 1, 40, 40, 70, 5, 5, 1, 6),
-          (16, 3, 97, 97, 96, 3, 3, 1, 0), (2, 17, 29, 28, 100, 3, 3, 1, 1), (3, 100, 25, 26, 70, 3, 3, 2, 1),
-          (6, 105, 22, 23, 200, 1, 1, 1, 0), (2, 9, 20, 20, 64, 15, 15, 1, 7), (8, 40, 17, 19, 300, 2, 3, 1, 1),
-          (1, 65, 24, 24, 65, 16, 3, 1, 3)]
+# 1x1 layers that one type has on the loop (fp32: few products an input value, fp32 copies), and a packed one in bf16
+OTHERS = [(5, 64, 50, 51, 130, 1, 1, 1, 0), (10, 64, 50, 50, 257, 1, 1, 1, 0), (31, 96, 50, 51, 130, 3, 1, 1, 1)]
+# packed copies, with the tiles of fp32 and bf16: stems (a kernel row a tap; four or eight channels a column by the
+# stride; padding past the kernel), channels that fill no block of eight, kernels up to the largest, units that end
+# inside a chunk, ragged tiles of every kind (None: fp32 gathers)
+PACKED = {
+    (16, 3, 43, 40, 64, 9, 9, 2, 4): ("64x128", "64x128"),
+    (6, 3, 61, 60, 96, 11, 11, 4, 0): ("64x64", "64x64"),
+    (2, 3, 43, 40, 96, 11, 11, 4, 0): ("64x64", "64x64"),
+    (24, 20, 53, 53, 90, 3, 3, 1, 1): ("96x256", "128x128"),
+    (11, 3, 224, 222, 61, 7, 7, 2, 3): (None, "64x256"),
+    (16, 6, 41, 40, 65, 7, 7, 2, 3): ("64x64", "64x64"),
+    (8, 8, 40, 40, 64, 7, 7, 2, 3): ("64x128", "64x128"),
+    (8, 2, 60, 60, 96, 15, 15, 2, 7): ("64x64", "64x64"),
+    (8, 1, 80, 80, 70, 9, 9, 4, 6): (None, "64x64"),
+    (16, 6, 31, 32, 33, 7, 5, 3, 2): (None, "64x128"),
+    (16, 3, 60, 61, 40, 5, 5, 1, 2): (None, "64x128"),
+    (2, 17, 29, 28, 100, 3, 3, 1, 1): (None, "64x64"),
+    (3, 100, 25, 26, 70, 3, 3, 2, 1): ("64x64", "64x64"),
+    (6, 105, 22, 23, 200, 1, 1, 1, 0): (None, "64x64"),
+    (2, 9, 20, 20, 64, 15, 15, 1, 7): ("64x128", "64x128"),
+    (8, 40, 17, 19, 300, 2, 3, 1, 1): ("64x64", "64x64"),
+    (16, 40, 17, 19, 300, 2, 3, 1, 1): ("128x128", "64x64"),
+    (4, 65, 24, 24, 31, 3, 3, 1, 1): ("32x128", "64x128"),
+    (16, 12, 40, 41, 60, 5, 4, 1, 2): ("64x128", "64x128"),
+    (24, 105, 30, 30, 130, 3, 3, 1, 1): ("128x128", "128x128"),
+}
+# short sums, small layers and kernels past 15 rows stay on the gather
+GATHERED = [(2, 3, 40, 41, 40, 7, 7, 2, 3), (3, 3, 40, 41, 130, 3, 3, 1, 1), (4, 5, 30, 31, 33, 5, 3, 3, 2),
+            (4, 8, 30, 31, 65, 3, 3, 2, 1), (8, 1, 40, 40, 70, 5, 5, 1, 6), (16, 3, 97, 97, 96, 3, 3, 1, 0),
+            (1, 65, 24, 24, 65, 16, 3, 1, 3)]
 
 
 def exact_conv(D, W, stride, pad):
@@ -46,7 +69,7 @@ def exact_conv(D, W, stride, pad):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("shape", SHAPES + FEW_FILTERS + PACKED, ids=lambda s: "-".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES + FEW_FILTERS + OTHERS + list(PACKED) + GATHERED, ids=lambda s: "-".join(map(str, s)))
 def test_edges_bit_for_bit(shape, dtype):
     print(f"[direct-to-lds] {dtype} {shape}", flush=True)
     n, ch, h, w, m, r, s, u, p = shape
@@ -68,13 +91,6 @@ def test_edges_bit_for_bit(shape, dtype):
     rep = lay.read_report()
     assert not rep.detected
     assert torch.equal(O.double().cpu(), ref)
-
-
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
-def test_layers_take_the_loop(shape, dtype):
-    packed, wide = shape[1] % (64 if dtype == "bf16" else 32) != 0, max(shape[5:7]) > 32
-    assert ft.conv_tile(ft.make_desc(*shape, dtype), 1)["loop"] in ((5, 6) if packed else (7,) if wide else (3, 4))
 
 
 def run_f32(D, W, u=1, p=1, scale=None):
@@ -152,7 +168,7 @@ def test_split_is_no_further_from_float64_than_fp32_instructions(shape, weights)
 
 def test_split_zeros_are_positive():
     # as the fp32 instructions give them: the sign of a filter's copy must not reach its outputs
-    for ch, k in ((64, 3), (3, 7)):
+    for ch, k in ((64, 3), (40, 3)):
         lay = ft.Layer(8, ch, 30, 30, 64, k, k, 1, k // 2, "f32")
         assert ft.conv_tile(lay.desc, 1)["loop"] >= 3
         D, W, O = torch.zeros(8, ch, 30, 30).cuda(), torch.ones(64, ch, k, k).cuda(), lay.empty_output()
@@ -160,19 +176,24 @@ def test_split_zeros_are_positive():
         assert not torch.signbit(O).any()
 
 
-@pytest.mark.parametrize("ch,dtype", [(3, "f32"), (3, "bf16"), (40, "f32")])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(6, 3, 61, 60, 96, 11, 11, 4, 0), (16, 3, 43, 40, 64, 9, 9, 2, 4), (8, 40, 17, 19, 300, 2, 3, 1, 1)],
+                         ids=lambda s: "-".join(map(str, s)))
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
-def test_packed_padding_meets_no_infinite_value(value, ch, dtype):
-    # a run of a kernel row reads on past its last column, against zero weights
+def test_packed_padding_meets_no_infinite_value(value, shape, dtype):
+    # a run of a kernel row reads on past its last column (stems: to the twelfth of eleven, the tenth of nine),
+    # against zero weights
+    n, ch, h, w, m, r, s, u, p = shape
     g = torch.Generator().manual_seed(10)
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
-    D, W = torch.rand(4, ch, 30, 30, generator=g) + 0.5, torch.rand(96, ch, 3, 3, generator=g) + 0.1
-    D[1, 2, 10, 10] = value
-    D[0, 0, 0, 29] = value
-    lay = ft.Layer(4, ch, 30, 30, 96, 3, 3, 1, 1, dtype)
+    D, W = torch.rand(n, ch, h, w, generator=g) + 0.5, torch.rand(m, ch, r, s, generator=g) + 0.1
+    D[1, 2, 10, 11 - p] = value   # just past the first output's run
+    D[0, 0, 0, w - 1] = value
+    lay = ft.Layer(*shape, dtype)
+    assert ft.conv_tile(lay.desc, 1)["loop"] in (5, 6)
     O = lay.empty_output()
     lay.conv_ws(D.to(dt).cuda(), W.to(dt).cuda(), O)
-    ref = torch.nn.functional.conv2d(D, W, padding=1)
+    ref = torch.nn.functional.conv2d(torch.nn.functional.pad(D, (p,) * 4), W, stride=u)
     assert torch.equal(torch.isfinite(O.cpu()), torch.isfinite(ref))
     assert torch.equal(torch.isnan(O.cpu()), torch.isnan(ref))
 
@@ -201,7 +222,7 @@ def test_nonfinite_operands_give_what_fp32_gives(value, where):
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
-@pytest.mark.parametrize("ch,k,dtype", [(64, 3, "f32"), (64, 3, "bf16"), (3, 7, "f32"), (3, 7, "bf16"), (40, 3, "bf16")])
+@pytest.mark.parametrize("ch,k,dtype", [(64, 3, "f32"), (64, 3, "bf16"), (40, 3, "f32"), (3, 7, "bf16"), (40, 3, "bf16")])
 def test_nonfinite_weight_meets_the_padding(ch, k, dtype, value):
     # zero padding is zeros that the filter multiplies: an infinite tap gives NaN there, as the gather does
     g = torch.Generator().manual_seed(12)

@@ -102,7 +102,7 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
         if (!pack_pays(g)) g.pk = g.split = 0;
     }
     pl->nhwc = allow_nhwc && nhwc_layer(g) && !g.pk;
-    if (!g.pk) g.split = pl->nhwc && allow_split && split_layer(g);
+    if (!g.pk) g.split = pl->nhwc && allow_split && split_layer(g) && split_pays(g);
     pl->copies = pl->nhwc || g.pk;
     pl->enc_apart = false;
     // summations fused into the convolution epilogue: one slice per (filter tile, image)

@@ -131,7 +131,7 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
 
 namespace {
 // What a protected layer takes (us) on a route is a sum of these, with coefficients fitted to layers drawn over the
-// workloads' ranges (373 of other counts in each type; 200 bf16 ones of 32,
+// workloads' ranges (1040 fp32 ones of 32, 64, ... channels; 373 of other counts in each type; 200 bf16 ones of 32,
 // 96, ...), batch 1 to 128: rms 8 to 14 % for the copies, 19 to 32 % for the gathers.
 struct Work {
     double d, w, o, cd;  // MB of D, W and O as given, and of Cd1 and Cd2
@@ -154,6 +154,33 @@ Work work_of(const Geom &g, bool nhwc, double k) {
     return w;
 }
 }  // namespace
+
+bool split_pays(const Geom &g) {
+    if (g.R > 32 || g.S > 32) return true;
+    Geom sp = g, f32 = g;
+    sp.split = 1;
+    f32.split = 0;
+    double conv = 0;
+    with_tile(sp, true, [&](auto t) {
+        using Tl = decltype(t);
+        if constexpr (Tl::SK_FORM) conv = split_cost<Tl>(sp, false);
+        return 0;
+    });
+    // the channels a tile of grouped layers walks
+    int tm = 0;
+    with_tile(f32, true, [&](auto t) {
+        tm = decltype(t)::TM;
+        return 0;
+    });
+    const int spans = std::min(g.G, (tm + 2 * g.Mg - 2) / g.Mg);
+    const double k = (double)g.R * g.S * (g.G > 1 ? std::min(g.C, spans * g.Cg + 32) : g.C);
+    const Work w = work_of(f32, true, k);
+    // rounds of eight images past the last one read it again
+    const double again = w.d * ((g.N + 7) / 8 * 8 - g.N) / g.N;
+    const double split = 13.5 + 0.76 * w.d + 0.32 * again + 0.94 * w.w + 0.43 * w.o + 0.83 * conv;
+    const double whole = 16.3 + 0.48 * w.d + 0.28 * again + 0.19 * w.o + std::max(20.0 * w.mac, 0.047 * w.k);
+    return split < 1.05 * whole;   // the least mean time over the drawn layers
+}
 
 bool pack_pays(const Geom &g) {
     Geom as_given = g;

@@ -311,6 +311,10 @@ inline void pack_geom(Geom &g) {
     if (g.K < 72 || 2.0 * g.M * (double)g.P_total * g.K < kPackFlops) return;
     g.pk = 1;
 }
+// Whether an fp32 channels-last layer is the faster on split copies: they are half as large again as fp32 ones, which
+// a layer of few products an input value does not win back (17 x 320 x 86^2, 6 filters 1x1: 187 us on split
+// copies, 149 on fp32 ones; conv_mfma.hip).
+bool split_pays(const Geom &g);
 // Whether a layer that has a packed form is the faster on it (its tile's work counted; conv_mfma.hip).
 bool pack_pays(const Geom &g);
 // The copies of a split layer hold D and W times 2^24, and its convolution's epilogue takes 2^48 out

@@ -16,7 +16,8 @@ CASES = [
     ("alexnet", "conv1", 1, False, 1),    # fp32 96 x 256 on packed copies, 11x11 stride 4
     ("resnet18", "stem", 1, False, 1),    # bf16 64 x 256 on packed copies, 7x7 stride 2
     ("vgg19", "v1", 1, False, 1),         # fp32 64 x 128, NCHW
-    ("darknet19", "c4", 1, False, 1),     # fp32 64 x 128 on split copies, 1x1
+    ("darknet19", "c2", 1, False, 1),     # fp32 64 x 128 on split copies
+    ("darknet19", "c4", 1, False, 1),     # fp32 64 x 256 on fp32 copies, 1x1
     ("alexnet", "conv5", 1, False, 1),    # fp32 128 x 256 on split copies, stream-K
     ("darknet19", "c10", 1, False, 1),    # fp32 128 x 128 on split copies, 1x1
     ("darknet19", "c15", 1, False, 1),    # fp32 64 x 64 on split copies, 1x1

@@ -71,3 +71,20 @@ def test_loop_test_shapes_run_their_loops():
     have = {(d, w) for tiles in t.PACKED.values() for d, w in zip(("f32", "bf16"), tiles) if w}
     assert have == {("f32", w) for w in ("32x128", "64x128", "96x256", "128x128", "64x64")} | \
                    {("bf16", w) for w in ("64x128", "64x256", "128x128", "64x64")}
+
+
+# fp32 layers of few products an input value: the half larger split copies cost more than the faster products save
+NOT_SPLIT = [((17, 320, 86, 86, 6, 1, 1, 1, 0), 1),       # 187, 149
+             ((16, 128, 104, 104, 64, 1, 1, 1, 0), 1),    # Darknet-19 c4: 115, 90
+             ((11, 992, 80, 50, 16, 1, 1, 1, 0), 2),      # 199, 166
+             ((60, 192, 73, 73, 3, 1, 1, 1, 0), 1)]       # 283, 189
+SPLIT = [((16, 256, 52, 52, 128, 1, 1, 1, 0), 1),         # Darknet-19 c7: fp32 copies 62, split 56
+         ((16, 512, 26, 26, 256, 1, 1, 1, 0), 1),         # 56, 44
+         ((32, 256, 56, 56, 256, 3, 3, 1, 1), 1),         # VGG-19 v6: 1010, 640
+         ((64, 96, 27, 27, 256, 5, 5, 1, 2), 2)]          # AlexNet conv2: 271, 200
+
+
+@pytest.mark.parametrize("shape,groups", NOT_SPLIT + SPLIT, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else f"g{v}")
+def test_split_copies_where_they_pay(shape, groups):
+    t = _loop(shape, "f32", groups)
+    assert t["nhwc"] and (t["loop"] in (3, 4)) == ((shape, groups) in SPLIT), t

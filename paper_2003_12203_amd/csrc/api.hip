@@ -4,6 +4,8 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "ftcnn_internal.h"
 
 namespace ftcnn {
@@ -175,6 +177,14 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
             co.cc = (int)(cc < 8 ? cc : 8);
             co.tiles_x = (int)ceil_div(g.F, co.tx);
             co.tiles = (int)(ceil_div(g.E, co.ty) * co.tiles_x);
+            // where a tile takes a compute unit, the few units that the tiles leave free take these workgroups
+            // one after another: fewer channels each until there are about 192 of them, of at least 24 taps a
+            // position (bf16 9 x 64 x 37^2, 288 filters of 5 x 5: 52 -> 39 us; 4 x 64 x 43^2, 432 of 7 x 7: 66
+            // -> 54)
+            if (2 * lds > (160u << 10)) {
+                const long long few = std::max((long long)g.C * co.tiles / 192, 24LL / (g.R * g.S));
+                co.cc = clampi(few, 1, co.cc);
+            }
             co.groups = clampi(ceil_div(768, co.tiles), 1, ceil_div(g.C, co.cc));
         }
         co.ns = pl->prep_ns;

@@ -237,6 +237,13 @@ SPLIT_COC_SHAPES = [
     (32, 32, 64, 32, 3, 1, 1, "f32"),
     (64, 64, 48, 64, 3, 1, 1, "bf16"),
 ]
+# tiles that take a compute unit each, where Co5..Co7 come from workgroups of one to four channels
+FEW_CHANNELS = [
+    (9, 64, 37, 288, 5, 1, 0, "bf16"),
+    (4, 64, 43, 432, 7, 1, 3, "bf16"),
+    (20, 32, 25, 200, 5, 1, 2, "f32"),
+    (9, 32, 25, 352, 9, 1, 4, "f32"),
+]
 
 
 def _split_spec(shape):
@@ -244,7 +251,7 @@ def _split_spec(shape):
     return wl.LayerSpec("split", n, ch, h, h, m, r, r, u, p, dtype)
 
 
-@pytest.mark.parametrize("shape", SPLIT_SHAPES + SPLIT_COC_SHAPES,
+@pytest.mark.parametrize("shape", SPLIT_SHAPES + SPLIT_COC_SHAPES + FEW_CHANNELS,
                          ids=lambda s: "n{}-c{}-h{}-m{}-r{}-u{}-{}".format(*s[:6], s[7]))
 def test_image_split_encode_integer_exact(shape):
     """Integer data: the combined image-range partials are exactly Cd1, Cd2, and the Co5..Co7

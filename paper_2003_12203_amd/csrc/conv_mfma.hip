@@ -27,17 +27,25 @@ long long n_tiles(const Geom &g, int tm, int tp) {
     return ((g.P_total + tp - 1) / tp) * (long long)((g.M + tm - 1) / tm);
 }
 
+// The channels that a tile of tm filters walks: the 32-channel blocks that its filters' groups reach into, on
+// average (tiles that straddle two groups walk both).
+double mean_channels(const Geom &g, int tm) {
+    if (g.G == 1) return g.C;
+    long long blocks = 0, tiles = 0;
+    for (int m0 = 0; m0 < g.M; m0 += tm, ++tiles) {
+        const int last = (std::min(m0 + tm, g.M) - 1) / g.Mg;
+        blocks += ((last + 1) * g.Cg + 31) / 32 - group_first_channel(g, m0) / 32;
+    }
+    return 32.0 * (double)blocks / (double)tiles;
+}
+
 // The predicted time of a split layer's convolution on a tile, on whole tiles or shared ones; with_fetch: no less
 // than its operands take to arrive.
 template <typename Tl> double split_cost(const Geom &g, bool with_fetch) {
     constexpr TileCost c = tile_cost<Tl>();
     const long long tiles = n_tiles(g, Tl::TM, Tl::TP);
-    // a tile walks the channel blocks that its filters' groups reach into
-    const int spans = g.G > 1 ? (Tl::TM + g.Mg - 1) / g.Mg : 1;
-    const int ch = g.G > 1 && spans * g.Cg + 32 < g.C ? spans * g.Cg + 32 : g.C;
-    const int nch = g.R * g.S * ((ch + 31) / 32);
-    const double whole = whole_cost(c, tiles, c.resident, nch);
-    const int S = g.G > 1 ? 0 : stream_k_size(tiles, c.resident, nch);
+    const double whole = whole_cost(c, tiles, c.resident, g.R * g.S * mean_channels(g, Tl::TM) / 32);
+    const int nch = g.R * g.S * (g.C / 32), S = g.G > 1 ? 0 : stream_k_size(tiles, c.resident, nch);
     if (S <= 0) return whole;
     double shared = shared_cost(c, tiles, c.resident, nch, S);
     if (with_fetch) {
@@ -166,14 +174,11 @@ bool split_pays(const Geom &g) {
         if constexpr (Tl::SK_FORM) conv = split_cost<Tl>(sp, false);
         return 0;
     });
-    // the channels a tile of grouped layers walks
-    int tm = 0;
+    double k = 0;
     with_tile(f32, true, [&](auto t) {
-        tm = decltype(t)::TM;
+        k = g.R * g.S * mean_channels(g, decltype(t)::TM);
         return 0;
     });
-    const int spans = std::min(g.G, (tm + 2 * g.Mg - 2) / g.Mg);
-    const double k = (double)g.R * g.S * (g.G > 1 ? std::min(g.C, spans * g.Cg + 32) : g.C);
     const Work w = work_of(f32, true, k);
     // rounds of eight images past the last one read it again
     const double again = w.d * ((g.N + 7) / 8 * 8 - g.N) / g.N;

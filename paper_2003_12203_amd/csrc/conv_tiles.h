@@ -213,7 +213,7 @@ inline int stream_k_size(long long tiles, int resident, int nch) {
     if (fill >= resident) return resident;
     return fill / 8 * 8 > tiles ? (int)(fill / 8 * 8) : 0;
 }
-inline double whole_cost(const TileCost &t, long long tiles, int resident, int nch) {
+inline double whole_cost(const TileCost &t, long long tiles, int resident, double nch) {
     const long long full = tiles / resident, rem = tiles % resident;
     const double busy = (double)rem / resident;
     return full * (nch * (t.chunk_idle + t.chunk_busy) + t.tile) +

@@ -25,7 +25,7 @@ CASES = [
     ("alexnet", "conv2", 1, False, 1),    # fp32 128 x 256 on split copies (the largest AlexNet layer), stream-K
     ("alexnet", "conv2", 1, True, 1),     # ... with a bias in the epilogue (Sec. 5.1)
     ("alexnet", "conv2", 2, False, 1),    # fp32 128 x 128 on split copies, grouped channel skip (Sec. 5.2)
-    ("alexnet", "conv4", 2, False, 1),    # fp32 128 x 128 on split copies, grouped channel skip
+    ("alexnet", "conv4", 2, False, 1),    # fp32 64 x 64 on split copies, grouped channel skip (192 filters a group)
     ("vgg19", "v10", 1, True, 1),         # fp32 128 x 256 on split copies, with a bias, stream-K
     ("vgg19_bf16", "v1", 1, False, 1),    # bf16 64 x 256, NCHW
     ("resnet18", "l1.0", 1, False, 1),    # bf16 64 x 128, direct-to-LDS

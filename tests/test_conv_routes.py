@@ -88,3 +88,11 @@ SPLIT = [((16, 256, 52, 52, 128, 1, 1, 1, 0), 1),         # Darknet-19 c7: fp32 
 def test_split_copies_where_they_pay(shape, groups):
     t = _loop(shape, "f32", groups)
     assert t["nhwc"] and (t["loop"] in (3, 4)) == ((shape, groups) in SPLIT), t
+
+
+def test_grouped_tiles_count_both_groups_they_straddle():
+    # 192 filters a group: every third tile of 128 walks two groups' channels (AlexNet conv4, 141 us against 134)
+    t = _loop((64, 384, 13, 13, 384, 3, 3, 1, 1), "f32", 2)
+    assert (t["tm"], t["tp"], t["group_skip"]) == (64, 64, True), t
+    t = _loop((64, 384, 13, 13, 256, 3, 3, 1, 1), "f32", 2)   # 128 a group: none straddles
+    assert t["tm"] == 128, t

@@ -98,6 +98,7 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     pl->ver_splits = row_splits(rows_o, ceil_div(cols_v, ctt), 1024, 32);
     if (pl->ver_splits > part_cap) pl->ver_splits = part_cap > 1 ? (int)part_cap : 1;
     g.split = g.pk = g.prun = g.pcs = g.pw = g.pupt = g.pkk = 0;
+    g.sk = allow_sk;
     if (allow_nhwc && (allow_split || g.dtype == FTCNN_BF16)) pack_geom(g);
     if (g.pk) {
         g.split = g.dtype == FTCNN_F32;

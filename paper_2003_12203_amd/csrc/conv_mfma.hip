@@ -45,7 +45,7 @@ template <typename Tl> double split_cost(const Geom &g, bool with_fetch) {
     constexpr TileCost c = tile_cost<Tl>();
     const long long tiles = n_tiles(g, Tl::TM, Tl::TP);
     const double whole = whole_cost(c, tiles, c.resident, g.R * g.S * mean_channels(g, Tl::TM) / 32);
-    const int nch = g.R * g.S * (g.C / 32), S = g.G > 1 ? 0 : stream_k_size(tiles, c.resident, nch);
+    const int nch = g.R * g.S * (g.C / 32), S = g.G > 1 || !g.sk ? 0 : stream_k_size(tiles, c.resident, nch);
     if (S <= 0) return whole;
     double shared = shared_cost(c, tiles, c.resident, nch, S);
     if (with_fetch) {

@@ -35,6 +35,7 @@ struct Geom {
     // up to eight.  prun = 1: a tap is a whole kernel row, its S columns of pcs (4 or 8) channels run on
     // in memory, and the copy carries the zero columns of the padding.
     int pk, prun, pcs, pw, pupt, pkk;
+    int sk;   // the plan may hold stream-K scratch: tiles are chosen for sharing too
 };
 // bytes of one value in the channels-last copies
 __host__ __device__ inline int copy_bytes(const Geom &g) { return g.dtype == FTCNN_BF16 ? 2 : (g.split ? 6 : 4); }

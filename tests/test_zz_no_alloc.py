@@ -2,8 +2,8 @@
 callers that cannot allocate) against ftcnn_protected_conv with a caller's workspace, through the
 C ABI, on two calls in a row whose second input is smaller:
 
-1. a layer whose channels-last workspace exceeds the 128 MiB static scratch, so the call takes the
-   plan without channels-last copies: O within the output tolerance of the workspace call's O (the
+1. a layer whose workspace exceeds the 128 MiB static scratch even with plain fp32 copies, so the call
+   takes the plan without channels-last copies: O within the output tolerance of the workspace call's O (the
    dot products are summed in another order), Cd1, Cd2, Co5..Co7 within float64 rounding of the
    workspace call's, So5..So7 and Q5 within float64 rounding of the oracle's summations of the
    call's own output (Sec. 3.6), both reports clean;
@@ -52,7 +52,7 @@ def _run_both(spec, D, W, corrupt_cw1=None):
 
 
 def test_noalloc_matches_workspace_entry_point_on_two_calls():
-    # call 1: 48 x 64 x 112 x 112 fp32, channels-last workspace ~170 MiB > 128 MiB
+    # call 1: 48 x 64 x 112 x 112 fp32: split copies 252 MiB, fp32 ones 168 MiB, both > 128 MiB
     big = wl.LayerSpec("big", 48, 64, 112, 112, 64, 3, 3, 1, 1, "f32")
     d = ft.make_desc(big.n, big.ch, big.h, big.w, big.m, big.r, big.s, big.stride, big.pad, big.dtype)
     assert ft.workspace_bytes(d) > (128 << 20), "the first layer must need the fallback plan"
@@ -98,3 +98,41 @@ def test_noalloc_bf16_after_fp32():
     assert torch.equal(O_na.view(torch.int16), O_ref.view(torch.int16))
     for k in CK_KEYS:
         np.testing.assert_array_equal(b_na[k], b_ref[k], err_msg=k)
+
+
+# layers whose workspace exceeds the scratch and that an earlier plan takes: (shape, groups, what fits)
+TIERS = [
+    ((14, 256, 56, 56, 256, 3, 3, 1, 1), 1),     # split copies without the stream-K scratch
+    ((32, 64, 112, 112, 64, 3, 3, 1, 1), 1),     # fp32 copies: 147 MiB split, 98 MiB fp32; M <= 64
+    ((32, 256, 56, 56, 256, 3, 3, 1, 1), 1),     # fp32 copies, M >= 128
+    ((32, 256, 56, 56, 256, 3, 3, 1, 1), 2),     # fp32 copies, the loop that skips the other group's channels
+]
+
+
+@pytest.mark.parametrize("shape,groups", TIERS, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else f"g{v}")
+def test_noalloc_plans_between(shape, groups):
+    n, ch, h, w, m, r, s, u, p = shape
+    print(f"[noalloc] {shape} groups {groups}", flush=True)
+    mk = lambda: ft.Layer(*shape, "f32", groups=groups)
+    ref, na = mk(), mk()
+    copies = 4 * (n * ch * h * w + m * ch * r * s)
+    assert copies < (128 << 20) and (1.5 * copies > (128 << 20) or ft.workspace_bytes(ref.desc) > (128 << 20))
+    g = torch.Generator(device="cuda").manual_seed(17)
+    D = torch.rand(shape[:4], generator=g, device="cuda")
+    W = torch.randn(m, ch // groups, r, s, generator=g, device="cuda") * 0.05
+    O, On = ref.empty_output(), na.empty_output()
+    for lay in (ref, na):
+        lay.encode_weights(W)
+    ref.protected(D, W, O)
+    ft.protected_conv_noalloc(na.desc, D, W, On, na.ck, na.policy, na.report, na.cap)
+    assert not ref.read_report().detected and not na.read_report().detected
+    # two orders of an fp32 sum: each within 2^-24 K of the sum of magnitudes, and D is in [0, 1)
+    K = ch // groups * r * s
+    assert ((On - O).abs().amax((0, 2, 3)) <= 2 * 2.0 ** -24 * K * W.abs().sum((1, 2, 3))).all()
+    for k in ("cd1", "cd2", "co5", "co6", "co7"):
+        assert_close_scaled(na.buf[k].cpu().numpy(), ref.buf[k].cpu().numpy(), 1e-11, k)
+    # the epilogue's sums, against float64 sums of the call's own output
+    s5 = sum(On[i].double().sum(0) for i in range(n)).reshape(-1)
+    q5 = sum(On[i].double().square().sum(0) for i in range(n)).sqrt().reshape(-1)
+    for k, want in (("so5", s5), ("q5", q5)):
+        assert_close_scaled(na.buf[k].cpu().numpy(), want.cpu().numpy(), 1e-11, k)

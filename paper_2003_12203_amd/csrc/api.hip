@@ -128,34 +128,25 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     off += align256(4ull * pl->ver_splits * EF * sizeof(double));
     pl->off_sums = off;
     off += align256(4ull * pl->sum_splits * EF * sizeof(double));
-    // channels-last copies of D and W for the vector-gather convolution; the copy of D encodes
-    // Cd1, Cd2 too, over image ranges when the layer has few tiles: enough ranges for about 1024
-    // workgroups, with at least 16 images (fp32) or 32 (bf16) a range, so that the float64 partial
-    // pairs (16 bytes per element of Cd) cost at most a quarter of D's traffic, and at most 16
+    // channels-last (or packed) copies of D and W for the convolution; their launch encodes Cd1, Cd2 too
     const size_t es = g.dtype == FTCNN_F32 ? 4 : 2, cs = copy_bytes(g);
-    pl->prep_ns = 1;
     pl->co_in_conv = false;
-    pl->co = CocTile{1, 1, 1, 1, 1, 1, 0, 1};
+    pl->co = CocTile{1, 1, 1, 1, 1, 1};
     if (pl->copies) {
-        // (packed copies: the encode is the copy's too, over all images at once)
-        const long long tiles = g.pk ? 1024 : (long long)(g.C / prep_tile_channels(g)) * ceil_div((long long)g.H * g.W, prep_tile_positions(g));
-        const int min_imgs = g.dtype == FTCNN_F32 ? 16 : 32;   // a multiple of both image batches
-        long long most = g.N / min_imgs;
-        most = most > 16 ? 16 : (most < 1 ? 1 : most);
-        pl->prep_ns = clampi(ceil_div(1024, tiles), 1, most);
-        // Where the copying workgroups are few (the images would be split into ranges of partial sums, or, in
-        // bf16, less than one a compute unit walks all images), the encode has workgroups of its own in
-        // the same launch, reading D a second time, and every round of images of the copy is a
-        // workgroup: bf16 VGG-19 v14 67 -> 61 us a protected layer, ResNet-18 l3 64.5 -> 60.5, its projection
-        // 36 -> 32.6 us; fp32 VGG-19 v14 170 -> 165 us.  With many, one pass over D is the better one (VGG-19 v6 bf16
-        // 158 against 161 us, Darknet-19 1x1 fp32 46 against 49 us).
-        pl->enc_apart = pl->nhwc && (pl->prep_ns > 1 || (g.dtype == FTCNN_BF16 && tiles < 256));
-        if (pl->enc_apart) pl->prep_ns = 1;
+        // Where the copying workgroups of a channels-last layer are few (less than four a compute unit that walk 32
+        // images or more in fp32, 64 in bf16; in bf16 less than one, however many the images), the encode has
+        // workgroups of its own in the same launch, reading D a second time, and every round of images of the
+        // copy is a workgroup: bf16 VGG-19 v14 67 -> 61 us a protected layer, ResNet-18 l3 64.5 -> 60.5, its
+        // projection 36 -> 32.6 us; fp32 VGG-19 v14 170 -> 165 us (against the images in ranges, whose partial sums
+        // the next launch added).  With many, one pass over D is the better one (VGG-19 v6 bf16 158 against
+        // 161 us, Darknet-19 1x1 fp32 46 against 49 us).
+        if (pl->nhwc) {
+            const long long wgs = (g.C / prep_tile_channels(g)) * ceil_div((long long)g.H * g.W, prep_tile_positions(g));
+            const int many = g.dtype == FTCNN_F32 ? 32 : 64;
+            pl->enc_apart = (wgs < 4 * kComputeUnits && g.N >= many) || (g.dtype == FTCNN_BF16 && wgs < kComputeUnits);
+        }
         // Co5..Co7 in extra workgroups of the convolution launch, in its threads and LDS, where
-        // they hide behind the matrix-core tiles: on layers with many taps to evaluate (E*F*K of
-        // at least 1M; one pass per image range when the input checksums come split) and on
-        // every layer whose input checksums are whole.  On the others (small and split) the
-        // final launch evaluates the taps itself.
+        // they hide behind the matrix-core tiles; else the final launch evaluates the taps itself.
         int nt = 0, sk_smax = 0;
         size_t lds = 0, sk_bytes = 0;
         long long sk_counters = 0;
@@ -165,14 +156,16 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
         co.tx = g.F >= 24 ? 32 : (g.F >= 12 ? 16 : 8);
         co.ty = nt / co.tx < g.E ? nt / co.tx : g.E;
         while (co.ty > 1 && coc_channel_bytes(g, co.ty, co.tx) > lds) co.ty /= 2;
-        // (where whole tiles take a compute unit each and their last round leaves next to none free, they
-        // come after it: AlexNet conv4, 255 tiles, 156 us with the taps in the final launch, 161 us with
-        // them)
+        // (where whole tiles take a compute unit each and their last round leaves fewer than an eighth of the units
+        // free, they would come after it: AlexNet conv4, 255 tiles, 156 us with the taps in the final launch, 161 us
+        // with these workgroups; fp32 41 x 32 x 28^2, 416 filters of 5 x 5 at stride 2, 252 tiles, 57 and 60.
+        // Layers of many taps have them all the same: E*F*K of 1M)
         int tile[6];
         conv_tile_info(g, true, tile);
-        const long long last = ceil_div(g.P_total, tile[1]) * ceil_div(g.M, tile[0]) % 256;
-        const bool behind = pl->enc_apart && 2 * lds > (160u << 10) && sk_smax == 0 && (last == 0 || last > 224);
-        if (((pl->prep_ns == 1 && !behind) || EF * K >= (1LL << 20)) && coc_channel_bytes(g, co.ty, co.tx) <= lds) {
+        const long long last = ceil_div(g.P_total, tile[1]) * ceil_div(g.M, tile[0]) % kComputeUnits;
+        const bool whole_unit = 2 * lds > kUnitLds;   // a tile takes a compute unit
+        const bool behind = pl->enc_apart && whole_unit && sk_smax == 0 && (last == 0 || last > kComputeUnits * 7 / 8);
+        if ((!behind || EF * K >= (1LL << 20)) && coc_channel_bytes(g, co.ty, co.tx) <= lds) {
             pl->co_in_conv = true;
             const size_t cc = lds / coc_channel_bytes(g, co.ty, co.tx);
             co.cc = (int)(cc < 8 ? cc : 8);
@@ -182,14 +175,12 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
             // one after another: fewer channels each until there are about 192 of them, of at least 24 taps a
             // position (bf16 9 x 64 x 37^2, 288 filters of 5 x 5: 52 -> 39 us; 4 x 64 x 43^2, 432 of 7 x 7: 66
             // -> 54)
-            if (2 * lds > (160u << 10)) {
+            if (whole_unit) {
                 const long long few = std::max((long long)g.C * co.tiles / 192, 24LL / (g.R * g.S));
                 co.cc = clampi(few, 1, co.cc);
             }
             co.groups = clampi(ceil_div(768, co.tiles), 1, ceil_div(g.C, co.cc));
         }
-        co.ns = pl->prep_ns;
-        co.comb_blocks = pl->prep_ns > 1 ? (int)ceil_div(CHW, 2LL * nt) : 0;
     }
     // 256 zero bytes for loads that fall outside the operands (written by the copy), directly in
     // front of Dt: the direct-to-LDS loads reach both through one buffer descriptor
@@ -199,10 +190,8 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     off += pl->nhwc ? align256((size_t)g.N * CHW * cs) : (g.pk ? align256((size_t)g.N * g.H * g.pw * g.pcs * cs) : 0);
     pl->off_wt = off;
     off += pl->nhwc ? align256((size_t)g.M * K * cs) : (g.pk ? align256((size_t)g.M * g.pkk * cs) : 0);
-    pl->off_encp = off;
-    off += pl->prep_ns > 1 ? align256(2ull * pl->prep_ns * CHW * sizeof(double)) : 0;
     pl->off_copart = off;
-    off += pl->co_in_conv ? align256(3ull * pl->co.groups * pl->prep_ns * EF * sizeof(double)) : 0;
+    off += pl->co_in_conv ? align256(3ull * pl->co.groups * EF * sizeof(double)) : 0;
     pl->off_corr = off;
     off += align256(corr_layout(g, pl->corr_stride).bytes);
     pl->off_wchk = off;   // Cw1, Cw2 re-encoded by ftcnn_check_weights

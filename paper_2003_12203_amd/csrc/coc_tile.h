@@ -1,18 +1,11 @@
 // Work that extra workgroups of the convolution launch do beside its
-// matrix-core tiles when the layer's input checksums were encoded by the
-// channels-last copy that precedes it (Sec. 3.2):
+// matrix-core tiles when the launch of the copies that precedes it has encoded
+// the layer's input checksums (Sec. 3.2): the checksum-of-checksum products at
+// every output position, Co5 = Cd1 (x) Cw1, Co6 = Cd1 (x) Cw2,
+// Co7 = Cd2 (x) Cw1, as partial products over ranges of input channels; the
+// final detection launch adds the slices in order.
 //
-//   combine   Cd1, Cd2 = the image-split partial sums of that copy, added in
-//             split order (only when the images were split);
-//   CoC       the checksum-of-checksum products of Sec. 3.2 at every output
-//             position, Co5 = Cd1 (x) Cw1, Co6 = Cd1 (x) Cw2, Co7 = Cd2 (x) Cw1,
-//             as partial products over ranges of input channels and, when the
-//             images were split, over the image ranges (the products are linear
-//             in Cd1 and Cd2, so each image range's partial checksums give their
-//             share); the final detection launch adds the slices in order.
-//
-// A CoC workgroup owns a tile of output positions, one channel range and one
-// image range (or the combined Cd when the images were not split).  For
+// A workgroup owns a tile of output positions and one channel range.  For
 // each group of cc channels it stages the tile's input window of Cd1 and Cd2
 // (float64, zero outside the feature map) in LDS, then every thread evaluates
 // the R x S taps of its own position from there: each checksum element is read
@@ -23,71 +16,17 @@
 
 namespace ftcnn {
 
-// Sources of Cd1 and Cd2 for the extra workgroups: final arrays (ns = 1) or
-// image-split partials [ns][2][Ch*H*W] (p2 = p1 + Ch*H*W, stride = 2*Ch*H*W).
-struct CdSrc {
-    const double *p1, *p2;
-    long long stride;
-    int ns;
-};
-
-// One combine workgroup: 2*NT consecutive elements of Cd1 and Cd2, each the sum of
-// its ns image-range partials added in range order; four ranges of loads (sixteen
-// values a thread) are in flight at a time.
-template <int NT>
-__device__ inline void combine_block(const Geom &g, const CdSrc &src, double *__restrict__ cd1,
-                                     double *__restrict__ cd2, int blk) {
-    const long long base = (long long)blk * 2 * NT + threadIdx.x;
-    long long idx[2];
-    bool in[2];
-    double a[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        idx[e] = base + e * NT;
-        in[e] = idx[e] < g.CHW;
-        if (!in[e]) idx[e] = 0;
-    }
-    for (int s0 = 0; s0 < src.ns; s0 += 4) {
-        double x[4][2][2];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const long long off = (long long)(s0 + u < src.ns ? s0 + u : 0) * src.stride;
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                x[u][e][0] = src.p1[off + idx[e]];
-                x[u][e][1] = src.p2[off + idx[e]];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (s0 + u < src.ns)
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    a[e][0] += x[u][e][0];
-                    a[e][1] += x[u][e][1];
-                }
-    }
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-        if (in[e]) {
-            cd1[idx[e]] = a[e][0];
-            cd2[idx[e]] = a[e][1];
-        }
-}
-
-// One CoC workgroup (blk < tiles * groups * ns), using lds (cc channels of
-// coc_channel_bytes).  Writes slice (group * ns + split) of copart
-// [groups * ns][3][E*F]: the share of Co5, Co6, Co7 at the tile's positions of
-// one channel range and one image range.  Each thread sums its taps in the fixed
-// order (channel, r, s).  The window is staged eight elements a thread at a
+// One CoC workgroup (blk < tiles * groups), using lds (cc channels of
+// coc_channel_bytes).  Writes slice `group` of copart [groups][3][E*F]: the
+// share of Co5, Co6, Co7 at the tile's positions of one channel range.  Each
+// thread sums its taps in the fixed order (channel, r, s).  The window is staged eight elements a thread at a
 // time (sixteen loads in flight), with the Cw1, Cw2 taps of the channels beside it.
 template <int NT>
-__device__ inline void coc_block(const Geom &g, const CocTile &ct, const CdSrc &src, const double *__restrict__ cw1,
+__device__ inline void coc_block(const Geom &g, const CocTile &ct, const double *__restrict__ cd1,
+                                 const double *__restrict__ cd2, const double *__restrict__ cw1,
                                  const double *__restrict__ cw2, double *__restrict__ copart, int blk,
                                  double *lds) {
-    const int tile = blk % ct.tiles, gs = blk / ct.tiles;
-    const int grp = gs / src.ns, split = gs - grp * src.ns;
-    const double *p1 = src.p1 + (long long)split * src.stride, *p2 = src.p2 + (long long)split * src.stride;
+    const int tile = blk % ct.tiles, grp = blk / ct.tiles;
     const int bx = tile / ct.tiles_x, by = tile - (tile / ct.tiles_x) * ct.tiles_x;
     const int x0 = bx * ct.ty, y0 = by * ct.tx;
     const int rows = ct.ty < g.E - x0 ? ct.ty : g.E - x0;
@@ -120,8 +59,8 @@ __device__ inline void coc_block(const Geom &g, const CocTile &ct, const CdSrc &
                 const int ih = ih0 + i, iw = iw0 + j;
                 ok[u] = c < nc && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
                 const long long idx = ok[u] ? ((long long)(cb + c) * g.H + ih) * g.W + iw : 0;
-                a1[u] = p1[idx];
-                a2[u] = p2[idx];
+                a1[u] = cd1[idx];
+                a2[u] = cd2[idx];
                 j += sj;
                 i += si;
                 c += sc;
@@ -162,7 +101,7 @@ __device__ inline void coc_block(const Geom &g, const CocTile &ct, const CdSrc &
     }
     if (mine) {
         const int p = (x0 + tyi) * g.F + y0 + txi;
-        double *o = copart + (size_t)gs * 3 * g.EF + p;
+        double *o = copart + (size_t)grp * 3 * g.EF + p;
         o[0] = c5;
         o[g.EF] = c6;
         o[2 * (size_t)g.EF] = c7;

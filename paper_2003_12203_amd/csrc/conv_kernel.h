@@ -931,10 +931,8 @@ __global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T
                     if (ep.aux_kind == 1) {
                         if (ep.enc_vec) encode_block<T, C::NT, kEncVec>(D, g, bid, ep.cd1, ep.cd2);
                         else encode_block<T, C::NT, 1>(D, g, bid, ep.cd1, ep.cd2);
-                    } else if (bid < ep.co.comb_blocks) {
-                        combine_block<C::NT>(g, ep.src, ep.cd1, ep.cd2, bid);
                     } else {
-                        coc_block<C::NT>(g, ep.co, ep.src, ep.cw1, ep.cw2, ep.copart, bid - ep.co.comb_blocks,
+                        coc_block<C::NT>(g, ep.co, ep.cd1, ep.cd2, ep.cw1, ep.cw2, ep.copart, bid,
                                          reinterpret_cast<double *>(smem));
                     }
                 }

@@ -70,11 +70,11 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
     if (nhwc && g.pk) {
         if (g.dtype == FTCNN_BF16) {
             if (g.M <= 64) return n_tiles(g, 64, 256) >= 512 ? f(BF16P_64x256{}) : f(BF16P_64x128{});
-            return n_tiles(g, 128, 128) >= 256 ? f(BF16P_128x128{}) : f(BF16P_64x64{});
+            return n_tiles(g, 128, 128) >= kComputeUnits ? f(BF16P_128x128{}) : f(BF16P_64x64{});
         }
         if (g.M <= 32) return f(S3P_32x128{});
         if (g.M <= 64) return f(S3P_64x128{});
-        if (g.M <= 96 && n_tiles(g, 96, 256) >= 256) return f(S3P_96x256{});
+        if (g.M <= 96 && n_tiles(g, 96, 256) >= kComputeUnits) return f(S3P_96x256{});
         return n_tiles(g, 128, 128) >= 128 ? f(S3P_128x128{}) : f(S3P_64x64{});
     }
     const bool wide = g.R > 32 || g.S > 32;
@@ -99,18 +99,18 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
         // groups' channels (192 filters a group: 64-row tiles)
         if (g.G > 1 && g.Mg % 128 != 0 && g.Mg % 64 == 0) return f(F32_64x64{});
         // the tile with the least predicted time: the padded outputs (tiles x TM x TP), plus half of
-        // the idle slots in the last round of 256 tiles, at the tile's own rate per output
+        // the idle slots in the last round of a tile a compute unit, at the tile's own rate per output
         // (128 x 128 : 128 x 64 : 64 x 64 = 1 : 0.972 : 0.925).  The one-half and the rates are
         // fitted to VGG-19 (224^2 .. 14^2, batch 32) and Darknet-19 (104^2 .. 13^2, batch 16),
         // where they pick the fastest of the three on every layer or one within 1%; 128 x 128
         // needs at least 600 tiles and 128 x 64 one a compute unit (fewer hide too little latency)
         const auto cost = [](long long tiles, double tile_outputs, double rate) {
-            const long long slots = (tiles + 255) / 256 * 256;
+            const long long slots = (tiles + kComputeUnits - 1) / kComputeUnits * kComputeUnits;
             return ((double)tiles + 0.5 * (double)(slots - tiles)) * tile_outputs / rate;
         };
         const long long t128 = n_tiles(g, 128, 128), t12864 = n_tiles(g, 128, 64);
         const double c64 = cost(n_tiles(g, 64, 64), 64.0 * 64.0, 0.925);
-        const double c12864 = t12864 >= 256 ? cost(t12864, 128.0 * 64.0, 0.972) : 1e300;
+        const double c12864 = t12864 >= kComputeUnits ? cost(t12864, 128.0 * 64.0, 0.972) : 1e300;
         const double c128 = t128 >= 600 ? cost(t128, 128.0 * 128.0, 1.0) : 1e300;
         if (c128 <= c12864 && c128 <= c64) return f(F32_128x128{});
         if (c12864 <= c64) return f(F32_128x64{});
@@ -120,7 +120,7 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
     if (g.M <= 32) return f(BF16_M32{});
     if (dma && wide) return g.M <= 64 ? f(BF16W_64x128{}) : f(BF16W_128x128{});
     // at most two 64 x 64 tiles a compute unit: nothing larger would fill it
-    if (dma && n_tiles(g, 64, 64) <= 512) return f(BF16_DMA_64x64_3{});
+    if (dma && n_tiles(g, 64, 64) <= 2 * kComputeUnits) return f(BF16_DMA_64x64_3{});
     // M <= 64 with 64-channel multiples: direct-to-LDS 64 x 128 (against register-staged loads,
     // VGG-19 v2 384 -> 308 us and ResNet-18 l1 109 -> 90 us for the convolution alone, before the
     // tile went from 64 x 256 to 64 x 128)
@@ -128,7 +128,7 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
     if (dma) {
         // 256 x 256 where M is large and there are enough such tiles
         if (g.M >= 256 && n_tiles(g, 256, 256) >= 192) return f(BF16_DMA_256x256{});
-        if (n_tiles(g, 128, 128) < 256) return f(BF16_DMA_128x128_3{});
+        if (n_tiles(g, 128, 128) < kComputeUnits) return f(BF16_DMA_128x128_3{});
         return f(BF16_DMA_128x128{});
     }
     if (g.M >= 256 && n_tiles(g, 256, 256) >= 192) return f(BF16_256x256{});
@@ -283,7 +283,6 @@ hipError_t launch_conv_sums(const Plan &pl, const void *D, const void *W, void *
     const void *Dc = D, *Wc = W;
     const void *zp = pl.copies ? w + pl.off_zero : nullptr;   // zeroed by the copy
     int aux_kind = 0, aux_blocks = 0, co_slices = 0;
-    CdSrc src{cd1, cd2, 0, 1};
     if (pl.copies) {
         // the copy of D also encodes Cd1, Cd2 (if asked and not given)
         double *e1 = cd_given ? nullptr : cd1, *e2 = cd_given ? nullptr : cd2;
@@ -291,34 +290,24 @@ hipError_t launch_conv_sums(const Plan &pl, const void *D, const void *W, void *
         if (e != hipSuccess) return e;
         Dc = w + pl.off_dt;
         Wc = w + pl.off_wt;
-        if (cd1) {
-            // given checksums are whole: no image-range partials to combine
-            const int ns = cd_given ? 1 : pl.prep_ns;
-            if (ns > 1) {
-                const double *p1 = reinterpret_cast<const double *>(w + pl.off_encp);
-                src = CdSrc{p1, p1 + pl.g.CHW, 2 * pl.g.CHW, ns};
-            }
-            const bool coc = pl.co_in_conv && ck->cw1 && ck->cw2;
-            const int comb = ns > 1 ? pl.co.comb_blocks : 0;
-            aux_blocks = comb + (coc ? pl.co.tiles * pl.co.groups * ns : 0);
-            aux_kind = aux_blocks > 0 ? 2 : 0;
-            co_slices = coc ? pl.co.groups * ns : 0;
+        if (cd1 && pl.co_in_conv && ck->cw1 && ck->cw2) {
+            aux_kind = 2;
+            aux_blocks = pl.co.tiles * pl.co.groups;
+            co_slices = pl.co.groups;
         }
     } else if (cd1 && !cd_given) {
         aux_kind = 1;   // encode workgroups; their count follows the tile's threads
     }
-    CocTile co = pl.co;
-    if (pl.prep_ns == 1 || cd_given) co.comb_blocks = 0;
     double *part = reinterpret_cast<double *>(w + pl.off_sums);
     double *copart = reinterpret_cast<double *>(w + pl.off_copart);
     const double *cw1 = ck ? ck->cw1 : nullptr, *cw2 = ck ? ck->cw2 : nullptr;
     const float *bias = ck ? ck->bias : nullptr;
     if (nf == 0) {
-        Epi<1> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, src, cw1, cw2, copart, co, co_slices, {}, bias, {D, W}};
+        Epi<1> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, cw1, cw2, copart, pl.co, co_slices, {}, bias, {D, W}};
         return with_tile(pl.g, pl.copies,
                          [&](auto t) { return decltype(t)::run(pl.g, Dc, Wc, O, st, ep, pl.copies, zp, sk_args(pl, ws)); });
     }
-    Epi<2> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, src, cw1, cw2, copart, co, co_slices, {}, bias, {D, W}};
+    Epi<2> ep{part, rep, cap, aux_kind, aux_blocks, 0, 0, cd1, cd2, 0, cw1, cw2, copart, pl.co, co_slices, {}, bias, {D, W}};
     for (int i = 0; i < nf; ++i) ep.fl.f[i] = faults[i];
     ep.fl.n = nf;
     return with_tile(pl.g, pl.copies,

@@ -71,10 +71,10 @@ struct Cfg {
 // that runs beside the matrix-bound tiles of the same launch:
 //   aux_kind 1: encode the input checksums Cd1, Cd2 of D (Sec. 3.2), in the first
 //               groups of the grid (they read D as the first tiles do);
-//   aux_kind 2: combine the image-split partials of Cd1, Cd2 left by the
-//               channels-last copy, and compute the Co5..Co7 partial products
-//               (coc_tile.h), in the last groups, after the tile_groups groups of
-//               tiles, where they fill the slots the tiles' last round leaves.
+//   aux_kind 2: the Co5..Co7 partial products (coc_tile.h) of Cd1, Cd2 left by the
+//               launch of the copies, in the last groups, after the tile_groups
+//               groups of tiles, where they fill the slots the tiles' last round
+//               leaves.
 struct NoFaults {};
 // D and (dense) W as given, for layers on split copies
 struct Given {
@@ -102,10 +102,9 @@ template <int EPI> struct Epi {
     int cap;
     int aux_kind, aux_blocks, aux_groups;
     int tile_groups;     // groups of eight tile workgroups in front of the aux_kind 2 ones
-    double *cd1, *cd2;   // kind 1: encoded here; kind 2: written by the combine workgroups
+    double *cd1, *cd2;   // kind 1: encoded here; kind 2: read
     int enc_vec;         // kind 1: 16-byte loads
-    CdSrc src;           // kind 2
-    const double *cw1, *cw2;
+    const double *cw1, *cw2;   // kind 2
     double *copart;
     CocTile co;
     int co_slices;       // Co partial slices this launch writes (recorded in rep->reserved[1])
@@ -227,12 +226,12 @@ inline int stream_k_workgroups(const TileCost &t, long long tiles, int resident,
     const int S = stream_k_size(tiles, resident, nch);
     return S > 0 && shared_cost(t, tiles, resident, nch, S) < whole_cost(t, tiles, resident, nch) ? S : 0;
 }
-template <typename Tl> constexpr TileCost tile_cost() { return TileCost{256, 1.0, 0.0, 4.0, 20.0}; }
-template <> constexpr TileCost tile_cost<S3_128x256>() { return TileCost{256, 1.35, 0.85, 4.0, 18.0}; }
-template <> constexpr TileCost tile_cost<S3_128x128>() { return TileCost{256, 0.75, 0.38, 6.0, 25.0}; }
-template <> constexpr TileCost tile_cost<S3_64x64>() { return TileCost{512, 0.60, 0.02, 2.0, 14.0}; }
-template <> constexpr TileCost tile_cost<S3_64x128>() { return TileCost{512, 0.80, 0.20, 2.0, 16.0}; }
-template <> constexpr TileCost tile_cost<S3_32x128>() { return TileCost{512, 0.60, 0.10, 2.0, 14.0}; }
+template <typename Tl> constexpr TileCost tile_cost() { return TileCost{kComputeUnits, 1.0, 0.0, 4.0, 20.0}; }
+template <> constexpr TileCost tile_cost<S3_128x256>() { return TileCost{kComputeUnits, 1.35, 0.85, 4.0, 18.0}; }
+template <> constexpr TileCost tile_cost<S3_128x128>() { return TileCost{kComputeUnits, 0.75, 0.38, 6.0, 25.0}; }
+template <> constexpr TileCost tile_cost<S3_64x64>() { return TileCost{2 * kComputeUnits, 0.60, 0.02, 2.0, 14.0}; }
+template <> constexpr TileCost tile_cost<S3_64x128>() { return TileCost{2 * kComputeUnits, 0.80, 0.20, 2.0, 16.0}; }
+template <> constexpr TileCost tile_cost<S3_32x128>() { return TileCost{2 * kComputeUnits, 0.60, 0.10, 2.0, 14.0}; }
 
 }  // namespace convk
 }  // namespace ftcnn

@@ -1288,10 +1288,10 @@ hipError_t run_fused(const Plan &pl, const void *D, const void *W, void *O, cons
     da.wide_done = reinterpret_cast<int *>(w + pl.off_corr + L.done);
     // Co5..Co7 of a channels-last layer come as partial slices from the convolution launch
     // (the kernel checks rep->reserved[1] and falls back to the taps)
-    const int taps = coc ? (pl.co_in_conv ? pl.co.groups * pl.prep_ns : pl.g.K) : 0;
+    const int taps = coc ? (pl.co_in_conv ? pl.co.groups : pl.g.K) : 0;
     const int tpp = final_tpp(sp, taps, pl.g.EF);
     da.copart = reinterpret_cast<const double *>(w + pl.off_copart);
-    da.max_groups = pl.co_in_conv ? pl.co.groups * pl.prep_ns : 0;
+    da.max_groups = pl.co_in_conv ? pl.co.groups : 0;
     da.co5 = ck.co5; da.co6 = ck.co6; da.co7 = ck.co7;
     da.so5 = ck.so5; da.so6 = ck.so6; da.so7 = ck.so7; da.q5 = ck.q5;
     const unsigned blocks = (unsigned)((pl.g.EF + kThreads / tpp - 1) / (kThreads / tpp));

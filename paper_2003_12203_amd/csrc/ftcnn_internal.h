@@ -41,18 +41,18 @@ struct Geom {
 __host__ __device__ inline int copy_bytes(const Geom &g) { return g.dtype == FTCNN_BF16 ? 2 : (g.split ? 6 : 4); }
 __host__ __device__ inline int group_first_channel(const Geom &g, int m) { return (m / g.Mg) * g.Cg; }
 
+// An MI355X: its compute units, and the LDS of one
+constexpr int kComputeUnits = 256;
+constexpr size_t kUnitLds = 160 << 10;
+
 // Tiling of the Co5..Co7 products computed by extra workgroups of the
 // convolution launch (channels-last layers): output tiles of tx columns (of F)
 // by ty rows (of E), cc channels staged in LDS per step, the channels split
-// into `groups` ranges and, when the input checksums come as ns image-range
-// partials, one workgroup per range as well (groups * ns partial slices);
-// comb_blocks workgroups combine those partials into Cd1, Cd2.
+// into `groups` ranges (a partial slice each).
 struct CocTile {
     int tx, ty, cc;
     int tiles_x, tiles;
     int groups;
-    int comb_blocks;
-    int ns;
 };
 // LDS one channel of a CoC workgroup takes: its input window of Cd1 and Cd2 for a
 // ty x tx tile of output positions, and its R*S taps of Cw1 and Cw2 (float64)
@@ -72,10 +72,9 @@ struct Plan {
     bool nhwc;                        // the convolution reads channels-last copies of D and W
     bool copies;                      // ... those, or packed ones (Geom::pk)
     bool enc_apart;                   // the encode in workgroups of the copy's launch that do not copy
-    int prep_ns;                      // image ranges of the encode fused into the channels-last copy
     bool co_in_conv;                  // Co5..Co7 partials computed by workgroups of the convolution launch
     CocTile co;                       // their tiling (co_in_conv)
-    size_t off_flags, off_enc, off_ver, off_sums, off_corr, off_dt, off_wt, off_encp, off_copart, off_zero,
+    size_t off_flags, off_enc, off_ver, off_sums, off_corr, off_dt, off_wt, off_copart, off_zero,
         off_wchk, off_wfull, bytes;
     int sk_smax;                      // stream-K workgroups the scratch has room for (0: none)
     size_t off_skpart, off_skcnt;     // their partial accumulators, and one arrival count per tile
@@ -346,9 +345,8 @@ inline int prep_tile_channels(const Geom &g) {
     return g.dtype == FTCNN_BF16 && g.C % 64 == 0 && (g.C / 64) * hw_tiles >= 512 ? 64 : 32;
 }
 // Dt = D in [n][h][w][c] order and Wt = W in [m][r][s][c] order into the workspace
-// (pl.off_dt, pl.off_wt); with cd1 and cd2 set, the copy of D also encodes them
-// (directly when pl.prep_ns == 1, else as image-split partials at pl.off_encp
-// that the convolution launch combines into cd1 and cd2).
+// (pl.off_dt, pl.off_wt); with cd1 and cd2 set, the same launch encodes them
+// (in the copying workgroups, or with pl.enc_apart in others).
 hipError_t launch_prep(const Plan &pl, const void *D, const void *W, double *cd1, double *cd2, void *ws,
                        hipStream_t st);
 // The copies of a packed layer (Geom::pk) into the workspace (pl.off_dt, pl.off_wt); with cd1 and cd2 set,

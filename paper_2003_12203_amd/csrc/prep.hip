@@ -7,11 +7,10 @@
 // The copy of D also encodes the input checksums of Sec. 3.2,
 //   Cd1 = sum_n D_n,   Cd2 = sum_n (n + wbase) D_n,
 // from the values it moves, so D is read once for both.  A workgroup owns a
-// tile of 32 (or 64) channels x TH positions of the feature maps and walks a
-// range of images in order, keeping the running float64 sums of its tile in
-// registers; layers with few tiles split the images into ranges (one partial
-// pair per range, combined in a fixed order by the convolution launch that
-// follows).
+// tile of 32 (or 64) channels x TH positions of the feature maps and walks the
+// images in order, keeping the running float64 sums of its tile in registers.
+// On layers with few tiles (Plan::enc_apart) other workgroups of the launch
+// encode, and each round of images of a tile is a workgroup.
 //
 // Every global access is a 16-byte vector.  A channel row of the tile is read
 // as eight aligned vectors.  When H*W is a multiple of the vector the row
@@ -87,8 +86,7 @@ __device__ inline int xcd_run(int b, int total) {
 template <typename T, bool ENC, int TC, bool SHIFT, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D, const T *__restrict__ W,
                                                         T *__restrict__ Dt, T *__restrict__ Wt, Geom g,
-                                                        double *cd1, double *cd2, long long split_stride,
-                                                        int tr_blocks, int hw_tiles, int c_tiles, int ns, int vec_d,
+                                                        double *cd1, double *cd2, int tr_blocks, int hw_tiles, int c_tiles, int ns, int vec_d,
                                                         int vec_w, uint4 *__restrict__ zero16, int *__restrict__ skcnt,
                                                         int skcnt_n, int enc_blocks, int enc_vec) {
     using P = PrepT<T, TC, SHIFT>;
@@ -222,7 +220,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const T *__restrict__ D,
         if constexpr (ENC) {
             // element v of the thread's vector is position rel + v of its row; each position of the
             // tile is in exactly one vector of the row
-            double *o1 = cd1 + (long long)split * split_stride, *o2 = cd2 + (long long)split * split_stride;
+            double *o1 = cd1, *o2 = cd2;
 #pragma unroll
             for (int q = 0; q < RPT; ++q) {
                 const long long row = (long long)(ct * TC + cr + 32 * q) * HW;
@@ -337,7 +335,7 @@ hipError_t run_tc(const Plan &pl, const void *D, const void *W, double *cd1, dou
     const long long hw_tiles = (HW + P::TH - 1) / P::TH, c_tiles = g.C / TC;
     // without the encode in the copying workgroups every round of images is a workgroup of its own
     const bool apart = cd1 && pl.enc_apart;
-    const int ns = cd1 && !apart ? pl.prep_ns : (g.N + P::BATCH - 1) / P::BATCH;
+    const int ns = cd1 && !apart ? 1 : (g.N + P::BATCH - 1) / P::BATCH;
     const int enc_vec = reinterpret_cast<uintptr_t>(D) % (kEncVec * sizeof(T)) == 0;
     const long long per = (long long)kThreads * (enc_vec ? kEncVec : 1);
     const long long enc_blocks = apart ? (g.CHW + per - 1) / per : 0;
@@ -347,21 +345,13 @@ hipError_t run_tc(const Plan &pl, const void *D, const void *W, double *cd1, dou
     const long long tr = (long long)ns * c_tiles * hw_tiles;
     const long long grid = enc_blocks + tr + g.M;
     if (grid > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    double *o1 = cd1, *o2 = cd2;
-    long long stride = 0;
-    if (cd1 && !apart && ns > 1) {
-        // image-split partials [ns][2][Ch*H*W], combined by the convolution launch
-        o1 = reinterpret_cast<double *>(w + pl.off_encp);
-        o2 = o1 + g.CHW;
-        stride = 2 * g.CHW;
-    }
     if (cd1 && !apart)
         prep_kernel<T, true, TC, SHIFT, SPLIT><<<(unsigned)grid, kThreads, 0, st>>>(
-            static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, o1, o2, stride, (int)tr, (int)hw_tiles,
+            static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, cd1, cd2, (int)tr, (int)hw_tiles,
             (int)c_tiles, ns, vec_d, vec_w, zero16, skcnt, skcnt_n, 0, 0);
     else
         prep_kernel<T, false, TC, SHIFT, SPLIT><<<(unsigned)grid, kThreads, 0, st>>>(
-            static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, cd1, cd2, 0, (int)tr,
+            static_cast<const T *>(D), static_cast<const T *>(W), Dt, Wt, g, cd1, cd2, (int)tr,
             (int)hw_tiles, (int)c_tiles, ns, vec_d, vec_w, zero16, skcnt, skcnt_n, (int)enc_blocks, enc_vec);
     return hipGetLastError();
 }

@@ -220,9 +220,9 @@ def test_protected_conv_single_call(li):
         np.testing.assert_allclose(one[k], two[k], rtol=0, atol=1e-12 * float(Q.max()) * max(spec.n, spec.m))
 
 
-# Layers with many images and few 32 x 32 feature-map tiles: the channels-last copy encodes Cd1,
-# Cd2 over several image ranges, the convolution launch combines them and computes the Co5..Co7
-# partials from them (ranges of 16 images in fp32, 32 in bf16; uneven ranges with n = 50).
+# Layers with many images and few 32 x 32 feature-map tiles: workgroups of their own in the
+# channels-last copy's launch encode Cd1, Cd2, and a copying workgroup takes a round of images (the
+# last one a short round with n = 50); the convolution launch computes the Co5..Co7 partials.
 SPLIT_SHAPES = [
     # n, ch, h, m, r, stride, pad, dtype
     (64, 32, 9, 40, 3, 1, 1, "f32"),
@@ -231,8 +231,7 @@ SPLIT_SHAPES = [
     (64, 64, 7, 48, 3, 1, 1, "bf16"),
     (96, 64, 6, 70, 3, 2, 1, "bf16"),
 ]
-# split images on layers with E*F*K of at least 1M: Co5..Co7 in the convolution launch, one pass
-# per image range
+# the same with many taps to evaluate (E*F*K of at least 1M)
 SPLIT_COC_SHAPES = [
     (32, 32, 64, 32, 3, 1, 1, "f32"),
     (64, 64, 48, 64, 3, 1, 1, "bf16"),
@@ -254,7 +253,7 @@ def _split_spec(shape):
 @pytest.mark.parametrize("shape", SPLIT_SHAPES + SPLIT_COC_SHAPES + FEW_CHANNELS,
                          ids=lambda s: "n{}-c{}-h{}-m{}-r{}-u{}-{}".format(*s[:6], s[7]))
 def test_image_split_encode_integer_exact(shape):
-    """Integer data: the combined image-range partials are exactly Cd1, Cd2, and the Co5..Co7
+    """Integer data: Cd1, Cd2 are exactly the sums over the images, and the Co5..Co7
     partial products of the convolution launch add up exactly to the summations of O."""
     spec = _split_spec(shape)
     D, W = wl.gen_int_d(spec, 11), wl.gen_int_w(spec, 11)

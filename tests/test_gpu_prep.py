@@ -26,13 +26,13 @@ SHAPES = [
     # n, ch, h, m, r, u, p, dtype
     (4, 64, 14, 32, 3, 1, 1, "bf16"),     # H*W = 196: shifted rows
     (6, 64, 7, 64, 3, 1, 1, "bf16"),      # H*W = 49: odd
-    (64, 32, 7, 32, 3, 1, 1, "bf16"),     # two image ranges
+    (64, 32, 7, 32, 3, 1, 1, "bf16"),     # encoded by workgroups of their own, many images
     (3, 32, 16, 32, 3, 2, 1, "bf16"),     # H*W = 256: aligned rows
     (2, 64, 170, 16, 3, 1, 1, "bf16"),    # 64-channel tiles with shifted rows
     (2, 64, 184, 16, 3, 1, 1, "bf16"),    # 64-channel tiles, aligned rows
     (3, 32, 13, 48, 3, 1, 1, "f32"),      # H*W = 169
     (2, 32, 27, 40, 5, 1, 2, "f32"),      # H*W = 729
-    (40, 32, 9, 32, 1, 1, 0, "f32"),      # two image ranges, 1x1
+    (40, 32, 9, 32, 1, 1, 0, "f32"),      # many images, 1x1
     (3, 64, 12, 32, 3, 1, 1, "f32"),      # H*W = 144: aligned rows
 ]
 

@@ -133,17 +133,19 @@ int make_plan(const ftcnn_conv_desc *d, Plan *pl, bool allow_nhwc = true, bool a
     pl->co_in_conv = false;
     pl->co = CocTile{1, 1, 1, 1, 1, 1};
     if (pl->copies) {
-        // Where the copying workgroups of a channels-last layer are few (less than four a compute unit that walk 32
+        // Where the copying workgroups of a channels-last layer are few (less than two a compute unit that walk 32
         // images or more in fp32, 64 in bf16; in bf16 less than one, however many the images), the encode has
         // workgroups of its own in the same launch, reading D a second time, and every round of images of the
-        // copy is a workgroup: bf16 VGG-19 v14 67 -> 61 us a protected layer, ResNet-18 l3 64.5 -> 60.5, its
-        // projection 36 -> 32.6 us; fp32 VGG-19 v14 170 -> 165 us (against the images in ranges, whose partial sums
-        // the next launch added).  With many, one pass over D is the better one (VGG-19 v6 bf16 158 against
-        // 161 us, Darknet-19 1x1 fp32 46 against 49 us).
+        // copy is a workgroup.  Protected layers, one pass over D and apart: bf16 VGG-19 v14 60.4 and 53.4 us,
+        // ResNet-18 l3 81.2 and 55.2, its projection 54.2 and 28.9; fp32 AlexNet conv4 172.8 and 163.2.  Between one
+        // and two a compute unit either is up to 8 % the faster (fp32 VGG-19 v10 609 and 605 us, 32 x 512 x 28^2,
+        // 128 filters 1x1 57 and 62; bf16 64 x 64 x 100^2 147 and 139, 64 x 64 x 112^2 176 and 182).  With more, one
+        // pass is: fp32 VGG-19 v6 617 and 640, 32 x 512 x 40^2, 256 filters 1x1 161 and 178; bf16 64 x 128 x 112^2
+        // 416 and 435, 64 x 512 x 64^2, 128 filters 1x1 222 and 262; of 15 such layers three were 2 to 4 % slower.
         if (pl->nhwc) {
             const long long wgs = (g.C / prep_tile_channels(g)) * ceil_div((long long)g.H * g.W, prep_tile_positions(g));
             const int many = g.dtype == FTCNN_F32 ? 32 : 64;
-            pl->enc_apart = (wgs < 4 * kComputeUnits && g.N >= many) || (g.dtype == FTCNN_BF16 && wgs < kComputeUnits);
+            pl->enc_apart = (wgs < 2 * kComputeUnits && g.N >= many) || (g.dtype == FTCNN_BF16 && wgs < kComputeUnits);
         }
         // Co5..Co7 in extra workgroups of the convolution launch, in its threads and LDS, where
         // they hide behind the matrix-core tiles; else the final launch evaluates the taps itself.

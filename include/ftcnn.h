@@ -183,7 +183,7 @@ const char *ftcnn_last_error(void);
  * between the matrix-core instructions, 2 two chunks in flight, 3 direct-to-LDS loads,
  * 4 the same with three stages, 5 and 6 like 3 and 4 from packed copies, 7 like 3 for
  * kernels above 32 rows or columns; an fp32 layer on 3 to 7 multiplies bf16 planes),
- * out[4] = 1 when the convolution reads channels-last copies, out[5] = 1 when its tiles
+ * out[4] = 1 when the convolution reads copies of D and W, out[5] = 1 when its tiles
  * skip the channels of other groups (grouped layers).  Lets a test check that it covers
  * every kernel a set of layers runs. */
 int ftcnn_conv_tile(const ftcnn_conv_desc *desc, int32_t path, int32_t out[6]);
@@ -227,7 +227,7 @@ int ftcnn_conv_fwd(const ftcnn_conv_desc *desc, const void *D, const void *W, vo
 /* Eq. (1) plus a bias (Sec. 5.1): O[n][m][x][y] = (eq. (1)) + bias[m], added to the fp32
  * accumulator before O is rounded to the layer dtype.  bias: device, fp32 [m].  With a
  * workspace (ftcnn_workspace_bytes) the convolution runs through the kernels of the
- * protected path (channels-last copies on layers whose ch is a multiple of 32), so O is
+ * protected path (ftcnn_conv_fwd_ws), so O is
  * bitwise that of ftcnn_conv_fwd_sums with the same bias; with NULL, through those of
  * ftcnn_conv_fwd. */
 int ftcnn_conv_fwd_bias(const ftcnn_conv_desc *desc, const void *D, const void *W, const float *bias,
@@ -278,16 +278,17 @@ int ftcnn_verify_correct(const ftcnn_conv_desc *desc, const void *D, const void 
                          int32_t cap_fixes, void *workspace, hipStream_t stream);
 
 /* Eq. (1) as ftcnn_conv_fwd, through the path the protected calls below use:
- * for layers with ch a multiple of 32, D and W are first copied channels-last
- * into the workspace (D as [n][h][w][ch], W as [m][r][s][ch]) so that the
- * convolution gathers 16-byte runs; K is then summed in (r, s, ch) order, so
+ * D and W are first copied into the workspace so that the convolution reads
+ * 16-byte runs: channels-last (D as [n][h][w][ch], W as [m][r][s][ch]) on layers with ch
+ * a multiple of 32, packed (taps of padded channels) on those of other counts that are
+ * predicted to be faster so; the rest take ftcnn_conv_fwd's kernel.  K is then summed in (r, s, ch) order, so
  * O may differ from ftcnn_conv_fwd's in the last bits (both are eq. (1) with
- * fp32 accumulation; fp32 copies hold every value as three bf16 planes whose sum it
- * is, six of whose nine products the matrix cores add up, the other three being below
- * an fp32 rounding of the product; outputs that this leaves non-finite, which besides
- * infinities and NaN are those of operands from 2e31 or sums from 1.2e24, are computed again
- * from D and W with fp32 products, at about a quarter of the speed).  O is bitwise that of
- * ftcnn_conv_fwd_sums.  Other layers take ftcnn_conv_fwd's kernel.  Needs the workspace of ftcnn_workspace_bytes. */
+ * fp32 accumulation).  Where it is predicted to be faster, fp32 copies hold every value as three
+ * bf16 planes whose sum it is, six of whose nine products the matrix cores add up, the other
+ * three being below an fp32 rounding of the product; outputs that this leaves non-finite, which
+ * besides infinities and NaN are those of operands from 2e31 or sums from 1.2e24, are computed
+ * again from D and W with fp32 products, at about a quarter of the speed.  O is bitwise that of
+ * ftcnn_conv_fwd_sums.  Needs the workspace of ftcnn_workspace_bytes. */
 int ftcnn_conv_fwd_ws(const ftcnn_conv_desc *desc, const void *D, const void *W, void *O,
                       void *workspace, hipStream_t stream);
 
@@ -299,10 +300,10 @@ int ftcnn_conv_fwd_ws(const ftcnn_conv_desc *desc, const void *D, const void *W,
  * recorded).  Follow it with ftcnn_verify_correct_sums on the same workspace
  * and report.
  * ck: may be NULL.  When ck->cd1 and ck->cd2 are set, Cd1 and Cd2 are encoded
- * from D as ftcnn_encode(which = 0) does (Sec. 3.2): by the channels-last copy
- * of D as it moves the values, or by extra workgroups beside the matrix-core
- * tiles.  When ck->cw1 and ck->cw2 (the encoded W) are set as well, layers
- * with ch a multiple of 32 also compute the products Co5, Co6, Co7 of Sec. 3.2
+ * from D as ftcnn_encode(which = 0) does (Sec. 3.2): by the launch that copies
+ * D, or by extra workgroups beside the matrix-core tiles of layers without copies.
+ * When ck->cw1 and ck->cw2 (the encoded W) are set as well, most layers
+ * with copies also compute the products Co5, Co6, Co7 of Sec. 3.2
  * in extra workgroups of the convolution launch, as per-channel-range partials
  * in the workspace that ftcnn_verify_correct_sums(which = CO5|CO6|CO7) adds up.
  * Other members are not used.
@@ -317,7 +318,7 @@ int ftcnn_conv_fwd_sums(const ftcnn_conv_desc *desc, const void *D, const void *
 /* ftcnn_conv_fwd_sums for a layer whose input checksums are already encoded:
  * ck->cd1 and ck->cd2 (required) hold Cd1, Cd2 of D as inputs, for instance from
  * ftcnn_relu_pool_encode of the layer before (Sec. 3.2), and are not written.  The
- * channels-last copy of D then only copies, and no encode or combine workgroups run;
+ * copies are then only copies, and no encode workgroups run;
  * everything else is as ftcnn_conv_fwd_sums (same O, same sums, Co5..Co7 partials when
  * ck->cw1 and ck->cw2 are set).  Follow it with ftcnn_verify_correct_sums. */
 int ftcnn_conv_fwd_sums_given(const ftcnn_conv_desc *desc, const void *D, const void *W, void *O,
@@ -338,9 +339,9 @@ int ftcnn_verify_correct_sums(const ftcnn_conv_desc *desc, const void *D, const 
                               uint32_t which, void *workspace, hipStream_t stream);
 
 /* The whole path of one protected layer on one stream:
- * conv_fwd_sums (with the encode of Cd1, Cd2, and Co5..Co7 on channels-last
- * layers) -> verify_correct_sums (with Co5..Co7): two launches, three for
- * channels-last layers.  ck->cw1/cw2 must hold the encoded W (ftcnn_encode with
+ * conv_fwd_sums (with the encode of Cd1, Cd2, and Co5..Co7 on most layers with
+ * copies) -> verify_correct_sums (with Co5..Co7): three launches, four for
+ * layers with copies, one more on grouped ones.  ck->cw1/cw2 must hold the encoded W (ftcnn_encode with
  * which = 1); ck->cd1, cd2, co5..co7, so5..so7 and q5 are written. */
 int ftcnn_protected_conv(const ftcnn_conv_desc *desc, const void *D, const void *W, void *O,
                          const ftcnn_checksums *ck, const ftcnn_policy *policy,
@@ -348,12 +349,13 @@ int ftcnn_protected_conv(const ftcnn_conv_desc *desc, const void *D, const void 
                          hipStream_t stream);
 
 /* ftcnn_protected_conv for callers that cannot allocate device memory (code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc): the same two or three
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * launches with no workspace argument.  Scratch comes from a static device array of the
  * library, 128 MiB on each device, which that device holds from the first call there until
  * the process ends; nothing is allocated or freed by the call.  The call uses the plan of
  * ftcnn_protected_conv when that plan's workspace (ftcnn_workspace_bytes) fits the array, and
- * otherwise the plan without channels-last copies, whose convolution gathers from D as given
+ * otherwise the first that does of: that plan without scratch for shared tiles, the one on
+ * fp32 copies, the one without copies, whose convolution gathers from D as given
  * (the same results within the output tolerance; K summed in (ch, r, s) order); a layer that
  * needs more than 128 MiB even then is rejected with FTCNN_E_WORKSPACE before any launch.
  * The device is the stream's (the current device for the NULL stream).  Every call on one

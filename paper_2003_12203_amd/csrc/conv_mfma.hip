@@ -8,21 +8,25 @@ namespace ftcnn {
 using namespace convk;
 namespace {
 
-// Tile choice per layer, from sweeps over the workload shapes on MI355X.  The filter tile follows M so
-// small-M layers waste no MFMA rows.
+// Tile choice per layer, from sweeps over the workload shapes and drawn layers on MI355X.  The filter tile
+// follows M so small-M layers waste no MFMA rows.
 //
-// fp32 channels-last layers run on split copies (three bf16 planes a value, six products): the bf16
-// matrix cores do six products in 3/8 of the time the fp32 ones take for one, and errors are no larger
-// (VGG-19 v6: 951 -> 505 us for the convolution, 124 -> 235 TFLOP/s against 157 of the fp32 matrix cores;
-// distance from float64 8.0e-7 -> 7.2e-7).  Their tile and its schedule are the ones with the least
-// predicted time (TileCost).  The other fp32 layers take 128 x 128, 128 x 64 or 64 x 64 fp32 tiles.
+// fp32 layers of 32-channel multiples run on split copies (three bf16 planes a value, six products) where
+// that is predicted to be the faster (split_pays): the bf16 matrix cores do six products in 3/8 of the time
+// the fp32 ones take for one, and errors are smaller (VGG-19 v6 protected: 1010 -> 647 us, distance from
+// float64 7.7e-7 -> 2.1e-7 of the norm).  Their tile and its schedule are the ones with the least
+// predicted time (split_cost).  The others take fp32 copies: 64 x 256 tiles for M <= 64, else 128 x 128,
+// 128 x 64 or 64 x 64.
 //
-// bf16 channels-last layers with 64-channel multiples take direct-to-LDS loads (WEAVE 3): 64 x 128 tiles
-// for M <= 64, 256 x 256 tiles (eight waves of 128 x 64) for M >= 256 where there are enough of them,
+// bf16 layers of 64-channel multiples take direct-to-LDS loads from channels-last copies (WEAVE 3, 4): 64 x 128
+// tiles for M <= 64, 256 x 256 tiles (eight waves of 128 x 64) for M >= 256 where there are enough of them,
 // 128 x 128 elsewhere, through three stages where they would not fill the compute units, and 64 x 64
-// where those are few; layers of other channel counts run on packed copies through the same loop, and
-// the rest (short sums, small layers, copies past 32-bit offsets) take 64 x 256, 256 x 256 or 128 x 128
-// tiles with register-staged loads, two chunks in flight (WEAVE 2).
+// where those are few.
+//
+// Layers of other channel counts run on packed copies through the same loops (WEAVE 5, 6) where that is
+// predicted to be the faster (pack_pays).  The rest (most short sums and small layers, copies past 32-bit
+// offsets) load through registers: bf16 64 x 256, 256 x 256 or 128 x 128 tiles with two chunks in flight
+// (WEAVE 2), from channels-last copies (32-channel multiples) or D and W as given; fp32 tiles as above.
 long long n_tiles(const Geom &g, int tm, int tp) {
     return ((g.P_total + tp - 1) / tp) * (long long)((g.M + tm - 1) / tm);
 }

@@ -76,7 +76,7 @@ struct Cfg {
 //               groups of tiles, where they fill the slots the tiles' last round
 //               leaves.
 struct NoFaults {};
-// D and (dense) W as given, for layers on split copies
+// D and (dense) W as given, for the outputs that a tile of split or packed copies computes again from them
 struct Given {
     const void *d, *w;
 };
@@ -148,9 +148,9 @@ using F32_128x128 = Tile<F32T<16>, 2, 2, 2, 2, true>;
 using F32_128x64 = Tile<F32T<32>, 2, 2, 2, 1, true>;
 using F32_64x64 = Tile<F32T<32>, 2, 2, 1, 1, true>;
 // fp32 on split copies.  128 x 256: eight waves of 64 x 64, a two-stage ring of 72 KB stages; 128 x 128:
-// eight waves of 64 x 32, three stages of 48 KB (two stages 4-8 % slower: a chunk's loads then have one
-// short chunk to land; VGG-19 v14 149 -> 144 us, Darknet-19 c14 141 -> 133 us); 64 x 64, three stages: layers
-// of few tiles; 64 x 128 and 32 x 128: few filters.
+// eight waves of 64 x 32, three stages of 48 KB (with two a chunk's loads have one short chunk to land: Darknet-19 1x1 43.4 -> 44.0 us
+// protected, AlexNet conv4 163 in both); 64 x 64, three stages: layers of few tiles; 64 x 128 and 32 x 128: few
+// filters.
 using S3_128x256 = Tile<S3T<32>, 2, 4, 2, 2, 3>;
 using S3_128x128 = Tile<S3T<32>, 2, 4, 2, 1, 4>;
 using S3_64x64 = Tile<S3T<32>, 2, 2, 1, 1, 4>;
@@ -196,8 +196,9 @@ using BF16_DMA_256x256 = Tile<BF16T<64>, 2, 4, 4, 2, 3>;
 // What a split layer's tiles take (us), as measured on one MI355X: chunk_idle + chunk_busy * (share of the
 // chip's slots in use) a chunk, since busy matrix cores lower the clock, `tile` a tile beyond its
 // chunks, and `shared` more where tiles are shared (publishing a workgroup's part and summing a
-// tile's parts).  Fitted to VGG-19 v4..v14, Darknet-19 c9..c14, AlexNet conv2..conv4 and batch-1 layers,
-// where the predictions lie within 10 %.
+// tile's parts).  Fitted to VGG-19 v4..v14, Darknet-19 c9..c14, AlexNet conv2..conv4 and batch-1 layers within
+// 10 %, before a step's products were summed from zero, which takes 4 to 8 % more on every tile; the choices
+// need the tiles' times only relative to each other.
 struct TileCost {
     int resident;   // workgroups on the chip at once
     double chunk_idle, chunk_busy, tile, shared;

@@ -69,11 +69,11 @@ template <int STEP> __device__ inline void store_split8(const float (&x)[8], uin
 
 // Workgroup b's tile of `total`: each XCD (ids are dealt round-robin over 8) takes a run of neighbouring
 // tiles, whose reads and stores then share lines in one L2.  The copies are bound by memory; with tiles
-// dealt out by id, protected layers took: VGG-19 v2 fp32 1026 -> 999 us, v4 725 -> 708, Darknet-19 1x1
-// 46.3 -> 44.2, AlexNet conv4 165.8 -> 163.0; bf16 ResNet-18 l3 59.4 -> 57.1, its projection 31.1 -> 28.9,
-// VGG-19 v6 unchanged in both types.  Channel blocks before positions within a run: v2 992, 1x1 45.8.
-// Packed copies keep the id order (with runs: AlexNet conv1 156 -> 161 us, 105 channels 199.3 -> 200.5, 160
-// channels 1x1 48.9 -> 46.4).
+// dealt out by id, protected layers took longer: VGG-19 v2 fp32 1062 us (in runs 1038), v4 733 (715), Darknet-19
+// 1x1 45.3 (43.4), AlexNet conv4 165.8 (163.2); bf16 VGG-19 v2 359 (351), ResNet-18 l3 57.4 (55.2), its
+// projection 31.0 (28.9); VGG-19 v6 the same in both types, Darknet-19 c4 87.7 (89).  Channel blocks before
+// positions within a run: v2 1 % faster, 1x1 4 % slower.  Packed copies keep the id order (with runs AlexNet
+// conv1 was 3 % slower, 160 channels 1x1 5 % faster).
 __device__ inline int xcd_run(int b, int total) {
     const int q = total / 8, rem = total % 8, x = b % 8;
     return x * q + (x < rem ? x : rem) + b / 8;

@@ -665,9 +665,10 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     // bits far below the largest one's, towards one side: adding the products to the accumulators
     // themselves left errors of up to 9.8e-7 of the norm (K = 4608, one filter; fp32 instructions 8.7e-7), all
     // leaning to one side.  So: 3.0e-7 there, VGG-19 v6 at batch 32 2.1e-7 (before 7.1e-7, fp32 instructions
-    // 7.9e-7), means within 2e-9 (the weights' signs, split_weight_scale).  It costs 4 to 8 % of a split
-    // layer's time (protected, one box: v6 639 -> 675 us, v2 1002 -> 1083, AlexNet conv4 165 -> 173, conv1
-    // 161 -> 169, Darknet-19 1x1 43.9 -> 45.5).
+    // 7.9e-7), means within 2e-9 (the weights' signs, split_weight_scale).  It costs 3 to 7 % of a split
+    // layer's time (protected, one box: v6 617 -> 630 us, v2 969 -> 1003, v4 693 -> 732, AlexNet conv4 159 -> 167,
+    // conv1 158 -> 165, Darknet-19 1x1 42.8 -> 44.1), of layers of a few 64 x 64 tiles, whose waves run alone, up
+    // to 16 % (packed 30 %).
     // part holds NBUF blocks' sums in turn; with two, a block's additions go between the next one's products
     // (one: 2 % slower; three filter blocks a wave leave no registers for two).
     constexpr int NBUF = NP == 1 ? 1 : (FM > 2 ? 1 : 2);
@@ -896,13 +897,16 @@ template <> struct Bits<uint16_t> {
     __device__ static float value(B b) { return bf16_bits_to_f32(b); }
 };
 
+// Two waves a SIMD at least on split tiles, as their LDS has room for: with up to 256 registers a lane the
+// compiler keeps the steps' sums (dma_mainloop) in VGPRs, with more in AGPRs, from where every value takes a copy
+// before its addition (protected: VGG-19 v2 1038 us, so 1003; 2 x 288 x 13^2 in two groups, 80 filters of 7 x 7, 64 x
+// 64 tiles 223, so 192; fp32 instructions 877).
 template <typename Tr, int WM, int WP, int FM, int FP, int WEAVE, bool KVEC, int EPI, bool NHWC, bool GRP = false,
           bool SK = false>
-__global__ __launch_bounds__(64 * WM * WP) void conv_kernel(const typename Tr::T *__restrict__ D,
-                                                            const typename Tr::T *__restrict__ Wt,
-                                                            typename Tr::T *__restrict__ O, Geom g,
-                                                            int tiles_m, int tiles_total, int m_major,
-                                                            const void *zp, Epi<EPI> ep, SkArgs sk) {
+__global__ __launch_bounds__(64 * WM * WP, Tr::NP == 3 || WM * WP > 4 ? 2 : 1)
+void conv_kernel(const typename Tr::T *__restrict__ D, const typename Tr::T *__restrict__ Wt,
+                 typename Tr::T *__restrict__ O, Geom g, int tiles_m, int tiles_total, int m_major, const void *zp,
+                 Epi<EPI> ep, SkArgs sk) {
     using C = Cfg<Tr, WM, WP, FM, FP, KVEC, dma_stages(WEAVE)>;
     using T = typename C::T;
     extern __shared__ __align__(16) unsigned char smem[];

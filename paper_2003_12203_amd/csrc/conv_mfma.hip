@@ -56,8 +56,8 @@ template <typename Tl> double split_cost(const Geom &g, bool with_fetch) {
         // Workgroups that share tiles are at chunks of their own, and no L2 serves two of them: the operands' bytes
         // bound the shared tiles, at about 14 TB/s from the Infinity Cache and half of that past its size, and
         // such a layer takes a larger tile (protected, 16 x 512 x 14^2, 512 filters of 3 x 3: 64 x 64 tiles 141 us,
-        // 128 x 256 117; 3 x 608 x 43^2, 448 of 11 x 11 at stride 4: 438 and 376; 9 x 352 x 74^2, 320 of 11 x 11 at
-        // stride 4: 1031 and 697)
+        // 128 x 128 116; 3 x 608 x 43^2, 448 of 11 x 11 at stride 4: 438 and 363; 9 x 352 x 74^2, 320 of 11 x 11 at
+        // stride 4: 1031, 128 x 256 697)
         const long long waves = (tiles + S - 1) / S, rest = tiles - (waves > 2 ? waves - 2 : 0) * S;
         const double copies = 6.0 * ((double)g.N * (double)g.CHW + (double)g.M * g.K);
         const double fetch = (double)rest * nch * (Tl::TM + Tl::TP) * 192 / (copies < 128e6 ? 14e6 : 7e6);
@@ -143,7 +143,7 @@ auto with_tile(const Geom &g, bool nhwc, Fn &&f) {
 
 namespace {
 // What a protected layer takes (us) on a route is a sum of these, with coefficients fitted to layers drawn over the
-// workloads' ranges (1040 fp32 ones of 32, 64, ... channels; 373 of other counts in each type; 200 bf16 ones of 32,
+// workloads' ranges (840 fp32 ones of 32, 64, ... channels; 373 of other counts in each type; 200 bf16 ones of 32,
 // 96, ...), batch 1 to 128: rms 8 to 14 % for the copies, 19 to 32 % for the gathers.
 struct Work {
     double d, w, o, cd;  // MB of D, W and O as given, and of Cd1 and Cd2
@@ -186,9 +186,9 @@ bool split_pays(const Geom &g) {
     const Work w = work_of(f32, true, k);
     // rounds of eight images past the last one read it again
     const double again = w.d * ((g.N + 7) / 8 * 8 - g.N) / g.N;
-    const double split = 13.5 + 0.76 * w.d + 0.32 * again + 0.94 * w.w + 0.43 * w.o + 0.83 * conv;
+    const double split = 10.9 + 0.77 * w.d + 0.37 * again + 0.89 * w.w + 0.27 * w.o + 0.99 * conv;
     const double whole = 16.3 + 0.48 * w.d + 0.28 * again + 0.19 * w.o + std::max(20.0 * w.mac, 0.047 * w.k);
-    return split < 1.05 * whole;   // the least mean time over the drawn layers
+    return split < 1.1 * whole;   // (1.05 and 1.1: the least mean time over the drawn layers)
 }
 
 bool pack_pays(const Geom &g) {

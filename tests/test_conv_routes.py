@@ -7,11 +7,12 @@ import paper_2003_12203_amd as ft
 
 # (n, ch, h, w, m, r, s, stride, pad), tile rows, pixels
 SHARED_TILES = [
-    ((16, 512, 14, 14, 512, 3, 3, 1, 1), 128, 256),     # 64 x 64 tiles 141, 117
-    ((3, 608, 43, 43, 448, 11, 11, 4, 5), 128, 256),    # 64 x 64 tiles 438, 376
+    ((16, 512, 14, 14, 512, 3, 3, 1, 1), 128, 128),     # 64 x 64 tiles 141, 116 (128 x 256: 119)
+    ((3, 608, 43, 43, 448, 11, 11, 4, 5), 128, 128),    # 64 x 64 tiles 438, 363 (128 x 256: 371)
     ((9, 352, 74, 74, 320, 11, 11, 4, 5), 128, 256),    # 64 x 64 tiles 1031, 697
     ((32, 512, 14, 14, 512, 3, 3, 1, 1), 128, 256),     # (VGG-19 v14: as before)
     ((1, 512, 7, 7, 512, 3, 3, 1, 1), 64, 64),          # (few outputs: as before)
+    ((64, 256, 13, 13, 256, 3, 3, 1, 1), 128, 128),     # 128 x 256 106, 92
 ]
 
 

@@ -63,6 +63,10 @@ template <typename Tl> double split_cost(const Geom &g, bool with_fetch) {
         const double fetch = (double)rest * nch * (Tl::TM + Tl::TP) * 192 / (copies < 128e6 ? 14e6 : 7e6);
         const double busy = (double)rest * nch / S * (c.chunk_idle + c.chunk_busy * S / c.resident);
         shared += std::max(fetch - busy, 0.0);
+        // and the last workgroup of a tile adds all its parts, at about 90 GB/s, which counts where they are many (6 x
+        // 960 x 58 x 19, 160 filters of 11 x 11 at stride 4: 254 us for the convolution on two 128 x 256 tiles of 113
+        // parts, 167 on twelve 64 x 64 ones)
+        shared += std::max((double)S / tiles - 32.0, 0.0) * Tl::TM * Tl::TP * 4 / 9e4;
     }
     return std::min(whole, shared);
 }
@@ -203,8 +207,9 @@ bool pack_pays(const Geom &g) {
         const double packed = 15.1 + 0.13 * copy + 0.78 * p.d + 0.51 * p.cd + 119 * p.cols + most(13.0 * p.mac, 0.0198 * p.k);
         const double gather = 10.5 + 0.37 * q.d + 0.42 * q.o + 0.61 * q.cd + (one ? 0.16 : 0.97) * q.fetch +
                               most(15.4 * q.mac, 0.082 * q.k);
-        // (small layers come out up to 8 us either side of the fit)
-        return packed < (gather < 45.0 ? 0.75 : 0.95) * gather;
+        // (small layers come out up to 8 us either side of the fit: of 158 drawn ones under 45 us, 0.85 leaves 6 more
+        // than 3 % slower than on the gather and takes 0.86 of its time on average; 0.75: 4 and 0.90; 0.95: 8 and 0.84)
+        return packed < (gather < 45.0 ? 0.85 : 0.95) * gather;
     }
     if (nhwc) {
         const double packed = 13.2 + 0.70 * p.d + 0.10 * p.o + 0.53 * p.cd + 38.3 * p.cols + most(3.67 * p.mac, 0.0085 * p.k);

@@ -13,6 +13,7 @@ SHARED_TILES = [
     ((32, 512, 14, 14, 512, 3, 3, 1, 1), 128, 256),     # (VGG-19 v14: as before)
     ((1, 512, 7, 7, 512, 3, 3, 1, 1), 64, 64),          # (few outputs: as before)
     ((64, 256, 13, 13, 256, 3, 3, 1, 1), 128, 128),     # 128 x 256 106, 92
+    ((6, 960, 58, 19, 160, 11, 11, 4, 0), 128, 128),    # two 128 x 256 tiles of 113 parts 354, 258
 ]
 
 

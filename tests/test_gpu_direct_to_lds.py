@@ -46,9 +46,9 @@ PACKED = {
     (8, 8, 40, 40, 64, 7, 7, 2, 3): ("64x128", "64x128"),
     (8, 2, 60, 60, 96, 15, 15, 2, 7): ("64x64", "64x64"),
     (8, 1, 80, 80, 70, 9, 9, 4, 6): (None, "64x64"),
-    (16, 6, 31, 32, 33, 7, 5, 3, 2): (None, "64x128"),
+    (16, 6, 31, 32, 33, 7, 5, 3, 2): ("64x128", "64x128"),
     (16, 3, 60, 61, 40, 5, 5, 1, 2): (None, "64x128"),
-    (2, 17, 29, 28, 100, 3, 3, 1, 1): (None, "64x64"),
+    (2, 17, 29, 28, 100, 3, 3, 1, 1): ("64x64", "64x64"),
     (3, 100, 25, 26, 70, 3, 3, 2, 1): ("64x64", "64x64"),
     (6, 105, 22, 23, 200, 1, 1, 1, 0): (None, "64x64"),
     (2, 9, 20, 20, 64, 15, 15, 1, 7): ("64x128", "64x128"),

@@ -666,7 +666,7 @@ __device__ inline void dma_mainloop(const void *__restrict__ Wt, const Geom &g, 
     // themselves left errors of up to 9.8e-7 of the norm (K = 4608, one filter; fp32 instructions 8.7e-7), all
     // leaning to one side.  So: 3.0e-7 there, VGG-19 v6 at batch 32 2.1e-7 (before 7.1e-7, fp32 instructions
     // 7.9e-7), means within 2e-9 (the weights' signs, split_weight_scale).  It costs 3 to 7 % of a split
-    // layer's time (protected, one box: v6 617 -> 630 us, v2 969 -> 1003, v4 693 -> 732, AlexNet conv4 159 -> 167,
+    // layer's time (protected: v6 617 -> 630 us, v2 969 -> 1003, v4 693 -> 732, AlexNet conv4 159 -> 167,
     // conv1 158 -> 165, Darknet-19 1x1 42.8 -> 44.1), of layers of a few 64 x 64 tiles, whose waves run alone, up
     // to 16 % (packed 30 %).
     // part holds NBUF blocks' sums in turn; with two, a block's additions go between the next one's products
